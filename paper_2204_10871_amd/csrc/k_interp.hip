@@ -1062,7 +1062,7 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
 // map, so the workgroup finds the bounding box of its landed pixels, counts
 // into an LDS histogram over that box and flushes each non-empty bin with one
 // global atomic; a box larger than the LDS histogram (rays scattered, as near
-// a lens) falls back to one global add per run of equal pixels in a lane.
+// a lens) takes a wrapped histogram instead (scatter_bins).
 // -------------------------------------------------------------------------
 constexpr int kL3Rows = 32;
 constexpr int kXcds = 8;               // MI355X: workgroups go to the 8 XCDs in turn
@@ -1477,13 +1477,80 @@ struct L3Map {
     int64_t corner_items[5];        // prefix of the corners' blocks of kThreads rays
 };
 
+// Binning of a tile whose landed-pixel box (origin bx0, by0) exceeds the LDS
+// histogram: a few of its rays passed close to a lens and landed far off, while
+// most still share a small patch.  The histogram then wraps: pixel (u, v) of
+// the box takes bin (u mod 64, v mod 64), so pixels of one 64 x 64 patch never
+// collide.  Each run of equal pixels down a lane's rows first writes its
+// pixel's wrap numbers as the bin's tag (one of the pixels that share a bin
+// wins); then runs whose pixel won the bin add to its LDS count, the others to
+// the map.  A tile counts at most 64 kL3Rows rays, so two 16-bit counts share a
+// word.  Called by every thread of the workgroup.
+//
+// Bound by the device-scope adds that reach the map.  With one add per run
+// (what these tiles did before) they were 8.0 of the 15.9 ms of level 3 at 1e5
+// lenses, 1.7e9 rays and 4096^2 pixels of 0.041 theta_E (runs of two rays);
+// merged in LDS first, level 3 takes 10.1 ms.  On the 1e6-lens map (runs of
+// eight) 418 -> 417 ms.
+constexpr int kWrapBits = 6, kWrap = 1 << kWrapBits, kWrapBins = kWrap * kWrap;
+static_assert(kWrapBins / 2 + kWrapBins <= kHistCap, "counts and tags share the histogram");
+static_assert(kWave * kL3Rows < 65536, "16-bit counts");
+
+__device__ __forceinline__ void scatter_bins(const int32_t *pxs, const int32_t *pys, int bx0,
+                                             int by0, int32_t npix, uint32_t *counts,
+                                             uint32_t *hist)
+{
+    constexpr int R = kL3RowsPerWave;
+    uint32_t *cnt = hist, *tag = hist + kWrapBins / 2;
+    for (int b = (int)threadIdx.x; b < kWrapBins / 2; b += kThreads) cnt[b] = 0u;
+    auto bin_of = [&](int k) {
+        return (uint32_t)(((pys[k] - by0) & (kWrap - 1)) << kWrapBits | ((pxs[k] - bx0) & (kWrap - 1)));
+    };
+    auto tag_of = [&](int k) {
+        return (uint32_t)((pys[k] - by0) >> kWrapBits << 16 | (pxs[k] - bx0) >> kWrapBits);
+    };
+    auto run_end = [&](int k) {               // row k ends a run of equal landed pixels
+        return pxs[k] >= 0 && (k == R - 1 || pxs[k] != pxs[k + 1] || pys[k] != pys[k + 1]);
+    };
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if (run_end(k)) tag[bin_of(k)] = tag_of(k);
+    __syncthreads();
+    uint32_t run = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        ++run;
+        if (run_end(k)) {
+            const uint32_t b = bin_of(k);
+            if (tag[b] == tag_of(k)) atomicAdd(&cnt[b >> 1], run << (16 * (b & 1u)));
+            else atomicAdd(&counts[pys[k] * npix + pxs[k]], run);
+        }
+        if (k + 1 < R && (pxs[k] != pxs[k + 1] || pys[k] != pys[k + 1])) run = 0;
+    }
+    __syncthreads();
+    for (int w = (int)threadIdx.x; w < kWrapBins / 2; w += kThreads) {
+        const uint32_t c = cnt[w];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t v = h ? c >> 16 : c & 0xffffu;
+            if (v) {
+                const int b = 2 * w + h;
+                const uint32_t t = tag[b];
+                const int x = bx0 + (int)((t & 0xffffu) << kWrapBits) + (b & (kWrap - 1));
+                const int y = by0 + (int)((t >> 16) << kWrapBits) + (b >> kWrapBits);
+                atomicAdd(&counts[y * npix + x], v);
+            }
+        }
+    }
+}
+
 // One tile of rays: columns tcol[tx] (one per lane) by rows trow[ty]
 // (kL3RowsPerWave per wave), restricted to rows [jr0, jr1).  Every ray: the
 // near lenses exactly, Horner of its level-2 point's C_0..C_4, the macro
 // term, beta and the pixel; BIN: binned through an LDS histogram over the
 // tile's landed-pixel box (flushed with one global atomic per non-empty bin),
-// or, for a box larger than the histogram, global adds by runs of equal
-// pixels down a lane's rows.  Called by every thread of the workgroup.
+// or, for a box larger than the histogram, the wrapped histogram of
+// scatter_bins.  Called by every thread of the workgroup.
 template <bool UNIT, bool BIN>
 __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t ty, L3Lds *lds)
 {
@@ -1614,22 +1681,8 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
     const int64_t area = (int64_t)(by1 - by0 + 1) << sh;
     uint32_t *counts = m.counts;
     if (area > kHistCap) {
-        // block-uniform fallback (rays scattered, as near a lens): global
-        // adds by runs of equal pixels down a lane's rows
-        int32_t cur = -1;
-        uint32_t run = 0;
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const int32_t pix = pxs[k] < 0 ? -1 : pys[k] * g.npix + pxs[k];
-            if (pix == cur) {
-                ++run;
-                continue;
-            }
-            if (cur >= 0) atomicAdd(&counts[cur], run);
-            cur = pix;
-            run = 1;
-        }
-        if (cur >= 0) atomicAdd(&counts[cur], run);
+        // rays scattered, as near a lens (block-uniform): a wrapped histogram
+        scatter_bins(pxs, pys, bx0, by0, g.npix, counts, lds->hist);
         return;
     }
     const int nbin = (int)area;
