@@ -386,12 +386,18 @@ irs_status irs_plan(const irs_params *params, int64_t n_lens, const double *x, c
         return st;
     }
     double msum = 0.0;
+    // extents for irs_plan_s::tame: with squared distances of 1e-70 .. 1e41
+    // products of four of them, quotients of a mass by one and their
+    // remainders are normal numbers
+    bool tame = std::max(hg.info.ix, hg.info.iy) < 1e20;
     for (int64_t i = 0; i < n_lens; ++i) {
         if (!std::isfinite(x[i]) || !std::isfinite(y[i]) || (m && !(std::isfinite(m[i]) && m[i] >= 0.0))) {
             set_error("irs_plan: lens positions must be finite and masses finite and >= 0");
             return IRS_E_INVALID;
         }
         msum += m ? m[i] : 1.0;
+        tame = tame && std::fabs(x[i]) < 1e20 && std::fabs(y[i]) < 1e20 &&
+               (!m || m[i] == 0.0 || (m[i] > 1e-100 && m[i] < 1e20));
     }
     if (params->method != IRS_DIRECT && n_lens > 0) {
         // the distant-field series hold for lenses inside their level-1 cells
@@ -417,6 +423,7 @@ irs_status irs_plan(const irs_params *params, int64_t n_lens, const double *x, c
     p->stream = (hipStream_t)hip_stream;
     p->n_lens = n_lens;
     p->unit_mass = (m == nullptr);
+    p->tame = tame;
     p->kappa_star_eff = M_PI * msum / (hg.info.ix * hg.info.iy);
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) {

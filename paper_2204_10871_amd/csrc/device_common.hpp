@@ -77,6 +77,8 @@ __device__ __forceinline__ double log_arg(double u, double v, bool top)
     return th;
 }
 
+constexpr double kHalfPiLo = 6.123233995736766e-17;      // pi/2 - M_PI_2
+
 // corner c's signed terms of I1 and I2 (corners (a1,b1) (a2,b1) (a2,b2) (a1,b2))
 __device__ __forceinline__ void sheet_unit_corner(const DevGeom &g, double t1, double t2, int c,
                                                   double &p1, double &p2)
@@ -86,8 +88,14 @@ __device__ __forceinline__ void sheet_unit_corner(const DevGeom &g, double t1, d
     const double sgn = (c == 0 || c == 2) ? 1.0 : -1.0;
     const double u = t1 - a, v = t2 - b;
     const double lr = log(u * u + v * v);
-    const double tu = (u != 0.0) ? u * atan(v / u) : 0.0;
-    const double tv = (v != 0.0) ? v * atan(u / v) : 0.0;
+    // atan(v/u) and atan(u/v) from one arctangent of the ratio of at most 1:
+    // they differ from its sign times pi/2 by each other
+    const bool steep = fabs(u) < fabs(v);
+    const double lo = steep ? u : v, hi = steep ? v : u;
+    const double q = hi != 0.0 ? lo / hi : 0.0;
+    const double t = atan(q);
+    const double o = (copysign(M_PI_2, q) - t) + copysign(kHalfPiLo, q);
+    const double tu = u * (steep ? o : t), tv = v * (steep ? t : o);
     const double lv = (v != 0.0) ? 0.5 * v * lr : 0.0;
     const double lu = (u != 0.0) ? 0.5 * u * lr : 0.0;
     p1 = sgn * (lv + tu);

@@ -75,44 +75,213 @@ __device__ __forceinline__ void emit(bool valid, int64_t out_idx, double a1, dou
 // FP64
 // -------------------------------------------------------------------------
 constexpr int kLens64 = 256;
+constexpr int64_t kRays4 = (int64_t)1 << 20;    // calls of at least this many rays: four a lane
 
-template <bool UNIT>
-__global__ __launch_bounds__(kThreads) void k_direct_f64(
-    DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
-    const double *__restrict__ lm, int32_t nl, int64_t r_begin, int64_t r_end,
-    int64_t out_base, double *a1o, double *a2o, int64_t *pixo, uint32_t *counts,
-    unsigned long long *landed)
+// Below this |theta_2 - y_i| a term takes the IEEE division: r^2 may be 0,
+// subnormal or too small for the refined reciprocals (a product of four r^2
+// has to stay a normal number).
+constexpr double kNear64 = 1e-35;
+
+// One lens's term for one ray, any r^2 (0 on the ray).
+__device__ __forceinline__ void term_any(double d1, double r2, double d2, double m, double &s1,
+                                         double &s2)
 {
-    __shared__ double s_x[kLens64], s_y[kLens64], s_m[UNIT ? 1 : kLens64];
+    if (r2 > 0.0) {
+        const double w = m / r2;
+        s1 += w * d1;
+        s2 += w * d2;
+    }
+}
+
+// m / r2, r2 and m (or m = 0) far from the ends of the exponent range: the
+// hardware estimate (2^-24) after one Newton step is within 2^-48 of 1/r2, and
+// the quotient corrected once with its exact remainder is the rounded
+// quotient, as the IEEE division's (which adds scaling and fix-up for the
+// ends of the range): before its rounding it is within 2^-94, so the two
+// differ for about one quotient in 2^41.
+template <bool UNIT>
+__device__ __forceinline__ double quotient(double m, double r2)
+{
+    double v = __builtin_amdgcn_rcp(r2);
+    v = fma(v, fma(-r2, v, 1.0), v);
+    const double q = UNIT ? v : m * v;
+    return fma(v, fma(-r2, q, m), q);
+}
+
+// m / r2[k] for four r2: the four estimates come from one reciprocal of their
+// product (refined once, 2^-48) by back-substitution through its prefixes;
+// each is then corrected with its own remainder as in quotient(), so the
+// quotients are rounded alike.
+template <bool UNIT>
+__device__ __forceinline__ void quotient4(double m, const double *r2, double *w)
+{
+    const double p1 = r2[0] * r2[1], p2 = p1 * r2[2], p = p2 * r2[3];
+    double v = __builtin_amdgcn_rcp(p);
+    v = fma(v, fma(-p, v, 1.0), v);
+    double e[4];
+    e[3] = v * p2;
+    v *= r2[3];
+    e[2] = v * p1;
+    v *= r2[2];
+    e[1] = v * r2[0];
+    e[0] = v * r2[1];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double q = UNIT ? e[k] : m * e[k];
+        w[k] = fma(e[k], fma(-r2[k], q, m), q);
+    }
+}
+
+// Lenses of a map staged in LDS, kLens64 at a time, by the whole workgroup.
+template <bool UNIT>
+struct Stage64 {
+    double2 xy[kLens64];
+    double m[UNIT ? 1 : kLens64];
+};
+
+// One lens for a lane's R rays of one row at d2 = theta_2 - y, |d2| >= kNear64.
+template <bool UNIT, int R>
+__device__ __forceinline__ void row_lens_far(double x, double d2, double m, const double *t1,
+                                             double *s1, double *s2)
+{
+    const double q2 = d2 * d2;
+    double d1[R], r2[R], w[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        d1[k] = t1[k] - x;
+        r2[k] = fma(d1[k], d1[k], q2);
+    }
+    if constexpr (R == 4) quotient4<UNIT>(m, r2, w);
+    else
+#pragma unroll
+        for (int k = 0; k < R; ++k) w[k] = quotient<UNIT>(m, r2[k]);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        s1[k] = fma(w[k], d1[k], s1[k]);
+        s2[k] = fma(w[k], d2, s2[k]);
+    }
+}
+
+// The same for a staged lens at any distance from the row.
+template <bool UNIT, int R>
+__device__ __forceinline__ void row_lens(const Stage64<UNIT> &sm, int t, const double *t1,
+                                         double t2, double *s1, double *s2)
+{
+    const double2 z = sm.xy[t];
+    const double m = UNIT ? 1.0 : sm.m[t];
+    const double d2 = t2 - z.y;
+    if (fabs(d2) < kNear64) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const double d1 = t1[k] - z.x;
+            term_any(d1, fma(d1, d1, d2 * d2), d2, m, s1[k], s2[k]);
+        }
+    } else {
+        row_lens_far<UNIT, R>(z.x, d2, m, t1, s1, s2);
+    }
+}
+
+// The lens sums of a lane's R rays (r0 + 64 k, k < R; R = 1 or 4), every lens
+// in packed order.  tame: the plan's lenses and masses allow quotient()
+// (irs_plan).  Where all the wave's rays lie in one row, theta_2 - y_i and its
+// square are taken once for the lane's R rays.
+//
+// Bound by FP64 issue: with four rays a lane, per ray and lens about 2.5
+// slots (a slot: one FMA) of offsets and r^2, 5.75 of the quotient (one
+// reciprocal for four rays) and 2 of the sums, against about 24 with the IEEE
+// division and one ray a lane.  2048^2 rays, 105 lenses: kernel 479 -> 320 us (one ray a
+// lane 362), of which the sheet's closed form, once a ray, is about 90.
+template <bool UNIT, int R>
+__device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const DevGeom &g,
+                                          const double *__restrict__ lx,
+                                          const double *__restrict__ ly,
+                                          const double *__restrict__ lm, int32_t nl, bool tame,
+                                          const double *t1, const double *t2, bool one_row,
+                                          double *s1, double *s2)
+{
     const int tid = threadIdx.x;
-    const int64_t r = r_begin + (int64_t)blockIdx.x * kThreads + tid;
-    const bool valid = r < r_end;
-    const int64_t rr = valid ? r : r_begin;
-    const double t1 = ray_x(g, rr % g.nx), t2 = ray_y(g, rr / g.nx);
-    double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) s1[k] = s2[k] = 0.0;
     for (int32_t base = 0; base < nl; base += kLens64) {
         __syncthreads();
         if (base + tid < nl) {
-            s_x[tid] = lx[base + tid];
-            s_y[tid] = ly[base + tid];
-            if (!UNIT) s_m[tid] = lm[base + tid];
+            sm.xy[tid] = make_double2(lx[base + tid], ly[base + tid]);
+            if (!UNIT) sm.m[tid] = lm[base + tid];
         }
         __syncthreads();
         const int cnt = min(kLens64, nl - base);
-        for (int t = 0; t < cnt; ++t) {
-            const double d1 = t1 - s_x[t], d2 = t2 - s_y[t];
-            const double r2 = d1 * d1 + d2 * d2;
-            if (r2 > 0.0) {
-                const double w = (UNIT ? 1.0 : s_m[t]) / r2;
-                s1 += w * d1;
-                s2 += w * d2;
+        if (tame && one_row) {                               // wave-uniform
+            int t = 0;
+            // two lenses a step: their chains overlap
+            for (; t + 1 < cnt; t += 2) {
+                const double2 za = sm.xy[t], zb = sm.xy[t + 1];
+                const double da = t2[0] - za.y, db = t2[0] - zb.y;
+                if (__builtin_expect(fmin(fabs(da), fabs(db)) < kNear64, 0)) {
+                    row_lens<UNIT, R>(sm, t, t1, t2[0], s1, s2);
+                    row_lens<UNIT, R>(sm, t + 1, t1, t2[0], s1, s2);
+                } else {
+                    row_lens_far<UNIT, R>(za.x, da, UNIT ? 1.0 : sm.m[t], t1, s1, s2);
+                    row_lens_far<UNIT, R>(zb.x, db, UNIT ? 1.0 : sm.m[t + 1], t1, s1, s2);
+                }
+            }
+            if (t < cnt) row_lens<UNIT, R>(sm, t, t1, t2[0], s1, s2);
+        } else {
+            for (int t = 0; t < cnt; ++t) {
+                const double2 z = sm.xy[t];
+                const double m = UNIT ? 1.0 : sm.m[t];
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    const double d1 = t1[k] - z.x, d2 = t2[k] - z.y;
+                    const double r2 = fma(d1, d1, d2 * d2);
+                    if (__builtin_expect(tame && fabs(d2) >= kNear64, 1)) {
+                        const double w = quotient<UNIT>(m, r2);
+                        s1[k] = fma(w, d1, s1[k]);
+                        s2[k] = fma(w, d2, s2[k]);
+                    } else {
+                        term_any(d1, r2, d2, m, s1[k], s2[k]);
+                    }
+                }
             }
         }
     }
-    double a1, a2;
-    int32_t pix;
-    assemble(g, t1, t2, s1, s2, a1, a2, pix);
-    emit(valid, r - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
+}
+
+// A workgroup takes kThreads R consecutive rays, a wave 64 R of them.
+template <bool UNIT, int R>
+__global__ __launch_bounds__(kThreads) void k_direct_f64(
+    DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
+    const double *__restrict__ lm, int32_t nl, bool tame, int64_t r_begin, int64_t r_end,
+    int64_t out_base, double *a1o, double *a2o, int64_t *pixo, uint32_t *counts,
+    unsigned long long *landed)
+{
+    __shared__ Stage64<UNIT> sm;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave;
+    const int64_t w0 = r_begin + ((int64_t)blockIdx.x * kWaves + wave) * (kWave * R);
+    double t1[R], t2[R], s1[R], s2[R];
+    // the wave's first ray's row; most waves stay in it
+    const int64_t j0 = w0 / g.nx, i0 = w0 - j0 * g.nx;
+    const bool one_row = i0 + kWave * R <= g.nx;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        int64_t i = i0 + lane + kWave * k, j = j0;
+        if (!one_row) {
+            const int64_t r = min(w0 + lane + kWave * k, r_end - 1);
+            j = r / g.nx;
+            i = r - j * g.nx;
+        }
+        t1[k] = ray_x(g, i);
+        t2[k] = ray_y(g, j);
+    }
+    lens_sums<UNIT, R>(sm, g, lx, ly, lm, nl, tame, t1, t2, one_row, s1, s2);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int64_t r = w0 + lane + kWave * k;
+        double a1, a2;
+        int32_t pix;
+        assemble(g, t1[k], t2[k], s1[k], s2[k], a1, a2, pix);
+        emit(r < r_end, r - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
+    }
 }
 
 // Persistent FP64 form for batches: item = 256 consecutive rays of a map.
@@ -121,7 +290,7 @@ __global__ __launch_bounds__(kThreads) void k_direct_f64_queue(
     const DirectArgs *__restrict__ maps, const int64_t *__restrict__ item_start, int32_t nmaps,
     unsigned long long *cursor)
 {
-    __shared__ double s_x[kLens64], s_y[kLens64], s_m[UNIT ? 1 : kLens64];
+    __shared__ Stage64<UNIT> sm;
     __shared__ long long s_item;
     const int tid = threadIdx.x;
     const int64_t total = item_start[nmaps];
@@ -143,26 +312,8 @@ __global__ __launch_bounds__(kThreads) void k_direct_f64_queue(
         const bool valid = r < g.nx * g.ny;
         const int64_t rr = valid ? r : 0;
         const double t1 = ray_x(g, rr % g.nx), t2 = ray_y(g, rr / g.nx);
-        double s1 = 0.0, s2 = 0.0;
-        for (int32_t base = 0; base < a.nl; base += kLens64) {
-            __syncthreads();
-            if (base + tid < a.nl) {
-                s_x[tid] = a.lx[base + tid];
-                s_y[tid] = a.ly[base + tid];
-                if (!UNIT) s_m[tid] = a.lm[base + tid];
-            }
-            __syncthreads();
-            const int cnt = min(kLens64, a.nl - base);
-            for (int t = 0; t < cnt; ++t) {
-                const double d1 = t1 - s_x[t], d2 = t2 - s_y[t];
-                const double r2 = d1 * d1 + d2 * d2;
-                if (r2 > 0.0) {
-                    const double w = (UNIT ? 1.0 : s_m[t]) / r2;
-                    s1 += w * d1;
-                    s2 += w * d2;
-                }
-            }
-        }
+        double s1, s2;
+        lens_sums<UNIT, 1>(sm, g, a.lx, a.ly, a.lm, a.nl, a.tame != 0, &t1, &t2, false, &s1, &s2);
         double a1, a2;
         int32_t pix;
         assemble(g, t1, t2, s1, s2, a1, a2, pix);
@@ -415,23 +566,32 @@ irs_status launch_direct(irs_plan_s *p, const RaySel &sel)
         const int64_t rb = std::max(sel.row0 * g.nx, sel.ray_first);
         const int64_t re = std::min(sel.row1 * g.nx, sel.ray_last);
         const int64_t chunk = (int64_t)kThreads << 22;   // rays per launch
+        const bool tame = p->tame;
+        // four rays a lane share the lens loads, theta_2 - y and a reciprocal
+        // (2048^2 rays: 320 against 362 us); with fewer than 2^20 rays that
+        // would be under four waves a SIMD
+        const int64_t per = re - rb >= kRays4 ? 4 : 1;
         if (sel.stats) sel.stats->direct_pairs += std::max<int64_t>(0, re - rb) * (int64_t)nl;
         for (int64_t c0 = rb; c0 < re; c0 += chunk) {
             const int64_t c1 = std::min(re, c0 + chunk);
-            const unsigned nb = (unsigned)((c1 - c0 + kThreads - 1) / kThreads);
+            const unsigned nb = (unsigned)((c1 - c0 + kThreads * per - 1) / (kThreads * per));
             if (sel.stats) {
                 irs_status st = sel.stats->begin(s, 1);
                 if (st != IRS_OK) return st;
                 sel.stats->n_rays++;
             }
-            if (unit)
-                hipLaunchKernelGGL(k_direct_f64<true>, dim3(nb), dim3(kThreads), 0, s, g, p->d_x,
-                                   p->d_y, p->d_m, nl, c0, c1, sel.ray_first, sel.alpha1,
-                                   sel.alpha2, sel.pixel, sel.counts, sel.landed);
-            else
-                hipLaunchKernelGGL(k_direct_f64<false>, dim3(nb), dim3(kThreads), 0, s, g,
-                                   p->d_x, p->d_y, p->d_m, nl, c0, c1, sel.ray_first,
-                                   sel.alpha1, sel.alpha2, sel.pixel, sel.counts, sel.landed);
+#define IRS_D64(U, R)                                                                          \
+    hipLaunchKernelGGL((k_direct_f64<U, R>), dim3(nb), dim3(kThreads), 0, s, g, p->d_x, p->d_y, \
+                       p->d_m, nl, tame, c0, c1, sel.ray_first, sel.alpha1, sel.alpha2,        \
+                       sel.pixel, sel.counts, sel.landed)
+            if (unit) {
+                if (per == 4) IRS_D64(true, 4);
+                else IRS_D64(true, 1);
+            } else {
+                if (per == 4) IRS_D64(false, 4);
+                else IRS_D64(false, 1);
+            }
+#undef IRS_D64
             IRS_HIP(hipGetLastError());
             if (sel.stats) {
                 irs_status st = sel.stats->end(s);
@@ -522,6 +682,7 @@ DirectArgs direct_args_full(const irs_plan_s *p, int variant, uint32_t *counts,
     a.lm = p->d_m;
     a.cell_start = p->d_cell_start;
     a.nl = (int32_t)p->n_lens;
+    a.tame = p->tame ? 1 : 0;
     a.ntx = (p->dg.nx + kTX - 1) / kTX;
     a.ty0 = 0;
     a.row0 = 0;

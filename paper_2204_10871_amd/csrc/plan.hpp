@@ -24,7 +24,7 @@ struct DirectArgs {
     const double *lx, *ly, *lm;          // sorted lenses (lm null: unit masses)
     const int32_t *cell_start;
     int32_t nl;
-    int32_t pad_;
+    int32_t tame;                        // irs_plan_s::tame (FP64 sums)
     int64_t ntx, ty0;                    // tiles per row; first tile row (queue kernels)
     int64_t row0, row1;                  // ray rows computed
     int64_t ray_first, ray_last;         // ray index range computed
@@ -43,6 +43,8 @@ struct irs_plan_s {
     int device = 0;
     int64_t n_lens = 0;
     bool unit_mass = true;
+    bool tame = true;                    // no squared distance or mass near the ends of FP64's
+                                         // exponent range (small distances aside)
     double kappa_star_eff = 0.0;
     int direct_variant = 1;              // FP32 direct tile shape (see k_direct.hip)
     bool no_alloc = false;               // set during irs_shoot_rows_noalloc: every
