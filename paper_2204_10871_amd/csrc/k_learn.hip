@@ -121,11 +121,9 @@ __device__ __forceinline__ void features(const float *__restrict__ freq, float h
     }
 }
 
-// one hidden layer: B (8 K-steps) -> relu(W B + b) -> B; mask: bit 16 mb + r
-// set where result register r of row block mb is positive
-template <bool SAVE>
+// one hidden layer: B (8 K-steps) -> relu(W B + b) -> B
 __device__ __forceinline__ void hidden_layer(const uint4 *__restrict__ wf, const float *__restrict__ bias,
-                                             uint4 B[8], uint64_t &mask)
+                                             uint4 B[8])
 {
     const int lane = threadIdx.x % kW, h = lane / 32;
     f32x16 acc[4];
@@ -140,17 +138,13 @@ __device__ __forceinline__ void hidden_layer(const uint4 *__restrict__ wf, const
         for (int ob = 0; ob < 4; ++ob) acc[ob] = mfma(wf[(ob * 8 + t) * kW + lane], B[t], acc[ob]);
         asm volatile("" ::: "memory");      // keep the fragment loads of later steps here
     }
-    if (SAVE) mask = 0;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             float o[8];
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                o[v] = fmaxf(acc[mb][8 * j + v], 0.0f);
-                if (SAVE && o[v] > 0.0f) mask |= 1ull << (16 * mb + 8 * j + v);
-            }
+            for (int v = 0; v < 8; ++v) o[v] = fmaxf(acc[mb][8 * j + v], 0.0f);
             B[2 * mb + j] = make_uint4(pack2(o[0], o[1]), pack2(o[2], o[3]), pack2(o[4], o[5]),
                                        pack2(o[6], o[7]));
         }
@@ -188,9 +182,8 @@ __device__ __forceinline__ void mlp_forward(const uint4 *__restrict__ wf, const 
     for (int nb = 0; nb < 2; ++nb) {
         uint4 B[8];
         features(freq, __shfl(hx, 32 * nb + n), __shfl(hy, 32 * nb + n), B);
-        uint64_t m;
 #pragma unroll 1
-        for (int L = 0; L < 4; ++L) hidden_layer<false>(wf + L * kFragHidden, bias + L * kHd, B, m);
+        for (int L = 0; L < 4; ++L) hidden_layer(wf + L * kFragHidden, bias + L * kHd, B);
         head_layer(wf + 4 * kFragHidden, bias + 4 * kHd, B, nb, y);
     }
 }
@@ -660,188 +653,242 @@ __global__ __launch_bounds__(kThreads) void k_mlp_fwd(const uint4 *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Training: forward + backward of 64 samples per wave
+// Training: forward + backward of 32 samples per workgroup
 // act:  a_0..a_4, unit-major BF16, a_l[u * bn + i]
 // dz:   dZ_1..dZ_4 (128 units each) then dY (16), unit-major BF16
+//
+// The four waves share one 32-sample column block: wave w computes row block w
+// of every product (units 32 w .. 32 w + 31) and hands its two K-steps of the
+// next layer's operand to the others through LDS.  A chain of nine dependent
+// layers bounds the kernel, not the matrix cores: with a wave carrying 64
+// samples alone, 8192 samples were 128 waves on 32 CUs and took 132 us; four
+// waves a block, 256 workgroups: 22 us, every product in the same order.
 // ---------------------------------------------------------------------------
+constexpr int kTrainCols = 32;             // samples per workgroup
+static_assert(kThreads / kW == 4 && kHd == 4 * 32, "a wave per row block");
+
+// units 32 w + 8 (r/4) + 4 h + r%4, r < 16, of 32 columns: a lane's 16 BF16
+// values (o8: two K-steps) to rows of dst (unit-major, pitch bn)
+__device__ __forceinline__ void store_units(uint16_t *__restrict__ dst, int64_t bn, int wave, int h,
+                                            const uint4 o8[2])
+{
+    uint16_t *lp = dst + (int64_t)(32 * wave + 4 * h) * bn;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint32_t w4[4] = {o8[j].x, o8[j].y, o8[j].z, o8[j].w};
+#pragma unroll
+        for (int v = 0; v < 8; ++v)
+            lp[(int64_t)(16 * j + 8 * (v / 4) + v % 4) * bn] = (uint16_t)(w4[v / 2] >> (16 * (v % 2)));
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void k_mlp_train(
     const uint4 *__restrict__ wf, const uint4 *__restrict__ wb, const float *__restrict__ theta,
     const float *__restrict__ freq, const float *__restrict__ samples, int64_t n_samples,
     uint64_t idx_base, uint64_t idx_mult, int32_t n_valid, int32_t bn, uint16_t *__restrict__ act,
-    uint16_t *__restrict__ dz, float *__restrict__ loss_part)
+    uint16_t *__restrict__ dz, float *__restrict__ loss_slot)
 {
-    __shared__ float s_loss[kThreads / kW];
-    __shared__ uint64_t s_mask[kThreads / kW][4][kW];     // relu masks, per wave, layer, lane
-    const int lane = threadIdx.x % kW, wave = threadIdx.x / kW, h = lane / 32, n = lane % 32;
-    const int32_t i0 = (blockIdx.x * (kThreads / kW) + wave) * kW;    // first batch slot
-    const int32_t i = i0 + lane;                                      // the lane's own slot
-    const bool valid = i < n_valid;
+    __shared__ uint4 s_b[2][8][kW];           // the next product's operand, by K-step
+    __shared__ uint4 s_bd[kW];                // dY's
+    const int lane = threadIdx.x % kW, h = lane / 32, n = lane % 32;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kW);
+    const int32_t col = (int32_t)blockIdx.x * kTrainCols + n;         // the column's batch slot
+    const bool valid = col < n_valid;
     int64_t s = 0;
-    if (valid) s = (int64_t)((((idx_base + (uint64_t)i) % (uint64_t)n_samples) * idx_mult) % (uint64_t)n_samples);
-    float f[20];
-#pragma unroll
-    for (int e = 0; e < 20; ++e) f[e] = valid ? samples[(int64_t)e * n_samples + s] : 0.0f;
-    const float hx = valid ? f[0] : 0.5f, hy = valid ? f[1] : 0.5f;
-    float lw = 0.0f;
+    if (valid) s = (int64_t)((((idx_base + (uint64_t)col) % (uint64_t)n_samples) * idx_mult) % (uint64_t)n_samples);
+    const float hx = valid ? samples[s] : 0.5f, hy = valid ? samples[n_samples + s] : 0.5f;
 
-#pragma unroll 1
-    for (int nb = 0; nb < 2; ++nb) {
-        const int32_t col = i0 + 32 * nb + n;        // slot of this column
+    int buf = 0;
+    {   // features: wave w takes frequencies 16 w .. 16 w + 15 (K-steps w and w + 4)
+        const float px = hx - 0.5f, py = hy - 0.5f;
+        float sn[8], cs[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const int j = 16 * wave + 8 * h + v;
+            const float a = fmaf(freq[2 * j], px, freq[2 * j + 1] * py);
+            const float r = a - rintf(a);                 // revolutions, |r| <= 1/2
+            sn[v] = __builtin_amdgcn_sinf(r);             // sin(2 pi r)
+            cs[v] = __builtin_amdgcn_cosf(r);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const float *f = e ? cs : sn;
+            const uint4 B = make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]),
+                                       pack2(f[6], f[7]));
+            s_b[0][wave + 4 * e][lane] = B;
+            // unit 16 t + 8 h + v of K-step t = wave + 4 e
+            uint16_t *lp = act + (int64_t)(16 * (wave + 4 * e) + 8 * h) * bn + col;
+            const uint32_t w4[4] = {B.x, B.y, B.z, B.w};
+#pragma unroll
+            for (int v = 0; v < 8; ++v) lp[(int64_t)v * bn] = (uint16_t)(w4[v / 2] >> (16 * (v % 2)));
+        }
+    }
+    __syncthreads();
+    uint32_t mask[4];                          // bit r: unit r of the wave's block is positive
+#pragma unroll
+    for (int L = 0; L < 4; ++L) {
+        const uint4 *w = wf + L * kFragHidden + wave * 8 * kW + lane;
+        const float *bias = theta + offB(L);
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = bias[drow(wave, r, h)];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc = mfma(w[t * kW], s_b[buf][t][lane], acc);
+        uint32_t mk = 0;
+        uint4 o8[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float o[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                o[v] = fmaxf(acc[8 * j + v], 0.0f);
+                if (o[v] > 0.0f) mk |= 1u << (8 * j + v);
+            }
+            o8[j] = make_uint4(pack2(o[0], o[1]), pack2(o[2], o[3]), pack2(o[4], o[5]),
+                               pack2(o[6], o[7]));
+            s_b[buf ^ 1][2 * wave + j][lane] = o8[j];
+        }
+        mask[L] = mk;
+        store_units(act + (int64_t)(L + 1) * kHd * bn + col, bn, wave, h, o8);
+        buf ^= 1;
+        __syncthreads();
+    }
+    // head, loss and d loss / d y: wave 0, whose lower lanes own the samples
+    if (wave == 0) {
+        float f[20];
+#pragma unroll
+        for (int e = 2; e < 20; ++e) f[e] = valid ? samples[(int64_t)e * n_samples + s] : 0.0f;
         uint4 B[8];
-        features(freq, __shfl(hx, 32 * nb + n), __shfl(hy, 32 * nb + n), B);
-        {
-            // unit 16 t + 8 h + v: lane part 8 h, uniform part 16 t + v
-            uint16_t *lp = act + (int64_t)(8 * h) * bn + col;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const uint32_t w4[4] = {B[t].x, B[t].y, B[t].z, B[t].w};
-#pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    lp[(16 * t + v) * bn] = (uint16_t)(w4[v / 2] >> (16 * (v % 2)));
-            }
-        }
-#pragma unroll 1
-        for (int L = 0; L < 4; ++L) {
-            uint64_t mk;
-            hidden_layer<true>(wf + L * kFragHidden, theta + offB(L), B, mk);
-            s_mask[wave][L][lane] = mk;
-            // unit 16 t + 8 (v/4) + 4 h + v%4: lane part 4 h, uniform part the rest
-            uint16_t *lp = act + ((int64_t)(L + 1) * kHd + 4 * h) * bn + col;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const uint32_t w4[4] = {B[t].x, B[t].y, B[t].z, B[t].w};
-#pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    lp[(16 * t + 8 * (v / 4) + v % 4) * bn] = (uint16_t)(w4[v / 2] >> (16 * (v % 2)));
-            }
-        }
+        for (int t = 0; t < 8; ++t) B[t] = s_b[buf][t][lane];
         float y[kNO];
 #pragma unroll
         for (int o = 0; o < kNO; ++o) y[o] = 0.0f;
-        head_layer(wf + 4 * kFragHidden, theta + kOffB5, B, nb, y);
-
-        // the owner lanes: loss and d loss / d y of their sample
-        const bool owner = h == nb;
+        head_layer(wf + 4 * kFragHidden, theta + kOffB5, B, 0, y);
+        const bool owner = h == 0;
         float dy[kNO];
-        {
-            float pr, pi;
-            combine(y, f + 2, pr, pi);
-            const bool use = owner && valid;
-            const float rr = use ? pr - f[18] : 0.0f, ri = use ? pi - f[19] : 0.0f;
-            const float sc = 2.0f / (float)n_valid;
+        float pr, pi;
+        combine(y, f + 2, pr, pi);
+        const bool use = owner && valid;
+        const float rr = use ? pr - f[18] : 0.0f, ri = use ? pi - f[19] : 0.0f;
+        const float sc = 2.0f / (float)n_valid;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float Dr = f[2 + 2 * k], Di = f[3 + 2 * k];
-                dy[2 * k] = sc * (rr * Dr + ri * Di);
-                dy[2 * k + 1] = sc * (ri * Dr - rr * Di);
-            }
-            lw += rr * rr + ri * ri;
-            if (owner) {
-                uint16_t *dst = dz + (int64_t)4 * kHd * bn;
+        for (int k = 0; k < 8; ++k) {
+            const float Dr = f[2 + 2 * k], Di = f[3 + 2 * k];
+            dy[2 * k] = sc * (rr * Dr + ri * Di);
+            dy[2 * k + 1] = sc * (ri * Dr - rr * Di);
+        }
+        if (owner) {
+            loss_slot[col] = rr * rr + ri * ri;
+            uint16_t *dst = dz + (int64_t)4 * kHd * bn + col;
 #pragma unroll
-                for (int o = 0; o < kNO; ++o) dst[(int64_t)o * bn + col] = f2bf(dy[o]);
-            }
+            for (int o = 0; o < kNO; ++o) dst[(int64_t)o * bn] = f2bf(dy[o]);
         }
         // dY as the B operand of W5^T: rows 8(v/4) + 4h + v%4 of the column's
         // sample; the owner has them, its partner receives the rows of its half
-        uint4 Bd;
-        {
-            float mine[8], send[8], recv[8];
+        float src[8];
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                const int r0 = 8 * (v / 4) + v % 4;
-                mine[v] = h ? dy[r0 + 4] : dy[r0];
-                send[v] = h ? dy[r0] : dy[r0 + 4];
-            }
-#pragma unroll
-            for (int v = 0; v < 8; ++v) recv[v] = __shfl_xor(send[v], 32);
-            float src[8];
-#pragma unroll
-            for (int v = 0; v < 8; ++v) src[v] = owner ? mine[v] : recv[v];
-            Bd = make_uint4(pack2(src[0], src[1]), pack2(src[2], src[3]), pack2(src[4], src[5]),
-                            pack2(src[6], src[7]));
+        for (int v = 0; v < 8; ++v) {
+            const int r0 = 8 * (v / 4) + v % 4;
+            const float recv = __shfl_xor(dy[r0 + 4], 32);
+            src[v] = owner ? dy[r0] : recv;
         }
-        f32x16 acc[4];
-#pragma unroll
-        for (int ib = 0; ib < 4; ++ib) {
-            f32x16 z;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) z[r] = 0.0f;
-            acc[ib] = mfma(wb[3 * kFragHidden + ib * kW + lane], Bd, z);
-        }
-        // dZ_L = dA_L (.) [a_L > 0]; dA_{L-1} = W_L^T dZ_L
-#pragma unroll 1
-        for (int L = 3; L >= 0; --L) {
-            const uint64_t mk = s_mask[wave][L][lane];
-            uint16_t *lp = dz + ((int64_t)L * kHd + 4 * h) * bn + col;    // unit drow(mb, r, h)
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    float o[8];
-#pragma unroll
-                    for (int v = 0; v < 8; ++v) {
-                        const int bit = 16 * mb + 8 * j + v;
-                        o[v] = ((mk >> bit) & 1ull) ? acc[mb][8 * j + v] : 0.0f;
-                        lp[(32 * mb + 8 * ((8 * j + v) / 4) + v % 4) * bn] = f2bf(o[v]);
-                    }
-                    B[2 * mb + j] = make_uint4(pack2(o[0], o[1]), pack2(o[2], o[3]), pack2(o[4], o[5]),
-                                               pack2(o[6], o[7]));
-                }
-            if (L == 0) break;
-#pragma unroll
-            for (int ib = 0; ib < 4; ++ib)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[ib][r] = 0.0f;
-            const uint4 *w = wb + (L - 1) * kFragHidden;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-#pragma unroll
-                for (int ib = 0; ib < 4; ++ib) acc[ib] = mfma(w[(ib * 8 + t) * kW + lane], B[t], acc[ib]);
-                asm volatile("" ::: "memory");
-            }
-        }
+        s_bd[lane] = make_uint4(pack2(src[0], src[1]), pack2(src[2], src[3]), pack2(src[4], src[5]),
+                                pack2(src[6], src[7]));
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lw += __shfl_xor(lw, o);
-    if (lane == 0) s_loss[wave] = lw;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float t = 0.0f;
-        for (int w = 0; w < kThreads / kW; ++w) t += s_loss[w];
-        loss_part[blockIdx.x] = t;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    acc = mfma(wb[3 * kFragHidden + wave * kW + lane], s_bd[lane], acc);
+    // dZ_L = dA_L (.) [a_L > 0]; dA_{L-1} = W_L^T dZ_L
+#pragma unroll
+    for (int L = 3; L >= 0; --L) {
+        uint4 o8[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float o[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) o[v] = ((mask[L] >> (8 * j + v)) & 1u) ? acc[8 * j + v] : 0.0f;
+            o8[j] = make_uint4(pack2(o[0], o[1]), pack2(o[2], o[3]), pack2(o[4], o[5]),
+                               pack2(o[6], o[7]));
+        }
+        store_units(dz + (int64_t)L * kHd * bn + col, bn, wave, h, o8);
+        if (L == 0) break;
+        // (the last reader of this buffer was the product before the latest barrier)
+        s_b[buf ^ 1][2 * wave][lane] = o8[0];
+        s_b[buf ^ 1][2 * wave + 1][lane] = o8[1];
+        buf ^= 1;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+        const uint4 *w = wb + (L - 1) * kFragHidden + wave * 8 * kW + lane;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc = mfma(w[t * kW], s_b[buf][t][lane], acc);
     }
 }
 
 // Weight gradients: dW_l[u][c] = sum_i dZ_l[u][i] a_{l-1}[c][i] over a chunk of
-// the batch (one wave per 32 x 32 tile and chunk); bias gradients: sum_i dZ.
-// Items per chunk: 64 hidden tiles, 4 head tiles, 5 bias rows.
-constexpr int kGradItems = 4 * 16 + 4 + 5;
+// the batch (one wave per 32 x 32 tile and chunk); bias gradients: sum_i dZ in
+// slot order; the losses of 256 slots.  Items per chunk: 64 hidden tiles, 4
+// head tiles, 9 x 64 units of biases; after all chunks, one per 256 slots.
+// Bound by the latency of its loads, so each wave keeps eight steps of them in
+// flight (the biases, one 2-byte load a step, held the kernel at 186 us for
+// 8192 samples; now 16).
+constexpr int kGradItems = 4 * 16 + 4 + 9;
 
 __global__ __launch_bounds__(kW) void k_mlp_wgrad(const uint16_t *__restrict__ act,
                                                    const uint16_t *__restrict__ dz, int32_t bn,
-                                                   int32_t chunk, float *__restrict__ part)
+                                                   int32_t chunk, int32_t nchunk,
+                                                   const float *__restrict__ loss_slot,
+                                                   float *__restrict__ part,
+                                                   float *__restrict__ loss_part)
 {
     const int lane = threadIdx.x, h = lane / 32, m = lane % 32;
     const int item = blockIdx.x % kGradItems, kc = blockIdx.x / kGradItems;
+    const int lb = (int)blockIdx.x - kGradItems * nchunk;
+    if (lb >= 0) {                             // losses of slots [256 lb, 256 lb + 256)
+        float t = 0.0f;
+        for (int w = 0; w < 4; ++w) {
+            float v = loss_slot[(int64_t)lb * 256 + w * kW + lane];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            t += v;
+        }
+        if (lane == 0) loss_part[lb] = t;
+        return;
+    }
     const int32_t s0 = kc * chunk, s1 = min(bn, s0 + chunk);
     float *out = part + (int64_t)kc * kNP;
+    constexpr int kFly = 8;                    // steps whose loads are in flight
     if (item < 68) {
         int l, ob, ib;
         if (item < 64) { l = item / 16; ob = (item % 16) / 4; ib = item % 4; }
         else { l = 4; ob = 0; ib = item - 64; }
-        const uint16_t *dzl = l < 4 ? dz + (int64_t)l * kHd * bn : dz + (int64_t)4 * kHd * bn;
-        const uint16_t *al = act + (int64_t)l * kHd * bn;
         const int urow = 32 * ob + m;
         const bool rowok = l < 4 || urow < kNO;
+        const uint16_t *ar = dz + ((int64_t)l * kHd + (rowok ? urow : 0)) * bn + 8 * h;
+        const uint16_t *br = act + ((int64_t)l * kHd + 32 * ib + m) * bn + 8 * h;
         f32x16 acc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-        for (int32_t s = s0; s < s1; s += 16) {
-            const uint4 a = rowok ? *reinterpret_cast<const uint4 *>(dzl + (int64_t)urow * bn + s + 8 * h)
-                                  : make_uint4(0, 0, 0, 0);
-            const uint4 b = *reinterpret_cast<const uint4 *>(al + (int64_t)(32 * ib + m) * bn + s + 8 * h);
-            acc = mfma(a, b, acc);
+        int32_t s = s0;
+        for (; s + 16 * kFly <= s1; s += 16 * kFly) {
+            uint4 a[kFly], b[kFly];
+#pragma unroll
+            for (int e = 0; e < kFly; ++e) {
+                a[e] = *reinterpret_cast<const uint4 *>(ar + s + 16 * e);
+                b[e] = *reinterpret_cast<const uint4 *>(br + s + 16 * e);
+            }
+#pragma unroll
+            for (int e = 0; e < kFly; ++e) {
+                if (!rowok) a[e] = make_uint4(0, 0, 0, 0);
+                acc = mfma(a[e], b[e], acc);
+            }
+        }
+        for (; s < s1; s += 16) {
+            const uint4 a = rowok ? *reinterpret_cast<const uint4 *>(ar + s) : make_uint4(0, 0, 0, 0);
+            acc = mfma(a, *reinterpret_cast<const uint4 *>(br + s), acc);
         }
         const int base = l < 4 ? offW(l) : kOffW5;
 #pragma unroll
@@ -850,14 +897,25 @@ __global__ __launch_bounds__(kW) void k_mlp_wgrad(const uint16_t *__restrict__ a
             if (l < 4 || u < kNO) out[base + u * kHd + 32 * ib + m] = acc[r];
         }
     } else {
-        const int l = item - 68;
-        const int nu = l < 4 ? kHd : kNO;
-        const uint16_t *dzl = dz + (int64_t)l * kHd * bn;     // dY follows dZ_4
-        for (int u = lane; u < nu; u += kW) {
-            float t = 0.0f;
-            for (int32_t s = s0; s < s1; ++s) t += bf2f(dzl[(int64_t)u * bn + s]);
-            out[(l < 4 ? offB(l) : kOffB5) + u] = t;
+        const int l = (item - 68) / 2, u = ((item - 68) % 2) * kW + lane;   // l = 4: dY
+        if (u >= (l < 4 ? kHd : kNO)) return;
+        const uint16_t *src = dz + ((int64_t)l * kHd + u) * bn;
+        float t = 0.0f;
+        auto add8 = [&](const uint4 &v) {
+            const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t += bf2f((uint16_t)(w4[e / 2] >> (16 * (e % 2))));
+        };
+        int32_t s = s0;
+        for (; s + 8 * kFly <= s1; s += 8 * kFly) {
+            uint4 v[kFly];
+#pragma unroll
+            for (int e = 0; e < kFly; ++e) v[e] = *reinterpret_cast<const uint4 *>(src + s + 8 * e);
+#pragma unroll
+            for (int e = 0; e < kFly; ++e) add8(v[e]);
         }
+        for (; s < s1; s += 8) add8(*reinterpret_cast<const uint4 *>(src + s));
+        out[(l < 4 ? offB(l) : kOffB5) + u] = t;
     }
 }
 
@@ -1491,7 +1549,7 @@ irs_status check_params(const irs_learn_params &lp, bool training)
 // into wf/wb; fills grad (device) and loss (device, one double)
 struct TrainBufs {
     DevBuf<uint16_t> act, dz;
-    DevBuf<float> part, loss_part;
+    DevBuf<float> part, loss_slot, loss_part;
     int32_t bn = 0, nchunk = 0;
     irs_status alloc(int32_t batch)
     {
@@ -1501,24 +1559,27 @@ struct TrainBufs {
         irs_status st = act.alloc((size_t)5 * kHd * bn);
         if (st == IRS_OK) st = dz.alloc((size_t)(4 * kHd + kNO) * bn);
         if (st == IRS_OK) st = part.alloc((size_t)nchunk * kNP);
-        if (st == IRS_OK) st = loss_part.alloc((size_t)bn / kThreads + 1);
+        if (st == IRS_OK) st = loss_slot.alloc((size_t)bn);
+        if (st == IRS_OK) st = loss_part.alloc((size_t)bn / 256 + 1);
         return st;
     }
 };
 
 // The furthest element each training kernel indexes, against the buffers:
-// k_mlp_train writes act[(5 kHd) bn], dz[(4 kHd + kNO) bn] and loss_part[nbt]
-// for slots up to nbt kThreads (so bn must be a multiple of kThreads);
-// k_mlp_wgrad reads slots [kc chunk16, min(bn, kc chunk16 + chunk16)) in
-// steps of 16 and writes part[nchunk kNP]; k_mlp_reduce reads what they wrote.
+// k_mlp_train writes act[(5 kHd) bn], dz[(4 kHd + kNO) bn] and loss_slot[bn]
+// for slots up to bn (a multiple of its kTrainCols); k_mlp_wgrad reads slots
+// [kc chunk16, min(bn, kc chunk16 + chunk16)) in steps of 16 and writes
+// part[nchunk kNP], and sums loss_slot by 256 slots (bn is a multiple of 256)
+// into loss_part[bn / 256]; k_mlp_reduce reads what they wrote.
 bool train_extents_ok(const TrainBufs &tb, int32_t n_valid)
 {
-    const int64_t nbt = (tb.bn + kThreads - 1) / kThreads;
     const int32_t chunk = (tb.bn + tb.nchunk - 1) / tb.nchunk;
     const int64_t chunk16 = (chunk + 15) / 16 * 16;
-    return tb.bn > 0 && tb.bn % kThreads == 0 && n_valid >= 0 && n_valid <= tb.bn &&
-           nbt * kThreads == tb.bn && tb.act.n >= (size_t)5 * kHd * tb.bn &&
-           tb.dz.n >= (size_t)(4 * kHd + kNO) * tb.bn && tb.loss_part.n >= (size_t)nbt &&
+    static_assert(256 % kTrainCols == 0, "whole workgroups of k_mlp_train");
+    return tb.bn > 0 && tb.bn % 256 == 0 && n_valid >= 0 && n_valid <= tb.bn &&
+           tb.act.n >= (size_t)5 * kHd * tb.bn &&
+           tb.dz.n >= (size_t)(4 * kHd + kNO) * tb.bn && tb.loss_slot.n >= (size_t)tb.bn &&
+           tb.loss_part.n >= (size_t)tb.bn / 256 &&
            tb.part.n >= (size_t)tb.nchunk * kNP && chunk16 % 16 == 0 &&
            (int64_t)tb.nchunk * chunk16 >= tb.bn && tb.bn % 16 == 0;
 }
@@ -1531,16 +1592,16 @@ irs_status grad_step(hipStream_t s, TrainBufs &tb, const void *wf, const void *w
         set_error("internal: training buffers smaller than the kernels index");
         return IRS_E_INVALID;
     }
-    const unsigned nbt = (unsigned)((tb.bn + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(k_mlp_train, dim3(nbt), dim3(kThreads), 0, s, (const uint4 *)wf,
-                       (const uint4 *)wb, theta, freq, samples, n_samples, base, mult, n_valid, tb.bn,
-                       tb.act.p, tb.dz.p, tb.loss_part.p);
+    hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)(tb.bn / kTrainCols)), dim3(kThreads), 0, s,
+                       (const uint4 *)wf, (const uint4 *)wb, theta, freq, samples, n_samples, base,
+                       mult, n_valid, tb.bn, tb.act.p, tb.dz.p, tb.loss_slot.p);
     const int32_t chunk = (tb.bn + tb.nchunk - 1) / tb.nchunk;
-    const int32_t chunk16 = (chunk + 15) / 16 * 16;
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kGradItems * tb.nchunk)), dim3(kW), 0, s, tb.act.p,
-                       tb.dz.p, tb.bn, chunk16, tb.part.p);
+    const int32_t chunk16 = (chunk + 15) / 16 * 16, nloss = tb.bn / 256;
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kGradItems * tb.nchunk + nloss)), dim3(kW), 0, s,
+                       tb.act.p, tb.dz.p, tb.bn, chunk16, tb.nchunk, tb.loss_slot.p, tb.part.p,
+                       tb.loss_part.p);
     hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)((kNP + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       s, tb.part.p, tb.nchunk, tb.loss_part.p, (int32_t)nbt, grad, loss);
+                       s, tb.part.p, tb.nchunk, tb.loss_part.p, nloss, grad, loss);
     IRS_HIP(hipGetLastError());
     return IRS_OK;
 }
