@@ -55,6 +55,15 @@ __device__ __forceinline__ int64_t level2_row(const DevGeom &g, int64_t j)
     return ((2 * j + 1) * (int64_t)g.n1y * g.q) / (2 * g.ny);
 }
 
+// floor(num / den) for 0 <= num < 2^53, den > 0, without 64-bit integer division
+__device__ __forceinline__ int64_t floor_div(int64_t num, int64_t den)
+{
+    int64_t v = (int64_t)((double)num / (double)den);
+    if (v * den > num) --v;
+    else if ((v + 1) * den <= num) ++v;
+    return v;
+}
+
 // Deflection of a uniform sheet of unit density over the rectangle, times pi
 // (the two closed-form integrals of Appendix A with A = 1), arranged as a sum
 // over the four corners: with u = theta_1 - a, v = theta_2 - b and sign +1 at

@@ -40,6 +40,7 @@
 #include <vector>
 
 #include "level2.hpp"
+#include "near.hpp"
 
 namespace irs {
 
@@ -329,11 +330,15 @@ __device__ __forceinline__ void ltab_blend(const float *__restrict__ t, float hx
                w11 * t01[NS + o * OS];
 }
 
+// The rays' copy of the table in LDS is node-major with kLPitch floats a node:
+// a wave's lanes read different nodes, and with 16 floats a node their 16-byte
+// reads would start in only four of the sixteen 4-bank groups.
+constexpr int kLPitch = 20;
+
 // sum_k L_k D_k with L the table's blend at (hx, hy) (combine's arithmetic on
-// ltab_blend's weights, one weight pair at a time)
-template <int NS, int OS>
-__device__ __forceinline__ void ltab_combine(const float *__restrict__ t, float hx, float hy,
-                                             const float D[16], float &pr, float &pi)
+// ltab_blend's weights, two weight pairs at a time)
+__device__ __forceinline__ void ltab_combine(const float *t, float hx, float hy, const float D[16],
+                                             float &pr, float &pi)
 {
     const float u = fminf(fmaxf(hx, 0.0f), 1.0f) * (float)kLTab;
     const float v = fminf(fmaxf(hy, 0.0f), 1.0f) * (float)kLTab;
@@ -341,19 +346,25 @@ __device__ __forceinline__ void ltab_combine(const float *__restrict__ t, float 
     const float fu = u - (float)a, fv = v - (float)b;
     const float w00 = (1.0f - fu) * (1.0f - fv), w10 = fu * (1.0f - fv);
     const float w01 = (1.0f - fu) * fv, w11 = fu * fv;
-    const float *t00 = t + (b * (kLTab + 1) + a) * NS;
-    const float *t01 = t00 + (kLTab + 1) * NS;
-    auto at = [&](int o) {
-        return w00 * t00[o * OS] + w10 * t00[NS + o * OS] + w01 * t01[o * OS] +
-               w11 * t01[NS + o * OS];
-    };
+    const float *t00 = t + (b * (kLTab + 1) + a) * kLPitch;
+    const float *t01 = t00 + (kLTab + 1) * kLPitch;
     pr = 0.0f;
     pi = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float yr = at(2 * k), yi = at(2 * k + 1);
-        pr = fmaf(yr, D[2 * k], fmaf(-yi, D[2 * k + 1], pr));
-        pi = fmaf(yr, D[2 * k + 1], fmaf(yi, D[2 * k], pi));
+    for (int c = 0; c < kNO; c += 4) {
+        const float4 q00 = *reinterpret_cast<const float4 *>(t00 + c);
+        const float4 q10 = *reinterpret_cast<const float4 *>(t00 + kLPitch + c);
+        const float4 q01 = *reinterpret_cast<const float4 *>(t01 + c);
+        const float4 q11 = *reinterpret_cast<const float4 *>(t01 + kLPitch + c);
+        const float y[4] = {w00 * q00.x + w10 * q10.x + w01 * q01.x + w11 * q11.x,
+                            w00 * q00.y + w10 * q10.y + w01 * q01.y + w11 * q11.y,
+                            w00 * q00.z + w10 * q10.z + w01 * q01.z + w11 * q11.z,
+                            w00 * q00.w + w10 * q10.w + w01 * q01.w + w11 * q11.w};
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+            pr = fmaf(y[e], D[c + e], fmaf(-y[e + 1], D[c + e + 1], pr));
+            pi = fmaf(y[e], D[c + e + 1], fmaf(y[e + 1], D[c + e], pi));
+        }
     }
 }
 
@@ -973,12 +984,37 @@ __global__ __launch_bounds__(kThreads) void k_learn_err(const float *__restrict_
 
 // The learned path's column table: ray column i's square column
 // gxc = floor((i + 1/2) n1x qc / nx) and level-1 column gxc / qc.
-__global__ __launch_bounds__(kThreads) void k_learn_cols(DevGeom g, int32_t qc, int2 *__restrict__ out)
+// What a ray row's rays share: theta_2, the square row, its edges and the
+// offset in it, the level-1 row.  Read with scalar loads.
+struct alignas(16) LearnRow {
+    double t2, hy;        // theta_2; (theta_2 - Y0)/sy
+    double Y0, Y1;        // the square row's lower and upper edge
+    int32_t gyc, cy;      // square row, level-1 row
+    int64_t pad_;
+};
+
+// Square and level-1 cell of every ray column (cols); the ray rows (rows).
+__global__ __launch_bounds__(kThreads) void k_learn_cols(DevGeom g, LearnGeom lg,
+                                                         int2 *__restrict__ cols,
+                                                         LearnRow *__restrict__ rows)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= g.nx) return;
-    const int64_t gxc = ((2 * i + 1) * ((int64_t)g.n1x * qc)) / (2 * g.nx);
-    out[i] = make_int2((int32_t)gxc, (int32_t)(gxc / qc));
+    if (i < g.nx) {
+        const int64_t gxc = ((2 * i + 1) * ((int64_t)g.n1x * lg.qc)) / (2 * g.nx);
+        cols[i] = make_int2((int32_t)gxc, (int32_t)(gxc / lg.qc));
+    }
+    if (i < g.ny) {
+        const int64_t gyc = ((2 * i + 1) * ((int64_t)g.n1y * lg.qc)) / (2 * g.ny);
+        LearnRow r;
+        r.t2 = ray_y(g, i);
+        r.Y0 = corner_y(g, lg, gyc);
+        r.Y1 = corner_y(g, lg, gyc + 1);
+        r.hy = (r.t2 - r.Y0) / lg.sy;
+        r.gyc = (int32_t)gyc;
+        r.cy = (int32_t)(gyc / lg.qc);
+        r.pad_ = 0;
+        rows[i] = r;
+    }
 }
 
 // The blended weights at n offsets hin (hx row, hy row) from the table tab
@@ -998,212 +1034,212 @@ __global__ __launch_bounds__(kThreads) void k_ltab_eval(const float *__restrict_
 
 // ---------------------------------------------------------------------------
 // Rays with the learned interpolant.  One wave item = 64 consecutive columns
-// of kLearnRows rows (a lane takes one column's rows); a persistent workgroup
-// of 6 waves keeps the weight table in LDS and walks the band's items.
+// of kLearnItem rows (a lane takes one column's rows, kLearnRows at a time); a
+// persistent workgroup keeps the weight table in LDS and walks the band's
+// items.  Rows are grouped by absolute row (groups start at multiples of
+// kLearnRows), so which rays share a reciprocal in the nearby-lens pass does
+// not depend on the call.  A lane keeps its square's corners and local data
+// from row to row until the square row changes.
+//
+// Bound by vector issue and LDS reads: a ray reads 256 bytes of the table
+// (four nodes), which at 64 bytes a node met four-way bank conflicts.  1e8 rays
+// through 9822 lenses: 2.80 -> 1.69 ms (the near pass with one reciprocal per
+// row and the conflicts before; the near pass is now about 0.57 of it, the
+// table 0.28, the binning 0.11, the squares and pixels the rest).  Four waves a
+// SIMD spill: 2.35 ms; items of 32 rows: 1.73 ms.
 // ---------------------------------------------------------------------------
-constexpr int kL3Threads = 384;
-
-// One nearby lens's term m (d1, d2)/r^2, d = theta - z: m/r^2 is the
-// hardware reciprocal estimate times m corrected once (relative error about
-// the square of the estimate's, <= 2.2e-15); 1e-300 added to d1^2 leaves any
-// r^2 above ~1e-284 unchanged and makes the term of a lens exactly on the ray
-// 0 x finite = 0.
-__device__ __forceinline__ void near_lens(double t1, double t2, double zx, double zy, double m,
-                                          double &n1, double &n2)
-{
-    const double d1 = t1 - zx, d2 = t2 - zy;
-    const double rr = fma(d2, d2, fma(d1, d1, 1e-300));
-    const double v = __builtin_amdgcn_rcp(rr);
-    const double y = m * v;
-    const double w = fma(v, fma(-rr, y, m), y);
-    n1 = fma(w, d1, n1);
-    n2 = fma(w, d2, n2);
-}
-
-// Rays of columns [i0, i1) and rows [j0, j1) in items of 64 columns of one
-// row.  CORNER = false: the sheet's analytic part outside the four corner
-// cells of the rectangle, whose rays (with a sheet) it leaves out;
-// CORNER = true: rays of one of those cells, with the sheet's closed form
-// (its logarithms would otherwise set every ray's register budget).
-// rays of a lane: kLearnRows consecutive rows of one column
+constexpr int kL3Threads = 768;            // one workgroup a CU (its table), three waves a SIMD
+constexpr int kL3CornerThreads = 384;
 constexpr int kLearnRows = 4;
-template <int A, int B>
-struct RowSpan {
-    static constexpr int first = A, last = B;
+constexpr int kLearnItem = 8;
+static_assert(kLearnItem % kLearnRows == 0, "whole groups");
+
+// a range of rays: columns [i0, i1), rows [j0, j1)
+struct RaySpan {
+    int64_t i0, i1, j0, j1;
+};
+struct RaySpans {
+    RaySpan s[4];
 };
 
+// Rays of the range sp.  CORNER = false: the sheet's analytic part outside the
+// four corner cells of the rectangle, whose rays (with a sheet) it leaves out;
+// CORNER = true: rays of one of those cells, with the sheet's closed form
+// (its logarithms would otherwise set every ray's register budget).
 #define IRS_LEARNED_RAY_ARGS                                                                      \
-    DevGeom g, LearnGeom lg, const double *__restrict__ lx, const double *__restrict__ ly,        \
-        const double *__restrict__ lm, const int32_t *__restrict__ cell_start,                    \
-        const double *__restrict__ corner, int32_t cy0, const float *__restrict__ tab,            \
-        const int2 *__restrict__ lcol, int64_t i0,                                                \
-        int64_t i1, int64_t j0, int64_t j1, int64_t ray_first, int64_t ray_last, double *a1o,     \
+    DevGeom g, LearnGeom lg, const double2 *__restrict__ lxy, const double *__restrict__ lm,      \
+        const int32_t *__restrict__ cell_start, const double *__restrict__ corner, int32_t cy0,   \
+        const float *__restrict__ tab, const int2 *__restrict__ lcol,                             \
+        const LearnRow *__restrict__ lrow, int64_t ray_first, int64_t ray_last, double *a1o,      \
         double *a2o, int64_t *pixo, uint32_t *counts, unsigned long long *landed
-template <bool UNIT, bool CORNER>
-__device__ __forceinline__ void learned_rays(IRS_LEARNED_RAY_ARGS)
+#define IRS_LEARNED_RAY_PASS                                                                      \
+    g, lg, lxy, lm, cell_start, corner, cy0, tab, lcol, lrow, ray_first, ray_last, a1o, a2o, pixo, \
+        counts, landed
+template <bool UNIT, bool CORNER, int THREADS>
+__device__ __forceinline__ void learned_rays(IRS_LEARNED_RAY_ARGS, const RaySpan &sp)
 {
     extern __shared__ uint4 s_raw[];
-    float *s_tab = reinterpret_cast<float *>(s_raw);          // node-major: [node][16]
-    for (int e = threadIdx.x; e < kLNodes * kNO; e += blockDim.x)
-        s_tab[e] = tab[(int64_t)(e % kNO) * kLNodes + e / kNO];
+    float *s_tab = reinterpret_cast<float *>(s_raw);          // node-major, kLPitch a node
+    for (int e = threadIdx.x; e < kLNodes * kNO; e += THREADS)
+        s_tab[e % kLNodes * kLPitch + e / kLNodes] = tab[e];
     __syncthreads();
     const int lane = threadIdx.x % kW;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kW);   // items are wave-uniform
-    constexpr int kWaves = kL3Threads / kW;
+    constexpr int kWaves = THREADS / kW;
     constexpr int R = kLearnRows;
-    const int64_t ntx = (i1 - i0 + kW - 1) / kW;
-    const int64_t items = (j1 - j0 + R - 1) / R * ntx;
+    static_assert(R == kNearGroup, "a lane's rows share a reciprocal");
+    const int64_t ntx = (sp.i1 - sp.i0 + kW - 1) / kW;
+    const int64_t jb = sp.j0 / R * R;                         // the first group's first row
+    const int64_t items = (sp.j1 - jb + kLearnItem - 1) / kLearnItem * ntx;
     const int q1 = lg.qc + 1;
-    const int64_t nyc = (int64_t)g.n1y * lg.qc;
-    auto cell_row = [&](int64_t j) { return (int32_t)(((2 * j + 1) * nyc) / (2 * g.ny) / lg.qc); };
+    const int32_t ny1 = (int32_t)g.ny - 1;
     unsigned long long nland = 0;
     for (int64_t it = (int64_t)blockIdx.x * kWaves + wave; it < items; it += (int64_t)gridDim.x * kWaves) {
-        // rows jg .. jg + nr - 1 of one column per lane
-        const int64_t jg = j0 + (it / ntx) * R;
-        const int nr = (int)min<int64_t>(R, j1 - jg);
-        const int64_t i = i0 + (it % ntx) * kW + lane;
-        const bool in_col = i < i1;
+        const int64_t ig = floor_div(it, ntx);
+        const int64_t i = sp.i0 + (it - ig * ntx) * kW + lane;
+        const bool in_col = i < sp.i1;
         // the lane's square column and level-1 column (lanes past the
         // range take its last column)
-        const int2 sq = lcol[in_col ? i : i1 - 1];
-        const double t1 = ray_x(g, in_col ? i : i1 - 1);
-        double t2s[R], n1[R], n2[R];
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            t2s[k] = ray_y(g, jg + min(k, nr - 1));     // rows past the range repeat the last
-            n1[k] = 0.0;
-            n2[k] = 0.0;
-        }
-        // nearby lenses, exactly, in a loop the whole wave shares: the lens
-        // data come in scalar loads, each lens serves all the lane's rows of
-        // one level-1 row; where the wave's columns straddle two level-1
-        // columns a lane gives the lenses outside its own 3 x 3 cells mass 0,
-        // adding exact zeros
-        {
-            const int32_t cxl = sq.y;
-            // columns grow with the lane: lane 0 has the first, lane 63 the last
-            const int32_t cxa = __builtin_amdgcn_readfirstlane(cxl);
-            const int32_t cxb = __builtin_amdgcn_readlane(cxl, kW - 1);
-            const int32_t cl = cxa > 0 ? cxa - 1 : 0, ch = cxb < g.n1x - 1 ? cxb + 1 : g.n1x - 1;
-            const int32_t xl = cxl > 0 ? cxl - 1 : 0, xh = cxl < g.n1x - 1 ? cxl + 1 : g.n1x - 1;
-            const bool straddle = cxa != cxb;
-            auto pass = [&](int32_t cyr, auto rows) {           // rows: compile-time [k0, k1)
-                constexpr int k0 = decltype(rows)::first, k1 = decltype(rows)::last;
-                const int32_t yl = cyr > 0 ? cyr - 1 : 0, yh = cyr < g.n1y - 1 ? cyr + 1 : g.n1y - 1;
-                for (int32_t row = yl; row <= yh; ++row) {
-                    const int32_t pb = cell_start[row * g.n1x + cl];
-                    const int32_t pe = cell_start[row * g.n1x + ch + 1];
-                    int32_t lpb = pb, lpe = pe;
-                    if (straddle) {
-                        lpb = cell_start[row * g.n1x + xl];
-                        lpe = cell_start[row * g.n1x + xh + 1];
-                    }
-                    for (int32_t q_ = pb; q_ < pe; ++q_) {
-                        double m = UNIT ? 1.0 : lm[q_];
-                        if (straddle) m = (q_ >= lpb && q_ < lpe) ? m : 0.0;
-                        const double zx = lx[q_], zy = ly[q_];
-#pragma unroll
-                        for (int k = k0; k < k1; ++k) near_lens(t1, t2s[k], zx, zy, m, n1[k], n2[k]);
-                    }
-                }
-            };
-            const int32_t cyA = cell_row(jg), cyB = cell_row(jg + nr - 1);   // wave-uniform
-            if (cyA == cyB) {
-                pass(cyA, RowSpan<0, R>{});
-            } else {                                        // rows sorted: split by cell row
-#pragma unroll
-                for (int k = 0; k < R; ++k)
-                    if (k < nr) {
-                        const int32_t cyk = cell_row(jg + k);
-                        if (k == 0) pass(cyk, RowSpan<0, 1>{});
-                        else if (k == 1) pass(cyk, RowSpan<1, 2>{});
-                        else if (k == 2) pass(cyk, RowSpan<2, 3>{});
-                        else pass(cyk, RowSpan<3, 4>{});
-                    }
-            }
-        }
-        // per row: the square's corners (cached loads) and, when the square
-        // row changes (a wave-uniform test), its local data; then each ray's
-        // base interpolant, learned correction, pixel and bin
-        const int64_t gxc = sq.x, cx = sq.y;
-        const int a = (int)(gxc - cx * lg.qc);
+        const int2 sq = lcol[in_col ? i : sp.i1 - 1];
+        const double t1 = ray_x(g, in_col ? i : sp.i1 - 1);
+        const int32_t gxc = sq.x, cx = sq.y;
+        const int a = gxc - cx * lg.qc;
         const double X0 = corner_x(g, lg, gxc), X1 = corner_x(g, lg, gxc + 1);
         const float hx = (float)((t1 - X0) / lg.sx);
         float D[16];
-        double sig = 0.0;
-        int64_t cgy = -1;
+        double sig = 0.0, C[4][4];
+        int32_t cgy = -1;                                     // the square row they hold
+        const int32_t je = (int32_t)min<int64_t>(sp.j1, jb + (ig + 1) * kLearnItem);
+        // rows jg .. jg + R - 1 of one column per lane; those outside the
+        // range [j0, j1) bin nothing
+#pragma unroll 1
+        for (int32_t jg = (int32_t)(jb + ig * kLearnItem); jg < je; jg += R) {
+            auto row = [&](int k) -> const LearnRow & { return lrow[min(jg + k, ny1)]; };
+            double t2s[R], n1[R], n2[R];
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if (k >= nr) break;                             // wave-uniform
-            const int64_t j = jg + k;
-            const int64_t gyc = ((2 * j + 1) * nyc) / (2 * g.ny);
-            const int64_t cy = gyc / lg.qc;
-            const double Y0 = corner_y(g, lg, gyc), Y1 = corner_y(g, lg, gyc + 1);
-            double C[4][4];
-            load_corners(corner, (cy - cy0) * g.n1x + cx, q1, a, (int)(gyc - cy * lg.qc), C);
-            if (gyc != cgy) {                               // wave-uniform
-                square_local(C, X0, X1, Y0, Y1, lg, D, sig);
-                cgy = gyc;
+            for (int k = 0; k < R; ++k) {
+                t2s[k] = row(k).t2;              // (a row past the grid repeats the last)
+                n1[k] = 0.0;
+                n2[k] = 0.0;
             }
-            const double t2 = t2s[k];
-            const int64_t r = j * g.nx + i;
-            bool valid = in_col && r >= ray_first && r < ray_last;
-            if (!CORNER && g.sheet && corner_cell_l(g, cx, cy)) valid = false;
-            int32_t pix = -1;
-            if (valid) {
-                const double dhy = (t2 - Y0) / lg.sy;
-                double Ar, Ai;
-                square_base(C, X0, X1, Y0, Y1, t1, t2, (double)hx, dhy, Ar, Ai);
-                if (g.sheet) {
-                    if constexpr (CORNER) {
-                        double I1, I2;
-                        sheet_unit(g, t1, t2, I1, I2);
-                        const double f = -g.kappa_star / M_PI;
-                        Ar += f * I1;
-                        Ai -= f * I2;
-                    } else {
-                        Ar -= g.kappa_star * t1;          // -kappa_* conj(z)
-                        Ai += g.kappa_star * t2;
+            // nearby lenses, exactly, in a loop the whole wave shares: the lens
+            // data come in scalar loads, each lens serves all the lane's rows of
+            // one level-1 row, which share its reciprocal; where the wave's
+            // columns straddle two level-1 columns a lane gives the lenses outside
+            // its own 3 x 3 cells mass 0, adding exact zeros
+            {
+                const int32_t cxl = sq.y;
+                // columns grow with the lane: lane 0 has the first, lane 63 the last
+                const int32_t cxa = __builtin_amdgcn_readfirstlane(cxl);
+                const int32_t cxb = __builtin_amdgcn_readlane(cxl, kW - 1);
+                const int32_t cl = cxa > 0 ? cxa - 1 : 0, ch = cxb < g.n1x - 1 ? cxb + 1 : g.n1x - 1;
+                const int32_t xl = cxl > 0 ? cxl - 1 : 0, xh = cxl < g.n1x - 1 ? cxl + 1 : g.n1x - 1;
+                const bool straddle = cxa != cxb;
+                auto pass = [&](int32_t cyr, auto term) {
+                    const int32_t yl = cyr > 0 ? cyr - 1 : 0, yh = cyr < g.n1y - 1 ? cyr + 1 : g.n1y - 1;
+                    for (int32_t cr = yl; cr <= yh; ++cr) {
+                        const int32_t pb = cell_start[cr * g.n1x + cl];
+                        const int32_t pe = cell_start[cr * g.n1x + ch + 1];
+                        int32_t lpb = pb, lpe = pe;
+                        if (straddle) {
+                            lpb = cell_start[cr * g.n1x + xl];
+                            lpe = cell_start[cr * g.n1x + xh + 1];
+                        }
+                        for (int32_t q_ = pb; q_ < pe; ++q_) {
+                            double m = UNIT ? 1.0 : lm[q_];
+                            if (straddle) m = (q_ >= lpb && q_ < lpe) ? m : 0.0;
+                            term(lxy[q_], m);
+                        }
+                    }
+                };
+                const int32_t cyA = row(0).cy;                    // wave-uniform
+                if (cyA == row(R - 1).cy) {
+                    pass(cyA, [&](const double2 &z, double m) {
+                        const double d1 = t1 - z.x;
+                        near_group<R>(d1, d1 * d1, t2s, z.y, m, n1, n2);
+                    });
+                } else {                                          // each row with its own cell row
+#pragma unroll
+                    for (int k = 0; k < R; ++k)
+                        pass(row(k).cy, [&](const double2 &z, double m) {
+                            const double d1 = t1 - z.x;
+                            near_term(d1, fma(d1, d1, kNearTiny), t2s[k], z.y, m, n1[k], n2[k]);
+                        });
+                }
+            }
+            // per row: the square's corners and local data when the square row
+            // changes (a wave-uniform test), then each ray's base interpolant,
+            // learned correction, pixel and bin
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                const int64_t j = jg + k;
+                if (j < sp.j0 || j >= sp.j1) continue;          // wave-uniform
+                const LearnRow &rk = row(k);
+                const int32_t cy = rk.cy;
+                const double Y0 = rk.Y0, Y1 = rk.Y1;
+                if (rk.gyc != cgy) {                            // wave-uniform
+                    load_corners(corner, (int64_t)(cy - cy0) * g.n1x + cx, q1, a, rk.gyc - cy * lg.qc, C);
+                    square_local(C, X0, X1, Y0, Y1, lg, D, sig);
+                    cgy = rk.gyc;
+                }
+                const double t2 = t2s[k];
+                const int64_t r = j * g.nx + i;
+                bool valid = in_col && r >= ray_first && r < ray_last;
+                if (!CORNER && g.sheet && corner_cell_l(g, cx, cy)) valid = false;
+                int32_t pix = -1;
+                if (valid) {
+                    const double dhy = rk.hy;
+                    double Ar, Ai;
+                    square_base(C, X0, X1, Y0, Y1, t1, t2, (double)hx, dhy, Ar, Ai);
+                    if (g.sheet) {
+                        if constexpr (CORNER) {
+                            double I1, I2;
+                            sheet_unit(g, t1, t2, I1, I2);
+                            const double f = -g.kappa_star / M_PI;
+                            Ar += f * I1;
+                            Ai -= f * I2;
+                        } else {
+                            Ar -= g.kappa_star * t1;          // -kappa_* conj(z)
+                            Ai += g.kappa_star * t2;
+                        }
+                    }
+                    float pr, pi;
+                    ltab_combine(s_tab, hx, (float)dhy, D, pr, pi);
+                    // alpha: the near lenses, the macro term, the base
+                    // interpolant and the conjugate of the learned correction
+                    const double a1 = (g.kpg * t1 + n1[k] + Ar) + sig * (double)pr;
+                    const double a2 = (g.kmg * t2 + n2[k] - Ai) - sig * (double)pi;
+                    int32_t px, py;
+                    if (pixel_xy_shifted(g, (t1 - a1) + g.half_side, (t2 - a2) + g.half_side, px, py))
+                        pix = py * g.npix + px;
+                    if (!counts) {
+                        const int64_t o = r - ray_first;
+                        if (a1o) a1o[o] = a1;
+                        if (a2o) a2o[o] = a2;
+                        if (pixo) pixo[o] = pix;
                     }
                 }
-                float pr, pi;
-                ltab_combine<kNO, 1>(s_tab, hx, (float)dhy, D, pr, pi);
-                // alpha: the near lenses, the macro term, the base
-                // interpolant and the conjugate of the learned correction
-                const double a1 = (g.kpg * t1 + n1[k] + Ar) + sig * (double)pr;
-                const double a2 = (g.kmg * t2 + n2[k] - Ai) - sig * (double)pi;
-                pix = pixel_of(g, t1 - a1, t2 - a2);
-                if (!counts) {
-                    const int64_t o = r - ray_first;
-                    if (a1o) a1o[o] = a1;
-                    if (a2o) a2o[o] = a2;
-                    if (pixo) pixo[o] = pix;
+                if (counts) {
+                    bin_runs(counts, pix);
+                    nland += __popcll(__ballot(pix >= 0));
                 }
             }
-            if (counts) {
-                bin_runs(counts, pix);
-                nland += __popcll(__ballot(pix >= 0));
-            }
-            asm volatile("" ::: "memory");      // keep the next row's corner loads in its row
         }
     }
     if (counts && lane == 0 && nland) landed_add(landed, nland);
 }
 
-#define IRS_LEARNED_RAY_PASS                                                                      \
-    g, lg, lx, ly, lm, cell_start, corner, cy0, tab, lcol, i0, i1, j0, j1, ray_first, ray_last, a1o, \
-        a2o, pixo, counts, landed
-// three waves a SIMD: two workgroups of six waves a CU (the table's LDS allows two)
 template <bool UNIT>
-__global__ __launch_bounds__(kL3Threads, 3) void k_level3_learned(IRS_LEARNED_RAY_ARGS)
+__global__ __launch_bounds__(kL3Threads, 3) void k_level3_learned(IRS_LEARNED_RAY_ARGS, RaySpan sp)
 {
-    learned_rays<UNIT, false>(IRS_LEARNED_RAY_PASS);
+    learned_rays<UNIT, false, kL3Threads>(IRS_LEARNED_RAY_PASS, sp);
 }
-// the corner cells: fewer waves, no spills
+// the corner cells (blockIdx.y: which): fewer waves, no spills
 template <bool UNIT>
-__global__ __launch_bounds__(kL3Threads) void k_level3_learned_corner(IRS_LEARNED_RAY_ARGS)
+__global__ __launch_bounds__(kL3CornerThreads) void k_level3_learned_corner(IRS_LEARNED_RAY_ARGS,
+                                                                            RaySpans sps)
 {
-    learned_rays<UNIT, true>(IRS_LEARNED_RAY_PASS);
+    learned_rays<UNIT, true, kL3CornerThreads>(IRS_LEARNED_RAY_PASS, sps.s[blockIdx.y]);
 }
 #undef IRS_LEARNED_RAY_PASS
 #undef IRS_LEARNED_RAY_ARGS
@@ -1218,7 +1254,7 @@ int device_cus()
 }
 
 constexpr size_t kMlpSmem = sizeof(MlpSmem);
-constexpr size_t kLTabSmem = sizeof(float) * kLNodes * kNO;
+constexpr size_t kLTabSmem = sizeof(float) * kLNodes * kLPitch;
 
 irs_status set_smem_limits()
 {
@@ -1660,22 +1696,16 @@ irs_status launch_learned(irs_plan_s *p, const RaySel &sel)
         dev_free(p->d_lcol);
         p->d_lcol = nullptr;
         p->lcol_qc = 0;
-        IRS_HIP(dev_alloc(&p->d_lcol, sizeof(int2) * (size_t)g.nx));
-        hipLaunchKernelGGL(k_learn_cols, dim3((unsigned)((g.nx + kThreads - 1) / kThreads)),
-                           dim3(kThreads), 0, p->stream, g, (int32_t)qc, (int2 *)p->d_lcol);
+        IRS_HIP(dev_alloc(&p->d_lcol, sizeof(LearnRow) * (size_t)g.ny + sizeof(int2) * (size_t)g.nx));
+        hipLaunchKernelGGL(k_learn_cols,
+                           dim3((unsigned)((std::max(g.nx, g.ny) + kThreads - 1) / kThreads)),
+                           dim3(kThreads), 0, p->stream, g, lg,
+                           (int2 *)((LearnRow *)p->d_lcol + g.ny), (LearnRow *)p->d_lcol);
         IRS_HIP(hipGetLastError());
         p->lcol_qc = qc;
     }
     CallStats *cs = sel.stats;
     const int ncu = device_cus();
-    int per_cu = 0;                         // resident workgroups per CU (the table in LDS)
-    if (p->unit_mass)
-        IRS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_level3_learned<true>,
-                                                             kL3Threads, kLTabSmem));
-    else
-        IRS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_level3_learned<false>,
-                                                             kL3Threads, kLTabSmem));
-    per_cu = std::max(1, per_cu);
     for (int64_t c0 = cyA; c0 <= cyB; c0 += p->corner_rows_cap) {
         const int64_t c1 = std::min(cyB, c0 + p->corner_rows_cap - 1);
         if (!(p->corner_c0 <= c0 && c1 <= p->corner_c1)) {
@@ -1708,41 +1738,46 @@ irs_status launch_learned(irs_plan_s *p, const RaySel &sel)
             if (st != IRS_OK) return st;
             cs->n_rays++;
         }
-        // rays of columns [i0, i1), rows [ja, jb): the main kernel, or one
-        // corner cell's
-        auto launch = [&](bool corner_cell, int64_t i0, int64_t i1, int64_t ja, int64_t jb) {
-            const int64_t items = (jb - ja + kLearnRows - 1) / kLearnRows * ((i1 - i0 + kW - 1) / kW);
-            const unsigned nb = (unsigned)std::max<int64_t>(
-                1, std::min<int64_t>((int64_t)per_cu * ncu, (items + kL3Threads / kW - 1) / (kL3Threads / kW)));
-#define IRS_L3L(K)                                                                                 \
-    hipLaunchKernelGGL(K, dim3(nb), dim3(kL3Threads), kLTabSmem, p->stream, g, lg, p->d_x, p->d_y,  \
-                       p->d_m, p->d_cell_start, p->d_corner, (int32_t)p->corner_c0, p->d_ltab,      \
-                       (const int2 *)p->d_lcol, i0,                                                \
-                       i1, ja, jb, sel.ray_first, sel.ray_last, sel.alpha1, sel.alpha2, sel.pixel, \
-                       sel.counts, sel.landed)
-            if (p->unit_mass) {
-                if (corner_cell) IRS_L3L(k_level3_learned_corner<true>);
-                else IRS_L3L(k_level3_learned<true>);
-            } else {
-                if (corner_cell) IRS_L3L(k_level3_learned_corner<false>);
-                else IRS_L3L(k_level3_learned<false>);
-            }
-#undef IRS_L3L
+        // workgroups of `threads` for a range: one a CU at most (the table)
+        auto blocks = [&](const RaySpan &sp, int threads) {
+            const int64_t items = (sp.j1 - sp.j0 / kLearnRows * kLearnRows + kLearnItem - 1) / kLearnItem *
+                                  ((sp.i1 - sp.i0 + kW - 1) / kW);
+            return (unsigned)std::max<int64_t>(
+                1, std::min<int64_t>(ncu, (items + threads / kW - 1) / (threads / kW)));
         };
-        launch(false, 0, g.nx, jA, jB);
+#define IRS_L3L(K, GRID, THREADS, SPANS)                                                           \
+    hipLaunchKernelGGL(K, GRID, dim3(THREADS), kLTabSmem, p->stream, g, lg,                        \
+                       (const double2 *)p->d_xy, p->d_m, p->d_cell_start, p->d_corner,             \
+                       (int32_t)p->corner_c0, p->d_ltab,                                           \
+                       (const int2 *)((const LearnRow *)p->d_lcol + g.ny),                         \
+                       (const LearnRow *)p->d_lcol, sel.ray_first, sel.ray_last, sel.alpha1,    \
+                       sel.alpha2, sel.pixel, sel.counts, sel.landed, SPANS)
+        const RaySpan all{0, g.nx, jA, jB};
+        if (p->unit_mass) IRS_L3L(k_level3_learned<true>, dim3(blocks(all, kL3Threads)), kL3Threads, all);
+        else IRS_L3L(k_level3_learned<false>, dim3(blocks(all, kL3Threads)), kL3Threads, all);
         if (g.sheet) {
-            // the rectangle's corner cells (distinct ones) that meet these rows
+            // the rectangle's corner cells (distinct ones) that meet these
+            // rows, in one launch
             const int64_t cxs[2] = {0, g.n1x - 1}, cys[2] = {0, g.n1y - 1};
+            RaySpans sps{};
+            unsigned ns = 0, nb = 1;
             for (int ky = 0; ky < (g.n1y > 1 ? 2 : 1); ++ky)
                 for (int kx = 0; kx < (g.n1x > 1 ? 2 : 1); ++kx) {
-                    int64_t ia, ib, ra, rb;
-                    level1_span(p->geo.info, 0, cxs[kx], ia, ib);
-                    level1_span(p->geo.info, 1, cys[ky], ra, rb);
-                    ra = std::max(ra, jA);
-                    rb = std::min(rb, jB);
-                    if (ia < ib && ra < rb) launch(true, ia, ib, ra, rb);
+                    RaySpan c;
+                    level1_span(p->geo.info, 0, cxs[kx], c.i0, c.i1);
+                    level1_span(p->geo.info, 1, cys[ky], c.j0, c.j1);
+                    c.j0 = std::max(c.j0, jA);
+                    c.j1 = std::min(c.j1, jB);
+                    if (c.i0 >= c.i1 || c.j0 >= c.j1) continue;
+                    sps.s[ns++] = c;
+                    nb = std::max(nb, blocks(c, kL3CornerThreads));
                 }
+            if (ns) {
+                if (p->unit_mass) IRS_L3L(k_level3_learned_corner<true>, dim3(nb, ns), kL3CornerThreads, sps);
+                else IRS_L3L(k_level3_learned_corner<false>, dim3(nb, ns), kL3CornerThreads, sps);
+            }
         }
+#undef IRS_L3L
         IRS_HIP(hipGetLastError());
         if (cs && (st = cs->end(p->stream)) != IRS_OK) return st;
     }
