@@ -855,19 +855,100 @@ __device__ __forceinline__ bool sheet_closed_form(const DevGeom &g, int32_t fold
     return g.sheet && !corner_cell(g, cx, cy) && !(fold && sheet_fold_ok(g, cx, cy));
 }
 
-// CLOSED = false: the cells that do not take the closed form; CLOSED = true:
-// the cells that do (a workgroup with none returns at once).  The closed
-// form's logarithms would otherwise set every point's register budget.
-// STAGED: the ring lenses of a workgroup's four cells, which lie in one block
-// of 7 rows x 10 columns of cells, are staged in LDS once; the host takes this
-// instance when no such block of the plan holds more than kRingCap lenses
-// (ring_fits), the other reads them from global memory.
 constexpr int kRingCap = 768;
 constexpr int kRingRows = 2 * kRing + 1, kRingCols = kCellsPerBlock + 2 * kRing;
 // a cell's ring as runs of cells in one row: one run in each of the 2 kRing - 2
 // outer rows, two (left and right of the 3 x 3 block) in each of the 3 inner
 constexpr int kRingSegs = (kRingRows - 3) + 2 * 3;
 
+// The ring lenses of a workgroup's four cells (one level-1 row), which lie in
+// one block of 7 rows x 10 columns of cells.  STAGED: the lenses are copied to
+// LDS; the host takes such an instance when no such block of the plan holds
+// more than kRingCap lenses (ring_fits).
+template <bool UNIT, bool STAGED>
+struct RingLds {
+    static constexpr int kCap = STAGED ? kRingCap : 1;
+    double rx[kCap], ry[kCap], rm[UNIT ? 1 : kCap];
+    int32_t cs[kRingRows][kRingCols + 1];     // cell_start over the block
+    int32_t rb[kRingRows + 1];                // LDS offset of each row
+    int2 seg[kCellsPerBlock][kRingSegs];      // STAGED: each cell's runs in LDS
+    int32_t ya, yb, ua;                       // the block's rows and first column
+};
+
+// Fills it (every thread of the workgroup; ends synchronised).
+template <bool UNIT, bool STAGED>
+__device__ __forceinline__ void stage_ring(RingLds<UNIT, STAGED> &sm, const DevGeom &g,
+                                           const double *__restrict__ lx,
+                                           const double *__restrict__ ly,
+                                           const double *__restrict__ lm,
+                                           const int32_t *__restrict__ cell_start, int32_t cy,
+                                           int32_t cx0)
+{
+    const int tid = threadIdx.x;
+    // the block of cells holding every ring lens of the four cells
+    const int32_t ya = max(0, cy - kRing), yb = min(g.n1y - 1, cy + kRing);
+    const int32_t ua = max(0, cx0 - kRing), ub = min(g.n1x - 1, cx0 + kCellsPerBlock - 1 + kRing);
+    const int nrow = yb - ya + 1, ncol = ub - ua + 1;
+    if (tid == 0) {
+        sm.ya = ya;
+        sm.yb = yb;
+        sm.ua = ua;
+    }
+    for (int e = tid; e < nrow * (ncol + 1); e += kThreads) {
+        const int r = e / (ncol + 1), c = e % (ncol + 1);
+        sm.cs[r][c] = cell_start[(int64_t)(ya + r) * g.n1x + ua + c];
+    }
+    __syncthreads();
+    if (tid == 0) {
+        sm.rb[0] = 0;
+        for (int r = 0; r < nrow; ++r) sm.rb[r + 1] = sm.rb[r] + (sm.cs[r][ncol] - sm.cs[r][0]);
+    }
+    __syncthreads();
+    if constexpr (STAGED) {
+        const int total = min(sm.rb[nrow], kRingCap);               // == rb[nrow] (ring_fits)
+        for (int i = tid; i < total; i += kThreads) {
+            int r = 0;
+            while (sm.rb[r + 1] <= i) ++r;
+            const int32_t src = sm.cs[r][0] + (i - sm.rb[r]);
+            sm.rx[i] = lx[src];
+            sm.ry[i] = ly[src];
+            if (!UNIT) sm.rm[i] = lm[src];
+        }
+        // each cell's runs of ring cells as ranges of the staged lenses, in
+        // row order (rows cy - kRing .. cy + kRing; left run before right)
+        if (tid < kCellsPerBlock * kRingSegs) {
+            const int w = tid / kRingSegs, sg = tid % kRingSegs;
+            const int outer = kRing - 1;                      // outer rows on each side
+            int dr, kind;                                     // kind 0: whole, 1: left, 2: right
+            if (sg < outer) { dr = sg - kRing; kind = 0; }
+            else if (sg < outer + 6) { dr = (sg - outer) / 2 - 1; kind = 1 + ((sg - outer) & 1); }
+            else { dr = sg - outer - 6 + 2; kind = 0; }
+            const int32_t row = cy + dr, ccx = cx0 + w;
+            int2 be = {0, 0};
+            if (row >= ya && row <= yb && ccx < g.n1x) {
+                int32_t xa = kind == 2 ? ccx + 2 : ccx - kRing;
+                int32_t xb = kind == 1 ? ccx - 2 : ccx + kRing;
+                xa = max(xa, 0);
+                xb = min(xb, g.n1x - 1);
+                if (xa <= xb) {
+                    const int r = row - ya;
+                    const int32_t off = sm.rb[r] - sm.cs[r][0];
+                    be.x = min(sm.cs[r][xa - ua] + off, kRingCap);
+                    be.y = min(sm.cs[r][xb + 1 - ua] + off, kRingCap);
+                }
+            }
+            sm.seg[w][sg] = be;
+        }
+    }
+    __syncthreads();
+}
+
+// The level-2 points of four cells, one a lane: the cell expansion by one
+// Horner pass and the ring lenses one by one.  Takes what k_level2_cells does
+// not: CLOSED: the cells whose sheet takes the closed form (a workgroup with
+// none returns at once; its logarithms would otherwise set every point's
+// register budget); STAGED = false: plans with denser rings than kRingCap; and
+// coarse grids of fewer points than that kernel's lanes.
 template <bool UNIT, int P, bool CLOSED, bool STAGED>
 __global__ __launch_bounds__(kThreads) void k_level2_points(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
@@ -876,11 +957,7 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
     double *__restrict__ coef)
 {
     __shared__ double s_L[kCellsPerBlock][P][2];
-    constexpr int kCap = STAGED ? kRingCap : 1;
-    __shared__ double s_rx[kCap], s_ry[kCap], s_rm[UNIT ? 1 : kCap];
-    __shared__ int32_t s_cs[kRingRows][kRingCols + 1];   // cell_start over the block
-    __shared__ int32_t s_rb[kRingRows + 1];              // LDS offset of each row
-    __shared__ int2 s_seg[kCellsPerBlock][kRingSegs];    // STAGED: each cell's runs in LDS
+    __shared__ RingLds<UNIT, STAGED> ring;
     const int tid = threadIdx.x;
     const int32_t cy = cy0 + (int32_t)(blockIdx.x / (uint32_t)nxb);
     const int32_t cx0 = (int32_t)(blockIdx.x % (uint32_t)nxb) * kCellsPerBlock;
@@ -903,57 +980,7 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
         }
         s_L[w][n][comp] = acc;
     }
-    // the block of cells holding every ring lens of the four cells
-    const int32_t ya = max(0, cy - kRing), yb = min(g.n1y - 1, cy + kRing);
-    const int32_t ua = max(0, cx0 - kRing), ub = min(g.n1x - 1, cx0 + kCellsPerBlock - 1 + kRing);
-    const int nrow = yb - ya + 1, ncol = ub - ua + 1;
-    for (int e = tid; e < nrow * (ncol + 1); e += kThreads) {
-        const int r = e / (ncol + 1), c = e % (ncol + 1);
-        s_cs[r][c] = cell_start[(int64_t)(ya + r) * g.n1x + ua + c];
-    }
-    __syncthreads();
-    if (tid == 0) {
-        s_rb[0] = 0;
-        for (int r = 0; r < nrow; ++r) s_rb[r + 1] = s_rb[r] + (s_cs[r][ncol] - s_cs[r][0]);
-    }
-    __syncthreads();
-    if constexpr (STAGED) {
-        const int total = min(s_rb[nrow], kRingCap);               // == s_rb[nrow] (ring_fits)
-        for (int i = tid; i < total; i += kThreads) {
-            int r = 0;
-            while (s_rb[r + 1] <= i) ++r;
-            const int32_t src = s_cs[r][0] + (i - s_rb[r]);
-            s_rx[i] = lx[src];
-            s_ry[i] = ly[src];
-            if (!UNIT) s_rm[i] = lm[src];
-        }
-        // each cell's runs of ring cells as ranges of the staged lenses, in
-        // row order (rows cy - kRing .. cy + kRing; left run before right)
-        if (tid < kCellsPerBlock * kRingSegs) {
-            const int w = tid / kRingSegs, sg = tid % kRingSegs;
-            const int outer = kRing - 1;                      // outer rows on each side
-            int dr, kind;                                     // kind 0: whole, 1: left, 2: right
-            if (sg < outer) { dr = sg - kRing; kind = 0; }
-            else if (sg < outer + 6) { dr = (sg - outer) / 2 - 1; kind = 1 + ((sg - outer) & 1); }
-            else { dr = sg - outer - 6 + 2; kind = 0; }
-            const int32_t row = cy + dr, ccx = cx0 + w;
-            int2 be = {0, 0};
-            if (row >= ya && row <= yb && ccx < g.n1x) {
-                int32_t xa = kind == 2 ? ccx + 2 : ccx - kRing;
-                int32_t xb = kind == 1 ? ccx - 2 : ccx + kRing;
-                xa = max(xa, 0);
-                xb = min(xb, g.n1x - 1);
-                if (xa <= xb) {
-                    const int r = row - ya;
-                    const int32_t off = s_rb[r] - s_cs[r][0];
-                    be.x = min(s_cs[r][xa - ua] + off, kRingCap);
-                    be.y = min(s_cs[r][xb + 1 - ua] + off, kRingCap);
-                }
-            }
-            s_seg[w][sg] = be;
-        }
-    }
-    __syncthreads();
+    stage_ring(ring, g, lx, ly, lm, cell_start, cy, cx0);
 
     // ---- phase B: the level-2 points of the four cells
     const int q = g.q, npts = q * q;
@@ -1010,11 +1037,12 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
         };
         if constexpr (STAGED) {
             for (int sg = 0; sg < kRingSegs; ++sg) {
-                const int2 be = s_seg[w][sg];
-                for (int32_t pl = be.x; pl < be.y; ++pl) ring_lens(s_rx[pl], s_ry[pl], UNIT ? 1.0 : s_rm[pl]);
+                const int2 be = ring.seg[w][sg];
+                for (int32_t pl = be.x; pl < be.y; ++pl)
+                    ring_lens(ring.rx[pl], ring.ry[pl], UNIT ? 1.0 : ring.rm[pl]);
             }
         } else {
-            for (int32_t row = ya; row <= yb; ++row) {
+            for (int32_t row = ring.ya; row <= ring.yb; ++row) {
                 const bool mid = abs(row - cy) <= 1;
                 for (int seg = 0; seg < (mid ? 2 : 1); ++seg) {
                     int32_t xa, xb;
@@ -1024,8 +1052,8 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
                     xa = max(xa, 0);
                     xb = min(xb, g.n1x - 1);
                     if (xa > xb) continue;
-                    const int r = row - ya;
-                    const int32_t pb = s_cs[r][xa - ua], pe = s_cs[r][xb + 1 - ua];
+                    const int r = row - ring.ya;
+                    const int32_t pb = ring.cs[r][xa - ring.ua], pe = ring.cs[r][xb + 1 - ring.ua];
                     for (int32_t pl = pb; pl < pe; ++pl) ring_lens(lx[pl], ly[pl], UNIT ? 1.0 : lm[pl]);
                 }
             }
@@ -1047,6 +1075,228 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
         for (int o = 0; o < 5; ++o) {
             dst[2 * o] = c[o].r;
             dst[2 * o + 1] = c[o].i;
+        }
+    }
+}
+
+// -------------------------------------------------------------------------
+// Level-2 points from one expansion per cell that holds the ring lenses too.
+//
+// Outside the 3 x 3 block the nearest lens is 1.5 cell sides from the cell's
+// centre and the furthest level-2 point half a cell diagonal, so a series about
+// the centre converges for the ring as well, at the ratio ring_order bounds
+// (0.45 for square cells of 20 x 20 points: PE = 68 terms by the order rule).
+// A wave takes a cell: it adds its ring lenses' terms
+//     E_n += sum_i m_i (-1)^n (s/(zc - z_i))^(n+1),  n < PE
+// to the cell expansion and evaluates, at each point d = (z0 - zc)/s,
+//     c_k = (1/(k! s^(k+1))) sum_m A_(m+k) d^m/m!,   A_n = n! E_n.
+// The points form a lattice symmetric about the centre.  With A_n = a_n + i b_n
+// the sums of a_n d^m/m! and of b_n d^m/m!, even and odd m apart, give the
+// value at d, -d, conj(d) and -conj(d), so a lane takes one point of the upper
+// right quarter and three mirror images: per term and derivative four FMAs for
+// four points.  The lattice's points are the ideal ones; a point's own rounded
+// position lies an ulp of its coordinate off, which one step along c_1 mends.
+//
+// Bound by FP64 issue and by writing the coefficients (80 bytes a point):
+// about 700 issue slots a point against 2,100 with every ring lens summed at
+// every point.  1e6 lenses, 4e8 points: 31.0 -> 12.8 ms, 9.5 of which remain
+// without the evaluation (32 GB of coefficients).
+// -------------------------------------------------------------------------
+// Points per cell side from which this pays (a wave has to fill its lanes with a
+// quarter of a cell).  1e5 lenses, points alone, this form against the ring
+// lenses at every point: q = 8 0.70 / 0.52 ms, 9 0.69 / 0.71, 10 0.72 / 0.83,
+// 12 0.77 / 1.09, 20 1.39 / 2.99.
+constexpr int kCellsMinQ = 9;
+constexpr int kPEMax = 80;                // terms, at most
+constexpr int kRingStep = 16;             // ring lenses a wave takes at a time
+static_assert(kPEMax % 16 == 0, "five terms a lane");
+
+struct NTable {
+    double fact[kPEMax], inv[kPEMax + 1];
+    constexpr NTable() : fact(), inv()
+    {
+        double f = 1.0;
+        for (int n = 0; n < kPEMax; ++n) {
+            fact[n] = f;
+            f *= (double)(n + 1);
+        }
+        inv[0] = 0.0;
+        for (int n = 1; n <= kPEMax; ++n) inv[n] = 1.0 / (double)n;
+    }
+};
+__constant__ NTable kN = NTable();        // n!, 1/n
+
+template <bool UNIT, int P>
+__global__ __launch_bounds__(kThreads, 3) void k_level2_cells(
+    DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
+    const double *__restrict__ lm, const int32_t *__restrict__ cell_start, int32_t cy0,
+    int32_t nxb, int32_t nchunk, int32_t fold, int32_t pe, const double *__restrict__ part,
+    double *__restrict__ coef)
+{
+    __shared__ RingLds<UNIT, true> ring;
+    __shared__ uint16_t s_idx[kCellsPerBlock][kRingCap];              // a cell's ring lenses
+    __shared__ double2 s_pow[kCellsPerBlock][kRingStep][16 + 1];      // m u (-u)^j, j < 16; (-u)^16
+    __shared__ double2 s_A[kCellsPerBlock][kPEMax + 4];
+    const int lane = threadIdx.x % kWave;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int32_t cy = cy0 + (int32_t)(blockIdx.x / (uint32_t)nxb);
+    const int32_t cx0 = (int32_t)(blockIdx.x % (uint32_t)nxb) * kCellsPerBlock;
+    stage_ring(ring, g, lx, ly, lm, cell_start, cy, cx0);
+    const int32_t cx = cx0 + w;
+    if (cx >= g.n1x || sheet_closed_form(g, fold, cx, cy)) return;    // wave-uniform; no barrier below
+    const double sc = fmax(g.w1, g.h1), isc = 1.0 / sc;
+    const double zcr = g.a1 + ((double)cx + 0.5) * g.w1, zci = g.b1 + ((double)cy + 0.5) * g.h1;
+
+    // the ring's runs laid end to end
+    int n = 0;
+    for (int sg = 0; sg < kRingSegs; ++sg) {
+        const int2 be = ring.seg[w][sg];
+        const int b = __builtin_amdgcn_readfirstlane(be.x), e = __builtin_amdgcn_readfirstlane(be.y);
+        for (int i = lane; i < e - b; i += kWave) s_idx[w][n + i] = (uint16_t)(b + i);
+        n += e - b;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // ring terms: for kRingStep lenses at a time the lanes tabulate the powers
+    // j < 16 (lane: lens lane % 16, powers 4 (lane / 16) ..), then lane
+    // (j = lane % 16, lens lane / 16 mod 4) sums the terms j, j + 16, ...
+    const int li = lane % 16, lg = lane / 16;
+    double Sr[kPEMax / 16], Si[kPEMax / 16];
+#pragma unroll
+    for (int e = 0; e < kPEMax / 16; ++e) Sr[e] = Si[e] = 0.0;
+    for (int c0 = 0; c0 < n; c0 += kRingStep) {
+        const bool use = c0 + li < n;
+        double X = zcr + sc, Y = zci, M = 0.0;                        // harmless stand-in
+        if (use) {
+            const int q = s_idx[w][c0 + li];
+            X = ring.rx[q];
+            Y = ring.ry[q];
+            M = UNIT ? 1.0 : ring.rm[q];
+        }
+        const double wr = (zcr - X) * isc, wi = (zci - Y) * isc;
+        const double inv = rcp64(wr * wr + wi * wi);
+        const cplx u = {wr * inv, -wi * inv};                         // s/(zc - z_i)
+        const cplx v = {-u.r, -u.i};
+        const cplx v2 = cmul(v, v), v4 = cmul(v2, v2), v8 = cmul(v4, v4);
+        cplx t = {M * u.r, M * u.i};
+        t = cmul(t, (lg & 1) ? v4 : cplx{1.0, 0.0});
+        t = cmul(t, (lg & 2) ? v8 : cplx{1.0, 0.0});
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            s_pow[w][li][4 * lg + j] = make_double2(t.r, t.i);
+            t = cmul(t, v);
+        }
+        if (lg == 0) {
+            const cplx v16 = cmul(v8, v8);
+            s_pow[w][li][16] = make_double2(v16.r, v16.i);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int j = 0; j < kRingStep / 4; ++j) {
+            const double2 q = s_pow[w][4 * j + lg][li], V = s_pow[w][4 * j + lg][16];
+            cplx x = {q.x, q.y};
+#pragma unroll
+            for (int e = 0; e < kPEMax / 16; ++e) {
+                Sr[e] += x.r;
+                Si[e] += x.i;
+                if (e + 1 < kPEMax / 16) x = cmul(x, cplx{V.x, V.y});
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+#pragma unroll
+    for (int e = 0; e < kPEMax / 16; ++e) {
+        Sr[e] += __shfl_xor(Sr[e], 16);
+        Si[e] += __shfl_xor(Si[e], 16);
+        Sr[e] += __shfl_xor(Sr[e], 32);
+        Si[e] += __shfl_xor(Si[e], 32);
+        const int t = 16 * e + li;
+        if (lg == (e & 3)) {
+            double ar = Sr[e], ai = Si[e];
+            if (t < P) {                       // the cell expansion, its parts in chunk order
+                const double *src = part + (((int64_t)(cy - cy0) * g.n1x + cx) * nchunk * P + t) * 2;
+                double lr = 0.0, lim = 0.0;
+                for (int k = 0; k < nchunk; ++k) {
+                    lr += src[(int64_t)k * P * 2];
+                    lim += src[(int64_t)k * P * 2 + 1];
+                }
+                ar += lr;
+                ai += lim;
+            }
+            const double f = t < pe ? kN.fact[t] : 0.0;
+            s_A[w][t] = make_double2(ar * f, ai * f);
+        }
+    }
+    if (lane < 4) s_A[w][kPEMax + lane] = make_double2(0.0, 0.0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+    // the points: lane = column ix, row iy of the upper right quarter
+    const int q = g.q, hq = (q + 1) / 2, reps = hq * hq;
+    const int64_t nxq = (int64_t)g.n1x * q;
+    const bool sheet = g.sheet && !corner_cell(g, cx, cy);
+    for (int r0 = 0; r0 < reps; r0 += kWave) {
+        const int r = min(r0 + lane, reps - 1);
+        const int ix = q - hq + r % hq, iy = q - hq + r / hq;
+        const double dr = ((double)ix - 0.5 * (double)(q - 1)) * g.w2 * isc;
+        const double di = ((double)iy - 0.5 * (double)(q - 1)) * g.h2 * isc;
+        // [k][parity of m]: sums of a d^m/m! (x, y) and of b d^m/m! (z, w)
+        double ax[5][2] = {}, ay[5][2] = {}, bx[5][2] = {}, by[5][2] = {};
+        double br = 1.0, bi = 0.0;                                    // d^m/m!
+        for (int mb = 0; mb < pe; mb += 8) {
+            double2 A[8 + 4];
+#pragma unroll
+            for (int e = 0; e < 12; ++e) A[e] = s_A[w][mb + e];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (e == 4 && mb + 4 >= pe) break;                    // pe = 4 mod 8
+#pragma unroll
+                for (int k = 0; k < 5; ++k) {
+                    ax[k][e & 1] = fma(A[e + k].x, br, ax[k][e & 1]);
+                    ay[k][e & 1] = fma(A[e + k].x, bi, ay[k][e & 1]);
+                    bx[k][e & 1] = fma(A[e + k].y, br, bx[k][e & 1]);
+                    by[k][e & 1] = fma(A[e + k].y, bi, by[k][e & 1]);
+                }
+                const double inv = kN.inv[mb + e + 1];
+                const double er = dr * inv, ei = di * inv;
+                const double nr = br * er - bi * ei;
+                bi = br * ei + bi * er;
+                br = nr;
+            }
+        }
+        if (r0 + lane >= reps) break;                                 // (the last pass)
+#pragma unroll
+        for (int sgn = 0; sgn < 4; ++sgn) {
+            // mirror images: bit 0 about the vertical, bit 1 about the horizontal
+            const bool fx = sgn & 1, fy = sgn & 2;
+            const int jx = fx ? q - 1 - ix : ix, jy = fy ? q - 1 - iy : iy;
+            if ((fx && jx == ix) || (fy && jy == iy)) continue;       // on an axis: the same point
+            const bool neg = fx, con = fx != fy;                      // at d, -conj d, conj d, -d
+            cplx c[5];
+            double sk = isc;                                          // 1/(k! s^(k+1))
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                const double pxr = neg ? ax[k][0] - ax[k][1] : ax[k][0] + ax[k][1];
+                const double pyr = neg ? ay[k][0] - ay[k][1] : ay[k][0] + ay[k][1];
+                const double qxr = neg ? bx[k][0] - bx[k][1] : bx[k][0] + bx[k][1];
+                const double qyr = neg ? by[k][0] - by[k][1] : by[k][0] + by[k][1];
+                // (px + i py) + i (qx + i qy), or the conjugates of both sums
+                c[k] = con ? cplx{(pxr + qyr) * sk, (qxr - pyr) * sk}
+                           : cplx{(pxr - qyr) * sk, (pyr + qxr) * sk};
+                sk *= isc * (1.0 / (double)(k + 1));
+            }
+            const int64_t gx = (int64_t)cx * q + jx;
+            const double x0 = level2_x(g, gx), y0 = level2_y(g, (int64_t)cy * q + jy);
+            // from the lattice's point to the rounded one: c_0 += c_1 delta
+            const double ex = fma(fx ? dr : -dr, sc, x0 - zcr), ey = fma(fy ? di : -di, sc, y0 - zci);
+            c[0].r += c[1].r * ex - c[1].i * ey;
+            c[0].i += c[1].r * ey + c[1].i * ex;
+            if (sheet) {
+                // G's series came with the cell expansion; F = conj(z) + G
+                c[0].r -= g.kappa_star * x0;
+                c[0].i += g.kappa_star * y0;
+            }
+            double2 *dst = (double2 *)(coef + (((int64_t)(cy - cy0) * q + jy) * nxq + gx) * 10);
+#pragma unroll
+            for (int o = 0; o < 5; ++o) dst[o] = make_double2(c[o].r, c[o].i);
         }
     }
 }
@@ -2023,6 +2273,24 @@ bool ring_fits(irs_plan_s *p)
     return p->ring_fit == 1;
 }
 
+// Terms of the cell expansions with the ring lenses (k_level2_cells): the order
+// rule of level2_order at the ratio of the furthest level-2 point from the
+// cell's centre to the nearest lens outside the 3 x 3 block; 0: the ring lenses
+// are summed at every point instead (grids coarser than kCellsMinQ, denser
+// rings than the staging holds, or no order up to kPEMax).
+int32_t ring_order(irs_plan_s *p)
+{
+    const DevGeom &g = p->dg;
+    if (g.q < kCellsMinQ || !ring_fits(p)) return 0;
+    const double e = 0.5 * (double)(g.q - 1) / (double)g.q;
+    const double rho = e * std::sqrt(g.w1 * g.w1 + g.h1 * g.h1) / (1.5 * std::min(g.w1, g.h1));
+    for (int P = 48; P <= kPEMax; P += 4) {
+        const double c4 = (double)P * (P - 1) * (P - 2) * (P - 3) / 24.0;
+        if (c4 * std::pow(rho, P - 4) / std::pow(1.0 - rho, 5) < 1e-14) return P;
+    }
+    return 0;
+}
+
 // super rows [Ya, Yb] that are not cached, in runs of consecutive rows
 irs_status ensure_super_rows(irs_plan_s *p, int64_t Ya, int64_t Yb, double *flops)
 {
@@ -2569,6 +2837,7 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
         // the sheet's series is in the cell expansions when they come
         // from the super-cell path (launch_level2_expand folds it)
         const int32_t fold = super_order(p) > 0 ? 1 : 0;
+        const int32_t pe = ring_order(p);
         const unsigned nbB = (unsigned)((c1 - c0 + 1) * nxb);
         double fl = 0.0;
         irs_status st3 = launch_level2_expand(p, c0, c1, cs ? &fl : nullptr, true);
@@ -2581,7 +2850,11 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
     do {                                                                                      \
         if (cs && (st2 = cs->end(s)) != IRS_OK) return st2;                                  \
         if (cs && (st2 = cs->begin(s, 2)) != IRS_OK) return st2;                             \
-        if (ring_fits(p))                                                                     \
+        if (pe > 0)                                                                           \
+            hipLaunchKernelGGL((k_level2_cells<U, PP>), dim3(nbB), dim3(kThreads), 0, s, g,     \
+                               p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, nxb,      \
+                               nchunk, fold, pe, p->d_part, coef);                           \
+        else if (ring_fits(p))                                                                \
             hipLaunchKernelGGL((k_level2_points<U, PP, false, true>), dim3(nbB), dim3(kThreads), \
                                0, s, g, p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, \
                                nxb, nchunk, fold, p->d_part, coef);                          \
