@@ -169,9 +169,8 @@ void release(irs_plan_s *p)
     dev_free(p->d_trow);
     dev_free(p->d_coef);
     dev_free(p->d_part);
-    dev_free(p->d_super);
-    dev_free(p->d_mid);
-    dev_free(p->d_super_part);
+    for (auto &l : p->tree) dev_free(l.d);
+    dev_free(p->d_tree_part);
     dev_free(p->d_counts);
     dev_free(p->d_tmp);
     dev_free(p->d_landed);
@@ -602,8 +601,8 @@ static irs_status shoot(irs_plan_t plan, int64_t row0, int64_t nrows, uint32_t *
         stats->kappa_star_eff = plan->kappa_star_eff;
         stats->ms_total = ms;
         stats->learned = (plan->params.method == IRS_LEARNED && plan->learn_ok) ? 1 : 0;
-        stats->super_cells = plan->super_k;
-        stats->mid_cells = plan->super_k > 0 ? plan->mid_k : 0;
+        stats->super_cells = plan->tree[0].k;
+        stats->mid_cells = plan->tree_n > 1 ? plan->tree[plan->tree_n - 1].k : 0;
     }
     set_error("");
     return IRS_OK;

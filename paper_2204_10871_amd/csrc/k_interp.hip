@@ -278,6 +278,23 @@ __global__ __launch_bounds__(kThreads) void k_level2(
     }
 }
 
+constexpr int kPEMax = 80;                // terms of the longest series (k_level2_cells)
+
+struct NTable {
+    double fact[kPEMax], inv[kPEMax + 1];
+    constexpr NTable() : fact(), inv()
+    {
+        double f = 1.0;
+        for (int n = 0; n < kPEMax; ++n) {
+            fact[n] = f;
+            f *= (double)(n + 1);
+        }
+        inv[0] = 0.0;
+        for (int n = 1; n <= kPEMax; ++n) inv[n] = 1.0 / (double)n;
+    }
+};
+__constant__ NTable kN = NTable();        // n!, 1/n
+
 // -------------------------------------------------------------------------
 // Level 2 through one local expansion per level-1 cell.
 //
@@ -489,10 +506,10 @@ __global__ __launch_bounds__(kThreads) void k_level2_expand(
 // Lt per cell directly.  The cell expansion is the same series as summing all
 // distant lenses into it, to FP64 rounding; the work per cell drops from N_*
 // lenses to about (2 R_S + 1)^2 K_S^2 lenses plus N_* / K_S^2, and K_S is
-// chosen per plan to balance the two (super_side).
+// chosen per plan (choose_tree).
 // -------------------------------------------------------------------------
 constexpr int kSuperR = 2;                     // R_S (and the mid cells' block radius)
-constexpr int kSuperKMax = 32;                 // largest super-cell side (cells)
+constexpr int kSuperKMax = 64;                 // largest super-cell side (cells)
 
 // centre and scale of super cell (X, Y) of side ks cells
 __device__ __forceinline__ void super_centre(const DevGeom &g, int32_t X, int32_t Y, int32_t ks,
@@ -613,18 +630,26 @@ __global__ __launch_bounds__(kThreads) void k_super_expand(
     }
 }
 
-// chunk partials summed in chunk order into the super table
-__global__ __launch_bounds__(kThreads) void k_super_reduce(const double *__restrict__ part, int64_t n_out,
-                                                           int32_t nchunk, int32_t PS,
-                                                           double *__restrict__ out)
+// chunk partials summed in chunk order into a tree level's table; eight loads
+// in flight (with one, 93 chunks took 29 us)
+__global__ __launch_bounds__(kWave) void k_super_reduce(const double *__restrict__ part, int64_t n_out,
+                                                        int32_t nchunk, int32_t PS,
+                                                        double *__restrict__ out)
 {
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t e = (int64_t)blockIdx.x * kWave + threadIdx.x;
     if (e >= n_out) return;
-    const int64_t cellterm = e / 2, comp = e % 2;
-    const int64_t cell = cellterm / PS, n = cellterm % PS;
-    const double *src = part + ((cell * nchunk) * PS + n) * 2 + comp;
+    const int64_t row = (int64_t)PS * 2;                 // doubles of an expansion
+    const double *src = part + e / row * nchunk * row + e % row;
     double acc = 0.0;
-    for (int k = 0; k < nchunk; ++k) acc += src[(int64_t)k * PS * 2];
+    int k = 0;
+    for (; k + 8 <= nchunk; k += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[(k + u) * row];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; k < nchunk; ++k) acc += src[k * row];
     out[e] = acc;
 }
 
@@ -634,8 +659,10 @@ __global__ __launch_bounds__(kThreads) void k_super_reduce(const double *__restr
 // centre, plus the lenses of the parent's 5 x 5 block that lie outside the
 // child's own exclusion block (rc children each way: 7 x 7 cells for a cell,
 // 5 x 5 mid cells for a mid cell), summed into P terms about its centre.
-// One wave per child, four children (of one parent) per workgroup; rows of
-// children from c0:  out[(((cy - c0) nCx + cx) P + n) 2 + c].
+// One wave per child, four children (of one parent) per workgroup, the block's
+// lenses in nchunk parts (the first also takes the parent's expansion and the
+// sheet's terms); rows of children from c0:
+//     out[((((cy - c0) nCx + cx) nchunk + part) P + n) 2 + c].
 constexpr int kSuperRows = (2 * kSuperR + 1) * kSuperKMax; // cell rows of a parent block, at most
 
 // Waves a SIMD: three for the 32-term children (168 registers and a few
@@ -645,8 +672,8 @@ __global__ __launch_bounds__(kThreads, P == 32 ? 3 : 2) void k_level2_near(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
     const double *__restrict__ lm, const uint32_t *__restrict__ lcxy,
     const int32_t *__restrict__ cell_start, const double *__restrict__ super, int32_t nSx,
-    int32_t c0, int32_t nxb, int32_t ks, int32_t kc, int32_t rc, int32_t nCx, int32_t fold,
-    double *__restrict__ out)
+    int32_t c0, int32_t nxb, int32_t nchunk, int32_t ks, int32_t kc, int32_t rc, int32_t nCx,
+    int32_t fold, double *__restrict__ out)
 {
     __shared__ double s_x[kThreads], s_y[kThreads], s_m[UNIT ? 1 : kThreads];
     __shared__ uint32_t s_c[kThreads];
@@ -655,52 +682,82 @@ __global__ __launch_bounds__(kThreads, P == 32 ? 3 : 2) void k_level2_near(
     __shared__ int32_t s_pb[kSuperRows], s_off[kSuperRows + 1];
     const int tid = threadIdx.x;
     const int lane = tid % kWave, wave = tid / kWave;
-    const int32_t cy = c0 + (int32_t)(blockIdx.x / (uint32_t)nxb);
-    const int32_t cx0 = (int32_t)(blockIdx.x % (uint32_t)nxb) * kCellsPerBlock;
+    const uint32_t group = blockIdx.x / (uint32_t)nchunk;
+    const int32_t chunk = (int32_t)(blockIdx.x - group * (uint32_t)nchunk);
+    const int32_t cy = c0 + (int32_t)(group / (uint32_t)nxb);
+    const int32_t cx0 = (int32_t)(group % (uint32_t)nxb) * kCellsPerBlock;
     const int32_t cx = cx0 + wave;
     const bool live = cx < nCx;
     // ks / kc is a multiple of kCellsPerBlock: the workgroup's children share a parent
     const int32_t X = cx0 * kc / ks, Y = cy * kc / ks;
+    const double sc = kc * fmax(g.w1, g.h1), isc = 1.0 / sc;
+    double zSr, zSi, sS;
+    super_centre(g, X, Y, ks, zSr, zSi, sS);
     // the parent expansion and the lens ranges of the parent block, row by row
-    for (int n = tid; n < kWave + PS; n += kThreads) {
-        double2 a = {0.0, 0.0};
-        if (n < PS) {
-            double f = 1.0;                                   // n!
-            for (int t = 2; t <= n; ++t) f *= (double)t;
-            const double *src = super + (((int64_t)Y * nSx + X) * PS + n) * 2;
-            a = {src[0] * f, src[1] * f};
+    if (chunk == 0) {
+        for (int n = tid; n < kWave + PS; n += kThreads) {
+            double2 a = {0.0, 0.0};
+            if (n < PS) {
+                const double *src = super + (((int64_t)Y * nSx + X) * PS + n) * 2;
+                a = {src[0] * kN.fact[n], src[1] * kN.fact[n]};
+            }
+            s_A[n] = a;
         }
-        s_A[n] = a;
+        if (tid < kWave) {                                   // ratio^(k+1)/k!
+            const double ratio = sc / sS;
+            double f = 1.0, r2 = ratio;
+#pragma unroll
+            for (int b = 0; b < 7; ++b) {
+                if (((tid + 1) >> b) & 1) f *= r2;
+                r2 *= r2;
+            }
+            s_F[tid] = f / kN.fact[tid];
+        }
     }
     const int32_t ya = max(0, (Y - kSuperR) * ks), yb = min(g.n1y, (Y + kSuperR + 1) * ks);
     const int32_t xa = max(0, (X - kSuperR) * ks), xb = min(g.n1x, (X + kSuperR + 1) * ks);
     const int nrow = yb - ya;
-    if (tid < nrow) {
-        const int32_t row = ya + tid;
-        s_pb[tid] = cell_start[row * g.n1x + xa];
-        s_off[tid + 1] = cell_start[row * g.n1x + xb] - cell_start[row * g.n1x + xa];
+    // s_off[r]: the block's lenses before row r (one wave's scan, rows / 64 a lane)
+    if (tid < kWave) {
+        constexpr int kPer = (kSuperRows + kWave - 1) / kWave;
+        int32_t cnt[kPer], sum = 0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int r = tid * kPer + e;
+            cnt[e] = 0;
+            if (r < nrow) {
+                const int32_t row = ya + r;
+                const int32_t p0 = cell_start[row * g.n1x + xa];
+                s_pb[r] = p0;
+                cnt[e] = cell_start[row * g.n1x + xb] - p0;
+            }
+            sum += cnt[e];
+        }
+        int32_t incl = sum;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int32_t v = __shfl_up(incl, o);
+            if (lane >= o) incl += v;
+        }
+        int32_t off = incl - sum;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int r = tid * kPer + e;
+            if (r <= nrow) s_off[r] = off;
+            off += cnt[e];
+        }
+        if (tid == kWave - 1 && nrow == kPer * kWave) s_off[nrow] = off;
     }
-    __syncthreads();
-    const double sc = kc * fmax(g.w1, g.h1), isc = 1.0 / sc;
     // the child's exclusion block in level-1 cells (a lens in cell column c
     // lies in child column c / kc: outside the block exactly when
     // c < (cx - rc) kc or c >= (cx + rc + 1) kc)
     const int32_t ex0 = (cx - rc) * kc, ex1 = (cx + rc + 1) * kc;
     const int32_t ey0 = (cy - rc) * kc, ey1 = (cy + rc + 1) * kc;
-    double zSr, zSi, sS;
-    super_centre(g, X, Y, ks, zSr, zSi, sS);
-    if (tid == 0) {
-        s_off[0] = 0;
-        for (int r = 0; r < nrow; ++r) s_off[r + 1] += s_off[r];
-        const double ratio = sc / sS;
-        double f = ratio;
-        for (int k = 0; k < kWave; ++k) {
-            s_F[k] = f;
-            f *= ratio / (double)(k + 1);
-        }
-    }
     __syncthreads();
-    const int32_t total = s_off[nrow];
+    // this part's lenses [lo, total), whole stages
+    const int32_t all = s_off[nrow];
+    const int32_t plen = ((all + nchunk - 1) / nchunk + kThreads - 1) / kThreads * kThreads;
+    const int32_t lo = min(all, chunk * plen), total = min(all, lo + plen);
 
     const double zcr = g.a1 + ((double)(kc * cx) + 0.5 * kc) * g.w1;
     const double zci = g.b1 + ((double)(kc * cy) + 0.5 * kc) * g.h1;
@@ -722,14 +779,14 @@ __global__ __launch_bounds__(kThreads, P == 32 ? 3 : 2) void k_level2_near(
     };
     double fx = 0.0, fy = 0.0, fm = 0.0;
     uint32_t fc = 0u;
-    if (tid < total) {
-        const int32_t li = lens_of(tid);
+    if (lo + tid < total) {
+        const int32_t li = lens_of(lo + tid);
         fx = lx[li];
         fy = ly[li];
         if (!UNIT) fm = lm[li];
         fc = lcxy[li];
     }
-    for (int32_t base = 0; base < total; base += kThreads) {
+    for (int32_t base = lo; base < total; base += kThreads) {
         __syncthreads();
         if (base + tid < total) {
             s_x[tid] = fx;
@@ -746,7 +803,7 @@ __global__ __launch_bounds__(kThreads, P == 32 ? 3 : 2) void k_level2_near(
             fc = lcxy[li];
         }
         const int cnt = min(kThreads, total - base);
-#pragma unroll
+#pragma unroll 1      // (unrolled: 713 against 695 us for 1e5 cells)
         for (int k = 0; k < kThreads / kWave; k += 2) {
             if (k * kWave >= cnt) break;                  // the stage's lenses are done
             double tr[2], ti[2], vr[2], vi[2];
@@ -794,8 +851,8 @@ __global__ __launch_bounds__(kThreads, P == 32 ? 3 : 2) void k_level2_near(
     // (with P = 32 both lanes of a term).
     constexpr int R = NV / kWave;
     const int k = R == 1 ? lane >> 1 : lane;
-    double Tr, Ti;
-    {
+    double Tr = 0.0, Ti = 0.0;
+    if (chunk == 0) {
         const double dr = (zcr - zSr) / sS, di = (zci - zSi) / sS;
         double br = 1.0, bi = 0.0;
         double ar0 = 0.0, ai0 = 0.0, ar1 = 0.0, ai1 = 0.0;   // even and odd j
@@ -836,7 +893,7 @@ __global__ __launch_bounds__(kThreads, P == 32 ? 3 : 2) void k_level2_near(
     }
     wave_reduce_scatter(L);
     if (live) {
-        double *dst = out + ((int64_t)(cy - c0) * nCx + cx) * P * 2;
+        double *dst = out + (((int64_t)(cy - c0) * nCx + cx) * nchunk + chunk) * P * 2;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int e = lane * R + r;
@@ -1107,24 +1164,8 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
 // lenses at every point: q = 8 0.70 / 0.52 ms, 9 0.69 / 0.71, 10 0.72 / 0.83,
 // 12 0.77 / 1.09, 20 1.39 / 2.99.
 constexpr int kCellsMinQ = 9;
-constexpr int kPEMax = 80;                // terms, at most
 constexpr int kRingStep = 16;             // ring lenses a wave takes at a time
 static_assert(kPEMax % 16 == 0, "five terms a lane");
-
-struct NTable {
-    double fact[kPEMax], inv[kPEMax + 1];
-    constexpr NTable() : fact(), inv()
-    {
-        double f = 1.0;
-        for (int n = 0; n < kPEMax; ++n) {
-            fact[n] = f;
-            f *= (double)(n + 1);
-        }
-        inv[0] = 0.0;
-        for (int n = 1; n <= kPEMax; ++n) inv[n] = 1.0 / (double)n;
-    }
-};
-__constant__ NTable kN = NTable();        // n!, 1/n
 
 template <bool UNIT, int P>
 __global__ __launch_bounds__(kThreads, 3) void k_level2_cells(
@@ -2142,102 +2183,124 @@ int32_t level2_chunks(const irs_plan_s *p)
 
 void level2_reset(irs_plan_s *p)
 {
-    std::fill(p->super_ok.begin(), p->super_ok.end(), 0);
-    std::fill(p->mid_ok.begin(), p->mid_ok.end(), 0);
+    for (auto &l : p->tree) std::fill(l.ok.begin(), l.ok.end(), 0);
     p->coef_c0 = -1;                 // no band of coefficients resident either
     p->coef_c1 = -2;
 }
 
-// Super-cell side K_S and mid-cell side K_M (cells; K_M = 0: no mid level),
-// once per plan.  Work in series terms, with nu lenses per cell and B(K) =
-// min(N_*, nu (2 R_S + 1)^2 K^2) the lenses of a 5 x 5 block of K x K cells:
-//   super expansions  N_* (cells / K_S^2) PS
-//   mid expansions    (cells / K_M^2) (B(K_S) PS + PS^2)
-//   cell expansions   cells (B(K_M or K_S) P + PS P)
-// over K_S in {4, .., 32} and K_M in {0, 4, 8} with K_S a multiple of
-// kCellsPerBlock K_M (a workgroup's kCellsPerBlock children must share one
-// parent); the accuracy of every series is that of the order rule whatever
-// the sides.
-void choose_sides(irs_plan_s *p)
+namespace {
+
+int32_t tree_nx(const irs_plan_s *p, int l) { const int32_t k = p->tree[l].k; return (p->dg.n1x + k - 1) / k; }
+int32_t tree_ny(const irs_plan_s *p, int l) { const int32_t k = p->tree[l].k; return (p->dg.n1y + k - 1) / k; }
+
+// The sides of the distant-field tree's levels above the cells (cells; each a
+// multiple of kCellsPerBlock times the next, so that a workgroup's children
+// share a parent), once per plan.  Work in series terms, with nu lenses per
+// cell and B(K) the lenses of a 5 x 5 block of K x K cells (clipped to the
+// grid):
+//   top level     N_* (cells / K_0^2) PS
+//   level i       (cells / K_i^2) (B(K_(i-1)) PS + PS^2)
+//   cells         cells (B(K_last) P + PS P)
+// plus kLevelCost a level (its launches); the accuracy of every series is that
+// of the order rule whatever the sides.  1e6 lenses: (64, 16, 4) takes half the
+// terms of the best two levels, (32, 8): all expansions 28.3 -> 16.5 ms.
+//
+// Parts of the lenses of each expansion: enough for kTreeWaves waves in the
+// level's launch over the whole map (a wave an expansion and part), of at
+// least one stage and, on the top level, at most kChunkLens lenses.  They
+// depend on the plan alone, so results do not depend on how a map is cut into
+// calls.  1e5 lenses: the top level of 435 expansions in 65536-lens parts took
+// 0.62 ms on a fifth of the chip's wave slots; three levels in parts take 0.52
+// where two took 0.95.
+constexpr double kLevelCost = 3e7;
+constexpr int64_t kTreeWaves = 4096;
+
+void choose_tree(irs_plan_s *p)
 {
-    if (p->super_k > 0) return;
+    if (p->tree_n > 0) return;
     const DevGeom &g = p->dg;
     const double cells = (double)g.n1x * (double)g.n1y, nl = (double)p->n_lens;
     const double nu = cells > 0.0 ? nl / cells : 0.0;
     const double PS = std::max(1, super_order(p)), P = std::max(1, level2_order(p));
     auto block = [&](int32_t K) {
         const double b = (double)(2 * kSuperR + 1) * K;
-        return std::min(nl, nu * b * b);
+        return nu * std::min(b, (double)g.n1x) * std::min(b, (double)g.n1y);
     };
     auto count = [&](int32_t K) { return std::ceil(g.n1x / (double)K) * std::ceil(g.n1y / (double)K); };
-    int32_t bs = 8, bm = 0;
-    double best = -1.0;
-    for (int32_t KS : {4, 8, 16, 32})
-        for (int32_t KM : {0, 4, 8}) {
-            if (KM != 0 && KS % (kCellsPerBlock * KM) != 0) continue;
-            double cost = nl * count(KS) * PS + cells * PS * P;
-            if (KM == 0) cost += cells * block(KS) * P;
-            else cost += count(KM) * (block(KS) * PS + PS * PS) + cells * block(KM) * P;
-            if (best < 0.0 || cost < best) {
-                best = cost;
-                bs = KS;
-                bm = KM;
+    const int32_t sides[] = {64, 32, 16, 8, 4, 0};
+    int32_t best[kTreeLevels] = {4, 0, 0};
+    double best_cost = -1.0;
+    for (int32_t k0 : sides)
+        for (int32_t k1 : sides)
+            for (int32_t k2 : sides) {
+                const int32_t k[kTreeLevels] = {k0, k1, k2};
+                if (k0 == 0 || (k1 == 0 && k2 != 0)) continue;
+                if (k1 != 0 && k0 % (kCellsPerBlock * k1) != 0) continue;
+                if (k2 != 0 && k1 % (kCellsPerBlock * k2) != 0) continue;
+                double cost = nl * count(k0) * PS + kLevelCost;
+                int32_t last = k0;
+                for (int l = 1; l < kTreeLevels && k[l] != 0; ++l) {
+                    cost += count(k[l]) * (block(last) * PS + PS * PS) + kLevelCost;
+                    last = k[l];
+                }
+                cost += cells * (block(last) * P + PS * P);
+                if (best_cost < 0.0 || cost < best_cost) {
+                    best_cost = cost;
+                    std::copy(k, k + kTreeLevels, best);
+                }
             }
-        }
-    p->super_k = bs;
-    p->mid_k = bm;
-}
-
-int32_t super_side(irs_plan_s *p)
-{
-    choose_sides(p);
-    return p->super_k;
-}
-
-int32_t mid_side(irs_plan_s *p)
-{
-    choose_sides(p);
-    return p->mid_k;
-}
-
-namespace {
-
-int32_t super_nx(irs_plan_s *p) { const int32_t k = super_side(p); return (p->dg.n1x + k - 1) / k; }
-int32_t super_ny(irs_plan_s *p) { const int32_t k = super_side(p); return (p->dg.n1y + k - 1) / k; }
-int32_t lens_chunks(const irs_plan_s *p)
-{
-    return p->n_lens > 0 ? (int32_t)((p->n_lens + kChunkLens - 1) / kChunkLens) : 1;
-}
-
-irs_status ensure_super_buffers(irs_plan_s *p, int64_t rows)
-{
-    const int PS = super_order(p);
-    const int32_t nSx = super_nx(p), nSy = super_ny(p);
-    if (!p->d_super) {
-        irs_status st = alloc_allowed(p, "the super-cell expansions");
-        if (st != IRS_OK) return st;
-        if (dev_alloc(&p->d_super, sizeof(double) * (size_t)nSy * nSx * PS * 2) != hipSuccess) {
-            (void)hipGetLastError();
-            p->d_super = nullptr;
-            set_error("cannot allocate the super-cell expansions");
-            return IRS_E_NOMEM;
-        }
-        p->super_ok.assign((size_t)nSy, 0);
+    for (int l = 0; l < kTreeLevels && best[l] != 0; ++l) {
+        irs::TreeLevel &t = p->tree[l];
+        t.k = best[l];
+        p->tree_n = l + 1;
+        const int64_t lenses = l == 0 ? p->n_lens : (int64_t)block(best[l - 1]);
+        const int64_t stages = std::max<int64_t>(1, (lenses + kThreads - 1) / kThreads);
+        const int64_t exps = (int64_t)tree_nx(p, l) * tree_ny(p, l);
+        int64_t parts = std::min(stages, std::max<int64_t>(1, kTreeWaves / exps));
+        if (l == 0) parts = std::max<int64_t>(parts, (p->n_lens + kChunkLens - 1) / kChunkLens);
+        t.parts = (int32_t)parts;
     }
-    const size_t need = sizeof(double) * (size_t)rows * nSx * lens_chunks(p) * PS * 2;
-    if (p->super_part_bytes < need) {
-        irs_status st = alloc_allowed(p, "the super-cell partial expansions");
-        if (st != IRS_OK) return st;
-        dev_free(p->d_super_part);
-        p->d_super_part = nullptr;
-        p->super_part_bytes = 0;
-        if (dev_alloc(&p->d_super_part, need) != hipSuccess) {
-            (void)hipGetLastError();
-            set_error("cannot allocate the super-cell partial expansions");
-            return IRS_E_NOMEM;
-        }
-        p->super_part_bytes = need;
+}
+
+irs_status ensure_tree_level(irs_plan_s *p, int l)
+{
+    irs::TreeLevel &t = p->tree[l];
+    if (t.d) return IRS_OK;
+    irs_status st = alloc_allowed(p, "the super- or mid-cell expansions");
+    if (st != IRS_OK) return st;
+    const size_t n = (size_t)tree_ny(p, l) * tree_nx(p, l);
+    if (dev_alloc(&t.d, sizeof(double) * n * super_order(p) * 2) != hipSuccess) {
+        (void)hipGetLastError();
+        t.d = nullptr;
+        set_error("cannot allocate the super- or mid-cell expansions");
+        return IRS_E_NOMEM;
     }
+    t.ok.assign((size_t)tree_ny(p, l), 0);
+    return IRS_OK;
+}
+
+// bytes of the partial expansions of `rows` rows of level l (0: not in parts)
+size_t tree_part_need(irs_plan_s *p, int l, int64_t rows)
+{
+    const irs::TreeLevel &t = p->tree[l];
+    if (l > 0 && t.parts == 1) return 0;
+    return sizeof(double) * (size_t)rows * tree_nx(p, l) * t.parts * super_order(p) * 2;
+}
+
+irs_status ensure_tree_part(irs_plan_s *p, size_t need)
+{
+    if (p->tree_part_bytes >= need) return IRS_OK;
+    irs_status st = alloc_allowed(p, "the partial super- or mid-cell expansions");
+    if (st != IRS_OK) return st;
+    dev_free(p->d_tree_part);
+    p->d_tree_part = nullptr;
+    p->tree_part_bytes = 0;
+    if (dev_alloc(&p->d_tree_part, need) != hipSuccess) {
+        (void)hipGetLastError();
+        set_error("cannot allocate the partial super- or mid-cell expansions");
+        return IRS_E_NOMEM;
+    }
+    p->tree_part_bytes = need;
     return IRS_OK;
 }
 
@@ -2291,127 +2354,84 @@ int32_t ring_order(irs_plan_s *p)
     return 0;
 }
 
-// super rows [Ya, Yb] that are not cached, in runs of consecutive rows
-irs_status ensure_super_rows(irs_plan_s *p, int64_t Ya, int64_t Yb, double *flops)
+// Rows [Ya, Yb] of tree level l that are not cached, in runs of consecutive
+// rows: the top level sums the lenses outside its 5 x 5 block; a level below
+// takes its parent's expansion re-expanded about its own centre plus the
+// lenses of the parent block outside its own 5 x 5 block.
+irs_status ensure_tree_rows(irs_plan_s *p, int l, int64_t Ya, int64_t Yb, double *flops)
 {
     const DevGeom &g = p->dg;
+    irs::TreeLevel &t = p->tree[l];
     const int PS = super_order(p);
-    const int32_t ks = super_side(p);
-    const int32_t nSx = super_nx(p);
-    const int32_t nSxb = (nSx + kCellsPerBlock - 1) / kCellsPerBlock;
-    const int32_t nchunk = lens_chunks(p);
-    const int32_t nl = (int32_t)p->n_lens;
-    irs_status st = ensure_super_buffers(p, 1);
+    const int32_t k = t.k, nX = tree_nx(p, l), nXb = (nX + kCellsPerBlock - 1) / kCellsPerBlock;
+    const int32_t kp = l > 0 ? p->tree[l - 1].k : 0;
+    if (l > 0 && kp % (kCellsPerBlock * k) != 0) {
+        set_error("internal: tree cells must tile their parents by workgroups");
+        return IRS_E_INVALID;
+    }
+    irs_status st = ensure_tree_level(p, l);
     if (st != IRS_OK) return st;
+    if (l > 0 && (st = ensure_tree_rows(p, l - 1, Ya * k / kp, Yb * k / kp, flops)) != IRS_OK)
+        return st;
+    const int32_t nl = (int32_t)p->n_lens, parts = t.parts;
+    // whole stages a part (top level)
+    const int32_t plen = ((nl + parts - 1) / parts + kThreads - 1) / kThreads * kThreads;
     for (int64_t y0 = Ya; y0 <= Yb;) {
-        if (p->super_ok[y0]) { ++y0; continue; }
+        if (t.ok[y0]) { ++y0; continue; }
         int64_t y1 = y0;
-        while (y1 + 1 <= Yb && !p->super_ok[y1 + 1]) ++y1;
-        if ((st = ensure_super_buffers(p, y1 - y0 + 1)) != IRS_OK) return st;
-        const unsigned nb = (unsigned)((y1 - y0 + 1) * nSxb * nchunk);
+        while (y1 + 1 <= Yb && !t.ok[y1 + 1]) ++y1;
+        if ((st = ensure_tree_part(p, tree_part_need(p, l, y1 - y0 + 1))) != IRS_OK) return st;
+        const unsigned nb = (unsigned)((y1 - y0 + 1) * nXb * parts);
+        double *dst = t.d + y0 * nX * PS * 2;
+        const bool reduce = l == 0 || parts > 1;
+        double *out = reduce ? p->d_tree_part : dst;
 #define IRS_SE(U, PP)                                                                          \
     hipLaunchKernelGGL((k_super_expand<U, PP>), dim3(nb), dim3(kThreads), 0, p->stream, g,      \
-                       p->d_x, p->d_y, p->d_m, p->d_cxy, nl, (int32_t)y0, nSx, nSxb, nchunk,  \
-                       kChunkLens, ks, p->d_super_part)
-        if (p->unit_mass) {
-            if (PS == 32) IRS_SE(true, 32);
-            else if (PS == 40) IRS_SE(true, 40);
-            else IRS_SE(true, 48);
-        } else {
-            if (PS == 32) IRS_SE(false, 32);
-            else if (PS == 40) IRS_SE(false, 40);
-            else IRS_SE(false, 48);
-        }
+                       p->d_x, p->d_y, p->d_m, p->d_cxy, nl, (int32_t)y0, nX, nXb, parts,      \
+                       plen, k, out)
+#define IRS_MID(U, PP)                                                                          \
+    hipLaunchKernelGGL((k_level2_near<U, PP, PP>), dim3(nb), dim3(kThreads), 0, p->stream, g,    \
+                       p->d_x, p->d_y, p->d_m, p->d_cxy, p->d_cell_start, p->tree[l - 1].d,    \
+                       tree_nx(p, l - 1), (int32_t)y0, nXb, parts, kp, k, kSuperR, nX, 0, out)
+#define IRS_TREE(U)                                                                             \
+    do {                                                                                        \
+        if (l == 0) {                                                                           \
+            if (PS == 32) IRS_SE(U, 32);                                                        \
+            else if (PS == 40) IRS_SE(U, 40);                                                   \
+            else IRS_SE(U, 48);                                                                 \
+        } else {                                                                                \
+            if (PS == 32) IRS_MID(U, 32);                                                       \
+            else if (PS == 40) IRS_MID(U, 40);                                                  \
+            else IRS_MID(U, 48);                                                                \
+        }                                                                                       \
+    } while (0)
+        if (p->unit_mass) IRS_TREE(true);
+        else IRS_TREE(false);
+#undef IRS_TREE
+#undef IRS_MID
 #undef IRS_SE
-        const int64_t n_out = (y1 - y0 + 1) * nSx * PS * 2;
-        hipLaunchKernelGGL(k_super_reduce, dim3((unsigned)((n_out + kThreads - 1) / kThreads)),
-                           dim3(kThreads), 0, p->stream, p->d_super_part, n_out, nchunk, PS,
-                           p->d_super + y0 * nSx * PS * 2);
+        if (reduce) {
+            const int64_t n_out = (y1 - y0 + 1) * nX * PS * 2;
+            hipLaunchKernelGGL(k_super_reduce, dim3((unsigned)((n_out + kWave - 1) / kWave)),
+                               dim3(kWave), 0, p->stream, p->d_tree_part, n_out, parts, PS, dst);
+        }
         IRS_HIP(hipGetLastError());
         if (flops)
             for (int64_t Y = y0; Y <= y1; ++Y)
-                for (int32_t X = 0; X < nSx; ++X) {
-                    const int64_t inside = lenses_in(p, (X - kSuperR) * ks, (X + kSuperR + 1) * ks,
-                                                     (Y - kSuperR) * ks, (Y + kSuperR + 1) * ks);
-                    *flops += (double)(p->n_lens - inside) * (10.0 + 8.0 * PS);
+                for (int64_t X = 0; X < nX; ++X) {
+                    int64_t n = p->n_lens;
+                    if (l > 0) {
+                        const int64_t SX = X * k / kp, SY = Y * k / kp;
+                        n = lenses_in(p, (SX - kSuperR) * kp, (SX + kSuperR + 1) * kp,
+                                      (SY - kSuperR) * kp, (SY + kSuperR + 1) * kp);
+                        *flops += 8.0 * PS * PS;
+                    }
+                    n -= lenses_in(p, (X - kSuperR) * k, (X + kSuperR + 1) * k, (Y - kSuperR) * k,
+                                   (Y + kSuperR + 1) * k);
+                    *flops += (double)n * (10.0 + 8.0 * PS);
                 }
-        for (int64_t Y = y0; Y <= y1; ++Y) p->super_ok[Y] = 1;
+        for (int64_t Y = y0; Y <= y1; ++Y) t.ok[Y] = 1;
         y0 = y1 + 1;
-    }
-    return IRS_OK;
-}
-
-int32_t mid_nx(irs_plan_s *p) { const int32_t k = mid_side(p); return (p->dg.n1x + k - 1) / k; }
-int32_t mid_ny(irs_plan_s *p) { const int32_t k = mid_side(p); return (p->dg.n1y + k - 1) / k; }
-
-irs_status ensure_mid_buffers(irs_plan_s *p)
-{
-    if (p->d_mid) return IRS_OK;
-    irs_status st = alloc_allowed(p, "the mid-cell expansions");
-    if (st != IRS_OK) return st;
-    const int PS = super_order(p);
-    const int32_t nMx = mid_nx(p), nMy = mid_ny(p);
-    if (dev_alloc(&p->d_mid, sizeof(double) * (size_t)nMy * nMx * PS * 2) != hipSuccess) {
-        (void)hipGetLastError();
-        p->d_mid = nullptr;
-        set_error("cannot allocate the mid-cell expansions");
-        return IRS_E_NOMEM;
-    }
-    p->mid_ok.assign((size_t)nMy, 0);
-    return IRS_OK;
-}
-
-// mid rows [Ma, Mb] that are not cached, in runs of consecutive rows: each mid
-// cell takes its super cell's expansion re-expanded about its centre plus the
-// lenses of the super block outside its own 5 x 5 block of mid cells
-irs_status ensure_mid_rows(irs_plan_s *p, int64_t Ma, int64_t Mb, double *flops)
-{
-    const DevGeom &g = p->dg;
-    const int PS = super_order(p);
-    const int32_t ks = super_side(p), km = mid_side(p);
-    if (km <= 0 || ks % (kCellsPerBlock * km) != 0) {
-        set_error("internal: mid cells must tile their super cells by workgroups");
-        return IRS_E_INVALID;
-    }
-    irs_status st = ensure_mid_buffers(p);
-    if (st != IRS_OK) return st;
-    if ((st = ensure_super_rows(p, Ma * km / ks, Mb * km / ks, flops)) != IRS_OK) return st;
-    const int32_t nSx = super_nx(p), nMx = mid_nx(p);
-    const int32_t nxb = (nMx + kCellsPerBlock - 1) / kCellsPerBlock;
-    for (int64_t m0 = Ma; m0 <= Mb;) {
-        if (p->mid_ok[m0]) { ++m0; continue; }
-        int64_t m1 = m0;
-        while (m1 + 1 <= Mb && !p->mid_ok[m1 + 1]) ++m1;
-        const unsigned nb = (unsigned)((m1 - m0 + 1) * nxb);
-        double *dst = p->d_mid + m0 * nMx * PS * 2;
-#define IRS_MID(U, PP)                                                                          \
-    hipLaunchKernelGGL((k_level2_near<U, PP, PP>), dim3(nb), dim3(kThreads), 0, p->stream, g,    \
-                       p->d_x, p->d_y, p->d_m, p->d_cxy, p->d_cell_start, p->d_super, nSx,     \
-                       (int32_t)m0, nxb, ks, km, kSuperR, nMx, 0, dst)
-        if (p->unit_mass) {
-            if (PS == 32) IRS_MID(true, 32);
-            else if (PS == 40) IRS_MID(true, 40);
-            else IRS_MID(true, 48);
-        } else {
-            if (PS == 32) IRS_MID(false, 32);
-            else if (PS == 40) IRS_MID(false, 40);
-            else IRS_MID(false, 48);
-        }
-#undef IRS_MID
-        IRS_HIP(hipGetLastError());
-        if (flops)
-            for (int64_t M = m0; M <= m1; ++M)
-                for (int32_t X = 0; X < nMx; ++X) {
-                    const int64_t SX = (int64_t)X * km / ks, SY = M * km / ks;
-                    const int64_t ring =
-                        lenses_in(p, (SX - kSuperR) * ks, (SX + kSuperR + 1) * ks,
-                                  (SY - kSuperR) * ks, (SY + kSuperR + 1) * ks) -
-                        lenses_in(p, ((int64_t)X - kSuperR) * km, ((int64_t)X + kSuperR + 1) * km,
-                                  (M - kSuperR) * km, (M + kSuperR + 1) * km);
-                    *flops += (double)ring * (10.0 + 8.0 * PS) + 8.0 * PS * PS;
-                }
-        for (int64_t M = m0; M <= m1; ++M) p->mid_ok[M] = 1;
-        m0 = m1 + 1;
     }
     return IRS_OK;
 }
@@ -2422,9 +2442,13 @@ irs_status level2_prepare(irs_plan_s *p)
 {
     level2_reset(p);
     if (super_order(p) <= 0) return IRS_OK;
-    irs_status st = ensure_super_buffers(p, super_ny(p));
-    if (st != IRS_OK || mid_side(p) == 0) return st;
-    return ensure_mid_buffers(p);
+    choose_tree(p);
+    irs_status st = IRS_OK;
+    for (int l = 0; l < p->tree_n && st == IRS_OK; ++l) {
+        st = ensure_tree_level(p, l);
+        if (st == IRS_OK) st = ensure_tree_part(p, tree_part_need(p, l, tree_ny(p, l)));
+    }
+    return st;
 }
 
 irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, double *flops,
@@ -2465,19 +2489,19 @@ irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, double *f
                                                               cy + kRing + 1)) * (10.0 + 8.0 * P);
         return IRS_OK;
     }
-    // the cells' parent level: mid cells if the plan has them, else super cells
-    const int32_t km = mid_side(p);
-    const int32_t ks = km > 0 ? km : super_side(p);
-    if (km > 0) st = ensure_mid_rows(p, c0 / km, c1 / km, flops);
-    else st = ensure_super_rows(p, c0 / ks, c1 / ks, flops);
+    // the cells' parent level: the tree's last
+    choose_tree(p);
+    const int last = p->tree_n - 1;
+    const int32_t ks = p->tree[last].k;
+    st = ensure_tree_rows(p, last, c0 / ks, c1 / ks, flops);
     if (st != IRS_OK) return st;
-    const double *parent = km > 0 ? p->d_mid : p->d_super;
-    const int32_t nSx = km > 0 ? mid_nx(p) : super_nx(p);
+    const double *parent = p->tree[last].d;
+    const int32_t nSx = tree_nx(p, last);
     const unsigned nb = (unsigned)((c1 - c0 + 1) * nxb);
 #define IRS_LN(U, PP, QS)                                                                         \
     hipLaunchKernelGGL((k_level2_near<U, PP, QS>), dim3(nb), dim3(kThreads), 0, p->stream, g,      \
                        p->d_x, p->d_y, p->d_m, p->d_cxy, p->d_cell_start, parent, nSx,          \
-                       (int32_t)c0, nxb, ks, 1, kRing, g.n1x, fold_sheet ? 1 : 0, p->d_part)
+                       (int32_t)c0, nxb, 1, ks, 1, kRing, g.n1x, fold_sheet ? 1 : 0, p->d_part)
     if (p->unit_mass) {
         if (P == 32) {
             if (PS == 32) IRS_LN(true, 32, 32);
@@ -2614,10 +2638,10 @@ irs_status interp_tables_ready(irs_plan_s *p)
     const char *missing = nullptr;
     if (!p->d_rows) missing = "the level-3 row table";
     else if (super_order(p) > 0) {
-        const size_t whole = sizeof(double) * (size_t)super_ny(p) * super_nx(p) * lens_chunks(p) *
-                             super_order(p) * 2;
-        if (!p->d_super || p->super_part_bytes < whole) missing = "the super-cell expansions";
-        else if (mid_side(p) > 0 && !p->d_mid) missing = "the mid-cell expansions";
+        choose_tree(p);
+        for (int l = 0; l < p->tree_n; ++l)
+            if (!p->tree[l].d || p->tree_part_bytes < tree_part_need(p, l, tree_ny(p, l)))
+                missing = "the super- and mid-cell expansions";
     }
     if (missing) {
         set_error(std::string(missing) + " of this plan are not allocated yet (shoot one whole "
@@ -2766,14 +2790,15 @@ irs_status level2_tree_rows(irs_plan_s *p, int64_t cyA, int64_t cyB, CallStats *
 {
     if (level2_order(p) <= 0 || super_order(p) <= 0) return IRS_OK;
     hipStream_t s = p->stream;
-    const int32_t ks = super_side(p), km = mid_side(p);
+    choose_tree(p);
+    const int last = p->tree_n - 1;
+    const int32_t ks = p->tree[last].k;
     if (cs) {
         irs_status st = cs->begin(s, 0);
         if (st != IRS_OK) return st;
     }
     double fl = 0.0;
-    irs_status st = km > 0 ? ensure_mid_rows(p, cyA / km, cyB / km, cs ? &fl : nullptr)
-                           : ensure_super_rows(p, cyA / ks, cyB / ks, cs ? &fl : nullptr);
+    irs_status st = ensure_tree_rows(p, last, cyA / ks, cyB / ks, cs ? &fl : nullptr);
     if (st != IRS_OK) return st;
     if (cs) {
         cs->level2_expand_flops += fl;

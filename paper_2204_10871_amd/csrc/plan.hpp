@@ -19,6 +19,15 @@ struct TileSpan {
     int32_t a, b;
 };
 
+// One level of the distant-field tree (irs_map_stats' super and mid cells).
+constexpr int kTreeLevels = 3;
+struct TreeLevel {
+    int32_t k = 0;                       // side in level-1 cells
+    int32_t parts = 1;                   // parts of an expansion's lenses
+    double *d = nullptr;                 // expansions of all rows
+    std::vector<char> ok;                // ok[Y]: row Y is computed
+};
+
 struct DirectArgs {
     DevGeom g;
     const double *lx, *ly, *lm;          // sorted lenses (lm null: unit masses)
@@ -63,10 +72,13 @@ struct irs_plan_s {
 
     // Level-2 coefficients of one band of level-1 rows: 10 doubles per point
     // (Re/Im of C0..C4), point (gx, gy) at ((gy - band_row0*q) * n1x*q + gx).
-    int32_t super_k = 0;                  // super-cell side (cells), chosen once per plan
-    int32_t mid_k = 0;                    // mid-cell side (cells), 0: no mid level
-    double *d_mid = nullptr;              // mid-cell expansions (all rows), like d_super
-    std::vector<char> mid_ok;
+    // Distant-field tree above the cells, top level first; chosen once per
+    // plan.  The expansions are kept while the plan lives (its lenses never
+    // change) or until level2_reset.
+    int32_t tree_n = 0;                   // levels
+    irs::TreeLevel tree[irs::kTreeLevels];
+    double *d_tree_part = nullptr;        // partial expansions of a level's launch
+    size_t tree_part_bytes = 0;
     void *d_rows = nullptr;               // level-3 row table (ny entries of 32 B)
     void *d_cols = nullptr;               // level-3 column table (nx entries of 48 B)
     // level-3 tiles: column tiles of <= 64 ray columns, row tiles of <= 32 ray
@@ -79,13 +91,6 @@ struct irs_plan_s {
     double *d_part = nullptr;             // per-cell expansions (or per-chunk partials)
     size_t part_bytes = 0;
     int ring_fit = -1;                    // level-2 points may stage ring lenses (-1: unknown)
-    // Two-level distant field: expansions of the super cells, kept while the
-    // plan lives (its lenses never change); super_ok[Y]: row Y is computed.
-    double *d_super = nullptr;
-    std::vector<char> super_ok;
-    double *d_super_part = nullptr;       // per-(super cell, lens chunk) partials
-    size_t super_part_bytes = 0;
-
     // Learned interpolant (IRS_LEARNED): network, validation decision and the
     // corner table of one band of level-1 rows (4 doubles per corner:
     // Re A, Im A, Re A', Im A'; (qc + 1)^2 corners per cell).
