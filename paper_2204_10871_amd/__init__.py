@@ -223,7 +223,7 @@ class Plan:
     def shoot_map(self, time_phases=False):
         """Full map on the host: (counts uint32 [npix, npix], stats dict)."""
         npix = self.params.npix_side
-        counts = np.zeros(npix * npix, np.uint32)
+        counts = np.empty(npix * npix, np.uint32)
         st = MapStats()
         fl = IRS_TIME_PHASES if time_phases else 0
         _check(self._lib.irs_shoot_map(self._h, _vp(counts), C.byref(st), fl), "irs_shoot_map")

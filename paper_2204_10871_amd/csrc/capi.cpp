@@ -156,24 +156,16 @@ DevGeom make_dev_geom(const HostGeometry &hg)
 void release(irs_plan_s *p)
 {
     if (!p) return;
-    dev_free(p->d_x);
-    dev_free(p->d_y);
-    dev_free(p->d_m);
-    dev_free(p->d_cell_start);
-    dev_free(p->d_cxy);
+    dev_free(p->d_cells);
+    dev_free(p->d_lenses);
     dev_free(p->d_order);
-    dev_free(p->d_xy);
-    dev_free(p->d_rows);
-    dev_free(p->d_cols);
-    dev_free(p->d_tcol);
-    dev_free(p->d_trow);
+    dev_free(p->d_tables);
     dev_free(p->d_coef);
     dev_free(p->d_part);
-    for (auto &l : p->tree) dev_free(l.d);
+    dev_free(p->d_tree);
     dev_free(p->d_tree_part);
     dev_free(p->d_counts);
     dev_free(p->d_tmp);
-    dev_free(p->d_landed);
     learn_release(p);
     delete p;
 }
@@ -277,12 +269,15 @@ struct Timer {
         }
         if (a) (void)hipEventRecord(a, s);
     }
-    double stop()
+    void stop()
     {
-        float ms = 0.0f;
-        if (a && hipEventRecord(b, s) == hipSuccess && hipEventSynchronize(b) == hipSuccess)
-            (void)hipEventElapsedTime(&ms, a, b);
-        return ms;
+        if (a) (void)hipEventRecord(b, s);
+    }
+    double ms() const                    // once the stream has passed stop()
+    {
+        float t = 0.0f;
+        if (a) (void)hipEventElapsedTime(&t, a, b);
+        return t;
     }
     ~Timer()
     {
@@ -384,31 +379,38 @@ irs_status irs_plan(const irs_params *params, int64_t n_lens, const double *x, c
         set_error("irs_plan: " + err);
         return st;
     }
-    double msum = 0.0;
     // extents for irs_plan_s::tame: with squared distances of 1e-70 .. 1e41
     // products of four of them, quotients of a mass by one and their
-    // remainders are normal numbers
-    bool tame = std::max(hg.info.ix, hg.info.iy) < 1e20;
-    for (int64_t i = 0; i < n_lens; ++i) {
-        if (!std::isfinite(x[i]) || !std::isfinite(y[i]) || (m && !(std::isfinite(m[i]) && m[i] >= 0.0))) {
-            set_error("irs_plan: lens positions must be finite and masses finite and >= 0");
-            return IRS_E_INVALID;
-        }
-        msum += m ? m[i] : 1.0;
-        tame = tame && std::fabs(x[i]) < 1e20 && std::fabs(y[i]) < 1e20 &&
-               (!m || m[i] == 0.0 || (m[i] > 1e-100 && m[i] < 1e20));
-    }
+    // remainders are normal numbers (all of it is checked without branches,
+    // and lens by lens only if something lies outside)
+    int wild = !(std::max(hg.info.ix, hg.info.iy) < 1e20);
+    for (int64_t i = 0; i < n_lens; ++i)
+        wild |= !(std::fabs(x[i]) < 1e20) | !(std::fabs(y[i]) < 1e20);
+    if (m)
+        for (int64_t i = 0; i < n_lens; ++i)
+            wild |= !(m[i] == 0.0) & (!(m[i] > 1e-100) | !(m[i] < 1e20));
+    if (wild)
+        for (int64_t i = 0; i < n_lens; ++i)
+            if (!std::isfinite(x[i]) || !std::isfinite(y[i]) ||
+                (m && !(std::isfinite(m[i]) && m[i] >= 0.0))) {
+                set_error("irs_plan: lens positions must be finite and masses finite and >= 0");
+                return IRS_E_INVALID;
+            }
+    double msum = m ? 0.0 : (double)n_lens;
+    if (m)
+        for (int64_t i = 0; i < n_lens; ++i) msum += m[i];
     if (params->method != IRS_DIRECT && n_lens > 0) {
         // the distant-field series hold for lenses inside their level-1 cells
         const irs_geometry_info &gi = hg.info;
         const double tol = 1e-6 * std::min(gi.ix / gi.n1x, gi.iy / gi.n1y);
-        for (int64_t i = 0; i < n_lens; ++i) {
-            if (x[i] < gi.a1 - tol || x[i] > gi.a2 + tol || y[i] < gi.b1 - tol ||
-                y[i] > gi.b2 + tol) {
-                set_error("irs_plan: the interpolated methods need every lens inside the lens "
-                          "rectangle [a1, a2] x [b1, b2]");
-                return IRS_E_INVALID;
-            }
+        const double xa = gi.a1 - tol, xb = gi.a2 + tol, ya = gi.b1 - tol, yb = gi.b2 + tol;
+        int out = 0;
+        for (int64_t i = 0; i < n_lens; ++i)
+            out |= (x[i] < xa) | (x[i] > xb) | (y[i] < ya) | (y[i] > yb);
+        if (out) {
+            set_error("irs_plan: the interpolated methods need every lens inside the lens "
+                      "rectangle [a1, a2] x [b1, b2]");
+            return IRS_E_INVALID;
         }
     }
     irs_plan_s *p = new (std::nothrow) irs_plan_s();
@@ -422,17 +424,11 @@ irs_status irs_plan(const irs_params *params, int64_t n_lens, const double *x, c
     p->stream = (hipStream_t)hip_stream;
     p->n_lens = n_lens;
     p->unit_mass = (m == nullptr);
-    p->tame = tame;
+    p->tame = !wild;
     p->kappa_star_eff = M_PI * msum / (hg.info.ix * hg.info.iy);
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) {
         st = hip_fail(e, "hipGetDevice");
-        release(p);
-        return st;
-    }
-    e = dev_alloc(&p->d_landed, sizeof(unsigned long long) * kLandedSlots);
-    if (e != hipSuccess) {
-        st = hip_fail(e, "hipMalloc");
         release(p);
         return st;
     }
@@ -497,9 +493,8 @@ irs_status irs_deflect_grid(irs_plan_t plan, int64_t first_ray, int64_t n, doubl
     }
     if (n == 0) return IRS_OK;
     const bool on_dev = (flags & IRS_OUT_ON_DEVICE) != 0;
-    CallStats cs;
     RaySel sel{};
-    sel.stats = &cs;
+    sel.stats = nullptr;                  // no statistics are reported
     sel.row0 = first_ray / g.nx;
     sel.row1 = (first_ray + n - 1) / g.nx + 1;
     sel.ray_first = first_ray;
@@ -552,34 +547,38 @@ static irs_status shoot(irs_plan_t plan, int64_t row0, int64_t nrows, uint32_t *
         if (!plan->d_counts) IRS_HIP(dev_alloc(&plan->d_counts, map_bytes));
         dst = plan->d_counts;
     }
-    if (!on_dev || overwrite) IRS_HIP(hipMemsetAsync(dst, 0, map_bytes, s));
-    IRS_HIP(hipMemsetAsync(plan->d_landed, 0, sizeof(unsigned long long) * kLandedSlots, s));
+    const bool clear = !on_dev || overwrite;
+    irs_status st = launch_zero(s, dst, clear ? map_bytes / sizeof(uint32_t) : 0, plan->d_landed,
+                                (size_t)kLandedSlots * 2);
+    if (st != IRS_OK) return st;
     CallStats cs;
     cs.timed = (flags & IRS_TIME_PHASES) != 0;
     RaySel sel{};
-    sel.stats = &cs;
+    sel.stats = stats || cs.timed ? &cs : nullptr;
     sel.row0 = row0;
     sel.row1 = row0 + nrows;
     sel.ray_first = 0;
     sel.ray_last = g.nx * g.ny;
     sel.counts = dst;
     sel.landed = plan->d_landed;
-    irs_status st = run(plan, sel);
+    st = run(plan, sel);
     if (st != IRS_OK) return st;
+    timer.stop();
+    if (stats) interp_account(plan, cs);  // while the GPU works
     unsigned long long slots[kLandedSlots];
     IRS_HIP(hipMemcpyAsync(slots, plan->d_landed, sizeof slots, hipMemcpyDeviceToHost, s));
-    if (!on_dev) {
+    if (!on_dev && overwrite) {
+        IRS_HIP(hipMemcpyAsync(counts, dst, map_bytes, hipMemcpyDeviceToHost, s));
+    } else if (!on_dev) {
         std::vector<uint32_t> tmp((size_t)plan->geo.npix * (size_t)plan->geo.npix);
         IRS_HIP(hipMemcpyAsync(tmp.data(), dst, map_bytes, hipMemcpyDeviceToHost, s));
         IRS_HIP(hipStreamSynchronize(s));
-        if (overwrite) std::memcpy(counts, tmp.data(), map_bytes);
-        else
-            for (size_t k = 0; k < tmp.size(); ++k) counts[k] += tmp[k];
+        for (size_t k = 0; k < tmp.size(); ++k) counts[k] += tmp[k];
     }
     IRS_HIP(hipStreamSynchronize(s));
     unsigned long long landed = 0;
     for (unsigned long long v : slots) landed += v;
-    const double ms = timer.stop();
+    const double ms = timer.ms();
     st = cs.collect();
     if (st != IRS_OK) return st;
     if (stats) {

@@ -724,19 +724,26 @@ irs_status launch_direct_queue(hipStream_t s, int precision, bool unit, int v,
 }
 
 namespace {
-__global__ void k_zero(uint32_t *__restrict__ p, size_t n)
+__global__ void k_zero(uint32_t *__restrict__ p, size_t n, uint32_t *__restrict__ p2, size_t m)
 {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = i0; i < m; i += step) p2[i] = 0u;
+    // 16 bytes a store where p allows it
+    const size_t head = min(n, (size_t)(-(intptr_t)p & 15) / 4), quads = (n - head) / 4;
+    uint4 *q = (uint4 *)(p + head);
+    for (size_t i = i0; i < quads; i += step) q[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 < head) p[i0] = 0u;
+    if (i0 < n - head - 4 * quads) p[head + 4 * quads + i0] = 0u;
 }
 }  // namespace
 
-irs_status launch_zero(hipStream_t s, void *ptr, size_t n_words)
+irs_status launch_zero(hipStream_t s, void *ptr, size_t n_words, void *ptr2, size_t m_words)
 {
-    if (n_words == 0) return IRS_OK;
-    const size_t blocks = std::min<size_t>((n_words + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t *)ptr, n_words);
+    if (n_words + m_words == 0) return IRS_OK;
+    const size_t blocks = std::min<size_t>((std::max(n_words / 4, m_words) + 255) / 256 + 1, 4096);
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t *)ptr, n_words,
+                       (uint32_t *)ptr2, m_words);
     IRS_HIP(hipGetLastError());
     return IRS_OK;
 }

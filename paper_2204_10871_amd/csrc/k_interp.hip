@@ -1997,12 +1997,12 @@ __device__ __forceinline__ void level3_corner_ray(const L3Map &m, int64_t i0, in
     }
 }
 
-// One corner cell's rays of a map, one per lane.
+// The corner cells' rays of a map, one per lane (blockIdx.y: the corner).
 template <bool UNIT, bool BIN>
-__global__ __launch_bounds__(kThreads) void k_level3_corner(L3Map m, int64_t i0, int64_t i1,
-                                                            int64_t j0, int64_t j1)
+__global__ __launch_bounds__(kThreads) void k_level3_corner(L3Map m)
 {
-    level3_corner_ray<UNIT, BIN>(m, i0, i1, j0, j1,
+    const int c = (int)blockIdx.y;
+    level3_corner_ray<UNIT, BIN>(m, m.corner[c][0], m.corner[c][1], m.corner[c][2], m.corner[c][3],
                                  (int64_t)blockIdx.x * kThreads + threadIdx.x);
 }
 
@@ -2262,20 +2262,21 @@ void choose_tree(irs_plan_s *p)
     }
 }
 
-irs_status ensure_tree_level(irs_plan_s *p, int l)
+irs_status ensure_tree(irs_plan_s *p)
 {
-    irs::TreeLevel &t = p->tree[l];
-    if (t.d) return IRS_OK;
-    irs_status st = alloc_allowed(p, "the super- or mid-cell expansions");
+    if (p->d_tree) return IRS_OK;
+    irs_status st = alloc_allowed(p, "the super- and mid-cell expansions");
     if (st != IRS_OK) return st;
-    const size_t n = (size_t)tree_ny(p, l) * tree_nx(p, l);
-    if (dev_alloc(&t.d, sizeof(double) * n * super_order(p) * 2) != hipSuccess) {
+    DevArena a;
+    for (int l = 0; l < p->tree_n; ++l)
+        a.add(p->tree[l].d, (size_t)tree_ny(p, l) * tree_nx(p, l) * super_order(p) * 2);
+    if (a.alloc((void **)&p->d_tree) != hipSuccess) {
         (void)hipGetLastError();
-        t.d = nullptr;
-        set_error("cannot allocate the super- or mid-cell expansions");
+        p->d_tree = nullptr;
+        set_error("cannot allocate the super- and mid-cell expansions");
         return IRS_E_NOMEM;
     }
-    t.ok.assign((size_t)tree_ny(p, l), 0);
+    for (int l = 0; l < p->tree_n; ++l) p->tree[l].ok.assign((size_t)tree_ny(p, l), 0);
     return IRS_OK;
 }
 
@@ -2304,6 +2305,26 @@ irs_status ensure_tree_part(irs_plan_s *p, size_t need)
     return IRS_OK;
 }
 
+// The table of lenses_in: its entries at (x, y) count the lenses of cells
+// [0, x) x [0, y); once per plan (false: no memory for it).
+bool build_sat(irs_plan_s *p)
+{
+    if (!p->h_sat.empty()) return true;
+    const int64_t nx = p->dg.n1x, ny = p->dg.n1y;
+    try {
+        p->h_sat.assign((size_t)((nx + 1) * (ny + 1)), 0);
+    } catch (const std::exception &) {
+        return false;
+    }
+    const int32_t *hc = p->h_cell_start.data();
+    for (int64_t y = 0; y < ny; ++y) {
+        const int32_t *above = p->h_sat.data() + y * (nx + 1), *row = hc + y * nx;
+        int32_t *out = p->h_sat.data() + (y + 1) * (nx + 1);
+        for (int64_t x = 0; x <= nx; ++x) out[x] = above[x] + (row[x] - row[0]);
+    }
+    return true;
+}
+
 // lenses of the cell block [xa, xb) x [ya, yb) (clipped), from the host copy
 int64_t lenses_in(const irs_plan_s *p, int64_t xa, int64_t xb, int64_t ya, int64_t yb)
 {
@@ -2313,6 +2334,11 @@ int64_t lenses_in(const irs_plan_s *p, int64_t xa, int64_t xb, int64_t ya, int64
     ya = std::max<int64_t>(0, ya);
     yb = std::min<int64_t>(g.n1y, yb);
     if (xa >= xb || ya >= yb) return 0;
+    if (!p->h_sat.empty()) {
+        const int32_t *t = p->h_sat.data();
+        const int64_t w = g.n1x + 1;
+        return (int64_t)(t[yb * w + xb] - t[yb * w + xa]) - (t[ya * w + xb] - t[ya * w + xa]);
+    }
     const std::vector<int32_t> &hc = p->h_cell_start;
     int64_t n = 0;
     for (int64_t row = ya; row < yb; ++row) n += hc[row * g.n1x + xb] - hc[row * g.n1x + xa];
@@ -2326,6 +2352,7 @@ bool ring_fits(irs_plan_s *p)
 {
     if (p->ring_fit < 0) {
         const DevGeom &g = p->dg;
+        build_sat(p);
         bool ok = true;
         for (int64_t cy = 0; cy < g.n1y && ok; ++cy)
             for (int64_t cx0 = 0; cx0 < g.n1x && ok; cx0 += kCellsPerBlock)
@@ -2358,7 +2385,7 @@ int32_t ring_order(irs_plan_s *p)
 // rows: the top level sums the lenses outside its 5 x 5 block; a level below
 // takes its parent's expansion re-expanded about its own centre plus the
 // lenses of the parent block outside its own 5 x 5 block.
-irs_status ensure_tree_rows(irs_plan_s *p, int l, int64_t Ya, int64_t Yb, double *flops)
+irs_status ensure_tree_rows(irs_plan_s *p, int l, int64_t Ya, int64_t Yb, CallStats *cs)
 {
     const DevGeom &g = p->dg;
     irs::TreeLevel &t = p->tree[l];
@@ -2369,9 +2396,9 @@ irs_status ensure_tree_rows(irs_plan_s *p, int l, int64_t Ya, int64_t Yb, double
         set_error("internal: tree cells must tile their parents by workgroups");
         return IRS_E_INVALID;
     }
-    irs_status st = ensure_tree_level(p, l);
+    irs_status st = ensure_tree(p);
     if (st != IRS_OK) return st;
-    if (l > 0 && (st = ensure_tree_rows(p, l - 1, Ya * k / kp, Yb * k / kp, flops)) != IRS_OK)
+    if (l > 0 && (st = ensure_tree_rows(p, l - 1, Ya * k / kp, Yb * k / kp, cs)) != IRS_OK)
         return st;
     const int32_t nl = (int32_t)p->n_lens, parts = t.parts;
     // whole stages a part (top level)
@@ -2416,20 +2443,7 @@ irs_status ensure_tree_rows(irs_plan_s *p, int l, int64_t Ya, int64_t Yb, double
                                dim3(kWave), 0, p->stream, p->d_tree_part, n_out, parts, PS, dst);
         }
         IRS_HIP(hipGetLastError());
-        if (flops)
-            for (int64_t Y = y0; Y <= y1; ++Y)
-                for (int64_t X = 0; X < nX; ++X) {
-                    int64_t n = p->n_lens;
-                    if (l > 0) {
-                        const int64_t SX = X * k / kp, SY = Y * k / kp;
-                        n = lenses_in(p, (SX - kSuperR) * kp, (SX + kSuperR + 1) * kp,
-                                      (SY - kSuperR) * kp, (SY + kSuperR + 1) * kp);
-                        *flops += 8.0 * PS * PS;
-                    }
-                    n -= lenses_in(p, (X - kSuperR) * k, (X + kSuperR + 1) * k, (Y - kSuperR) * k,
-                                   (Y + kSuperR + 1) * k);
-                    *flops += (double)n * (10.0 + 8.0 * PS);
-                }
+        if (cs) cs->work.push_back({CallStats::kTreeRows, l, y0, y1});
         for (int64_t Y = y0; Y <= y1; ++Y) t.ok[Y] = 1;
         y0 = y1 + 1;
     }
@@ -2443,15 +2457,13 @@ irs_status level2_prepare(irs_plan_s *p)
     level2_reset(p);
     if (super_order(p) <= 0) return IRS_OK;
     choose_tree(p);
-    irs_status st = IRS_OK;
-    for (int l = 0; l < p->tree_n && st == IRS_OK; ++l) {
-        st = ensure_tree_level(p, l);
-        if (st == IRS_OK) st = ensure_tree_part(p, tree_part_need(p, l, tree_ny(p, l)));
-    }
+    irs_status st = ensure_tree(p);
+    for (int l = 0; l < p->tree_n && st == IRS_OK; ++l)
+        st = ensure_tree_part(p, tree_part_need(p, l, tree_ny(p, l)));
     return st;
 }
 
-irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, double *flops,
+irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, CallStats *cs,
                                 bool fold_sheet)
 {
     const int P = level2_order(p);
@@ -2482,18 +2494,14 @@ irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, double *f
         }
 #undef IRS_L2E
         IRS_HIP(hipGetLastError());
-        if (flops)
-            for (int64_t cy = c0; cy <= c1; ++cy)
-                for (int64_t cx = 0; cx < g.n1x; ++cx)
-                    *flops += (double)(p->n_lens - lenses_in(p, cx - kRing, cx + kRing + 1, cy - kRing,
-                                                              cy + kRing + 1)) * (10.0 + 8.0 * P);
+        if (cs) cs->work.push_back({CallStats::kCellExpansions, 0, c0, c1});
         return IRS_OK;
     }
     // the cells' parent level: the tree's last
     choose_tree(p);
     const int last = p->tree_n - 1;
     const int32_t ks = p->tree[last].k;
-    st = ensure_tree_rows(p, last, c0 / ks, c1 / ks, flops);
+    st = ensure_tree_rows(p, last, c0 / ks, c1 / ks, cs);
     if (st != IRS_OK) return st;
     const double *parent = p->tree[last].d;
     const int32_t nSx = tree_nx(p, last);
@@ -2525,17 +2533,7 @@ irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, double *f
     }
 #undef IRS_LN
     IRS_HIP(hipGetLastError());
-    if (flops)
-        for (int64_t cy = c0; cy <= c1; ++cy) {
-            const int64_t Y = cy / ks;
-            for (int64_t cx = 0; cx < g.n1x; ++cx) {
-                const int64_t X = cx / ks;
-                const int64_t ring = lenses_in(p, (X - kSuperR) * ks, (X + kSuperR + 1) * ks,
-                                               (Y - kSuperR) * ks, (Y + kSuperR + 1) * ks) -
-                                     lenses_in(p, cx - kRing, cx + kRing + 1, cy - kRing, cy + kRing + 1);
-                *flops += (double)ring * (10.0 + 8.0 * P) + 8.0 * PS * P;
-            }
-        }
+    if (cs) cs->work.push_back({CallStats::kCellExpansions, 0, c0, c1});
     return IRS_OK;
 }
 
@@ -2597,31 +2595,31 @@ irs_status ensure_rows(irs_plan_s *p)
     // cell holds a whole tile of rows
     p->h_tcol = make_tiles(p->geo.info, 0, kWave, kWave + kWave / 2, true);
     p->h_trow = make_tiles(p->geo.info, 1, kL3Rows, kL3Rows, false);
-    dev_free(p->d_tcol);
-    dev_free(p->d_trow);
-    dev_free(p->d_cols);
-    p->d_tcol = p->d_trow = nullptr;
-    p->d_cols = nullptr;
-    IRS_HIP(dev_alloc(&p->d_tcol, p->h_tcol.size() * sizeof(TileSpan)));
-    IRS_HIP(dev_alloc(&p->d_trow, p->h_trow.size() * sizeof(TileSpan)));
-    IRS_HIP(hipMemcpyAsync(p->d_tcol, p->h_tcol.data(), p->h_tcol.size() * sizeof(TileSpan),
-                           hipMemcpyHostToDevice, p->stream));
-    IRS_HIP(hipMemcpyAsync(p->d_trow, p->h_trow.data(), p->h_trow.size() * sizeof(TileSpan),
-                           hipMemcpyHostToDevice, p->stream));
-    IRS_HIP(dev_alloc(&p->d_cols, (size_t)g.nx * sizeof(ColInfo)));
+    // the tiles in one copy: the rows' follow the columns'
+    const size_t ntc = p->h_tcol.size(), nt = ntc + p->h_trow.size();
+    std::vector<TileSpan> tiles(p->h_tcol);
+    tiles.insert(tiles.end(), p->h_trow.begin(), p->h_trow.end());
+    RowInfo *rows = nullptr;
+    ColInfo *cols = nullptr;
+    dev_free(p->d_tables);
+    p->d_tables = nullptr;
+    DevArena ar;
+    ar.add(rows, (size_t)g.ny);
+    ar.add(cols, (size_t)g.nx);
+    ar.add(p->d_tcol, nt);
+    IRS_HIP(ar.alloc(&p->d_tables));
+    p->d_cols = cols;
+    p->d_trow = p->d_tcol + ntc;
+    IRS_HIP(hipMemcpyAsync(p->d_tcol, tiles.data(), nt * sizeof(TileSpan), hipMemcpyHostToDevice,
+                           p->stream));
     hipLaunchKernelGGL(k_col_table, dim3((unsigned)((g.nx + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, p->stream, g, (ColInfo *)p->d_cols);
+                       dim3(kThreads), 0, p->stream, g, cols);
     IRS_HIP(hipGetLastError());
-    void *rows = nullptr;
-    IRS_HIP(dev_alloc(&rows, (size_t)g.ny * sizeof(RowInfo)));
     const unsigned nb = (unsigned)((g.ny + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(k_row_table, dim3(nb), dim3(kThreads), 0, p->stream, g, (RowInfo *)rows);
+    hipLaunchKernelGGL(k_row_table, dim3(nb), dim3(kThreads), 0, p->stream, g, rows);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
-    if (e != hipSuccess) {
-        dev_free(rows);
-        return hip_fail(e, "the level-3 row and column tables");
-    }
+    if (e != hipSuccess) return hip_fail(e, "the level-3 row and column tables");
     p->d_rows = rows;
     return IRS_OK;
 }
@@ -2640,7 +2638,7 @@ irs_status interp_tables_ready(irs_plan_s *p)
     else if (super_order(p) > 0) {
         choose_tree(p);
         for (int l = 0; l < p->tree_n; ++l)
-            if (!p->tree[l].d || p->tree_part_bytes < tree_part_need(p, l, tree_ny(p, l)))
+            if (!p->d_tree || p->tree_part_bytes < tree_part_need(p, l, tree_ny(p, l)))
                 missing = "the super- and mid-cell expansions";
     }
     if (missing) {
@@ -2666,36 +2664,80 @@ irs_status interp_prepare(irs_plan_s *p)
     return level2_prepare(p);
 }
 
-// Algorithmic FP64 flops of the level-3 rays of rows [j0, j1): per ray 46
-// (Horner of C_0..C_4: 32, sheet 2, macro term 6, beta 2, pixel 4) plus 10 per
-// nearby lens (offsets 2, r^2 3, m/r^2 1, products 2, sums 2).
-double level3_flops(irs_plan_s *p, int64_t j0, int64_t j1)
+// The sums over cells of the work recorded in cs.  Algorithmic FP64 flops:
+// expansions 10 + 8 P per lens and 8 PS P per re-expansion; level-2 points 44
+// per (point, ring lens) or, in the paper's form, distant lens, and 60 P for
+// the cell expansion's translation; level-3 rays 46 (Horner of C_0..C_4: 32,
+// sheet 2, macro term 6, beta 2, pixel 4) plus 10 per nearby lens (offsets 2,
+// r^2 3, m/r^2 1, products 2, sums 2).
+void interp_account(irs_plan_s *p, CallStats &cs)
 {
+    if (cs.work.empty()) return;
     const DevGeom &g = p->dg;
-    if (j1 <= j0) return 0.0;
-    std::vector<int64_t> &cols = p->h_cell_cols;
-    if ((int64_t)cols.size() != g.n1x) {                    // ray columns of each cell column
-        cols.assign(g.n1x, 0);
-        for (int64_t cx = 0, i = 0; cx < g.n1x; ++cx)
-            while (i < g.nx && ((2 * i + 1) * (int64_t)g.n1x) / (2 * g.nx) == cx) { ++cols[cx]; ++i; }
-    }
-    double f = 0.0;
-    for (int64_t j = j0; j < j1;) {
-        const int64_t cy = ((2 * j + 1) * (int64_t)g.n1y) / (2 * g.ny);
-        int64_t jn = j;
-        while (jn < j1 && ((2 * jn + 1) * (int64_t)g.n1y) / (2 * g.ny) == cy) ++jn;
-        double row = 0.0;
-        for (int64_t cx = 0; cx < g.n1x; ++cx) {
-            const int64_t xl = std::max<int64_t>(0, cx - 1), xh = std::min<int64_t>(g.n1x - 1, cx + 1);
-            int64_t nn = 0;
-            for (int64_t r = std::max<int64_t>(0, cy - 1); r <= std::min<int64_t>(g.n1y - 1, cy + 1); ++r)
-                nn += p->h_cell_start[r * g.n1x + xh + 1] - p->h_cell_start[r * g.n1x + xl];
-            row += (double)cols[cx] * (46.0 + 10.0 * (double)nn);
+    build_sat(p);
+    const int P = level2_order(p), PS = super_order(p);
+    auto block = [&](int64_t cx, int64_t cy, int64_t r) {   // lenses in a (2r+1)^2 block
+        return lenses_in(p, cx - r, cx + r + 1, cy - r, cy + r + 1);
+    };
+    auto around = [&](int64_t X, int64_t Y, int64_t k) {    // ... of k x k cells' 5 x 5 block
+        return lenses_in(p, (X - kSuperR) * k, (X + kSuperR + 1) * k, (Y - kSuperR) * k,
+                         (Y + kSuperR + 1) * k);
+    };
+    std::vector<int64_t> cols;                              // ray columns per cell column
+    for (const CallStats::Work &w : cs.work) {
+        double fl = 0.0;
+        if (w.kind == CallStats::kTreeRows) {
+            const int64_t k = p->tree[w.level].k, kp = w.level > 0 ? p->tree[w.level - 1].k : 0;
+            const int64_t nX = tree_nx(p, w.level);
+            for (int64_t Y = w.a; Y <= w.b; ++Y)
+                for (int64_t X = 0; X < nX; ++X) {
+                    const int64_t n = (kp ? around(X * k / kp, Y * k / kp, kp) : p->n_lens) - around(X, Y, k);
+                    fl += (double)n * (10.0 + 8.0 * PS) + (kp ? 8.0 * PS * PS : 0.0);
+                }
+            cs.level2_expand_flops += fl;
+            cs.level2_flops += fl;
+        } else if (w.kind == CallStats::kCellExpansions) {
+            const int64_t ks = PS > 0 ? p->tree[p->tree_n - 1].k : 0;
+            for (int64_t cy = w.a; cy <= w.b; ++cy)
+                for (int64_t cx = 0; cx < g.n1x; ++cx) {
+                    const int64_t n = (ks ? around(cx / ks, cy / ks, ks) : p->n_lens) - block(cx, cy, kRing);
+                    fl += (double)n * (10.0 + 8.0 * P) + (ks ? 8.0 * PS * P : 0.0);
+                }
+            cs.level2_expand_flops += fl;
+            cs.level2_flops += fl;
+        } else if (w.kind == CallStats::kPoints) {
+            const int64_t q2 = (int64_t)g.q * g.q;
+            for (int64_t cy = w.a; cy <= w.b; ++cy)
+                for (int64_t cx = 0; cx < g.n1x; ++cx) {
+                    const int64_t b3 = block(cx, cy, 1);
+                    cs.level2_pairs += q2 * (p->n_lens - b3);
+                    if (P == 0) fl += 44.0 * (double)(q2 * (p->n_lens - b3));
+                    else fl += (double)q2 * (44.0 * (double)(block(cx, cy, kRing) - b3) + 60.0 * P);
+                }
+            if (P == 0) cs.level2_expand_flops += fl;
+            cs.level2_flops += fl;
+        } else {
+            if (cols.empty()) {
+                cols.resize((size_t)g.n1x);
+                for (int64_t cx = 0; cx < g.n1x; ++cx) {
+                    int64_t a, b;
+                    level1_span(p->geo.info, 0, cx, a, b);
+                    cols[cx] = b - a;
+                }
+            }
+            for (int64_t j = w.a; j < w.b;) {
+                const int64_t cy = ((2 * j + 1) * (int64_t)g.n1y) / (2 * g.ny);
+                int64_t ra, rb;
+                level1_span(p->geo.info, 1, cy, ra, rb);
+                const int64_t jn = std::max(j + 1, std::min(w.b, rb));
+                double row = 0.0;
+                for (int64_t cx = 0; cx < g.n1x; ++cx)
+                    row += (double)cols[cx] * (46.0 + 10.0 * (double)block(cx, cy, 1));
+                cs.ray_flops += row * (double)(jn - j);
+                j = jn;
+            }
         }
-        f += row * (double)(jn - j);
-        j = jn;
     }
-    return f;
 }
 
 namespace {
@@ -2759,27 +2801,25 @@ int corner_blocks(const irs_plan_s *p, int64_t jA, int64_t jB, int64_t c[4][4])
 
 // k_level3_corner over the rays of rows [jA, jB) in the rectangle's corner
 // cells (m: the band's launch arguments)
-irs_status launch_corners(irs_plan_s *p, const L3Map &m, int64_t jA, int64_t jB)
+irs_status launch_corners(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
 {
-    int64_t c[4][4];
-    const int nc = corner_blocks(p, jA, jB, c);
+    m.ncorner = corner_blocks(p, jA, jB, m.corner);
+    int64_t most = 0;
+    for (int k = 0; k < m.ncorner; ++k)
+        most = std::max(most, (m.corner[k][1] - m.corner[k][0]) * (m.corner[k][3] - m.corner[k][2]));
+    if (most == 0) return IRS_OK;
     const bool bin = m.counts != nullptr;
-    for (int k = 0; k < nc; ++k) {
-        const int64_t n = (c[k][1] - c[k][0]) * (c[k][3] - c[k][2]);
-        const unsigned nb = (unsigned)((n + kThreads - 1) / kThreads);
-#define IRS_L3C(U, B)                                                                        \
-    hipLaunchKernelGGL((k_level3_corner<U, B>), dim3(nb), dim3(kThreads), 0, p->stream, m,   \
-                       c[k][0], c[k][1], c[k][2], c[k][3])
-        if (p->unit_mass) {
-            if (bin) IRS_L3C(true, true);
-            else IRS_L3C(true, false);
-        } else {
-            if (bin) IRS_L3C(false, true);
-            else IRS_L3C(false, false);
-        }
-#undef IRS_L3C
-        IRS_HIP(hipGetLastError());
+    const dim3 grid((unsigned)((most + kThreads - 1) / kThreads), (unsigned)m.ncorner);
+#define IRS_L3C(U, B) hipLaunchKernelGGL((k_level3_corner<U, B>), grid, dim3(kThreads), 0, p->stream, m)
+    if (p->unit_mass) {
+        if (bin) IRS_L3C(true, true);
+        else IRS_L3C(true, false);
+    } else {
+        if (bin) IRS_L3C(false, true);
+        else IRS_L3C(false, false);
     }
+#undef IRS_L3C
+    IRS_HIP(hipGetLastError());
     return IRS_OK;
 }
 
@@ -2797,14 +2837,9 @@ irs_status level2_tree_rows(irs_plan_s *p, int64_t cyA, int64_t cyB, CallStats *
         irs_status st = cs->begin(s, 0);
         if (st != IRS_OK) return st;
     }
-    double fl = 0.0;
-    irs_status st = ensure_tree_rows(p, last, cyA / ks, cyB / ks, cs ? &fl : nullptr);
+    irs_status st = ensure_tree_rows(p, last, cyA / ks, cyB / ks, cs);
     if (st != IRS_OK) return st;
-    if (cs) {
-        cs->level2_expand_flops += fl;
-        cs->level2_flops += fl;
-        if ((st = cs->end(s)) != IRS_OK) return st;
-    }
+    if (cs && (st = cs->end(s)) != IRS_OK) return st;
     return IRS_OK;
 }
 
@@ -2824,27 +2859,7 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
         if (st != IRS_OK) return st;
         cs->n_level2++;
         cs->level2_points += (c1 - c0 + 1) * row_pts;
-        const std::vector<int32_t> &hc = p->h_cell_start;
-        auto block = [&](int64_t cx, int64_t cy, int64_t r) {   // lenses in a (2r+1)^2 block
-            const int64_t xl = std::max<int64_t>(0, cx - r), xh = std::min<int64_t>(g.n1x - 1, cx + r);
-            int64_t n = 0;
-            for (int64_t row = std::max<int64_t>(0, cy - r); row <= std::min<int64_t>(g.n1y - 1, cy + r); ++row)
-                n += hc[row * g.n1x + xh + 1] - hc[row * g.n1x + xl];
-            return n;
-        };
-        for (int64_t cy = c0; cy <= c1; ++cy)
-            for (int64_t cx = 0; cx < g.n1x; ++cx) {
-                const int64_t b3 = block(cx, cy, 1);
-                cs->level2_pairs += q * q * (p->n_lens - b3);
-                if (P == 0) {
-                    const double f = 44.0 * (double)(q * q * (p->n_lens - b3));
-                    cs->level2_flops += f;
-                    cs->level2_expand_flops += f;
-                } else {
-                    const int64_t b7 = block(cx, cy, kRing);
-                    cs->level2_flops += (double)(q * q) * (44.0 * (double)(b7 - b3) + 60.0 * P);
-                }
-            }
+        cs->work.push_back({CallStats::kPoints, 0, c0, c1});
     }
     if (P == 0) {
         const unsigned nb2 = (unsigned)((c1 - c0 + 1) * g.n1x);
@@ -2864,13 +2879,8 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
         const int32_t fold = super_order(p) > 0 ? 1 : 0;
         const int32_t pe = ring_order(p);
         const unsigned nbB = (unsigned)((c1 - c0 + 1) * nxb);
-        double fl = 0.0;
-        irs_status st3 = launch_level2_expand(p, c0, c1, cs ? &fl : nullptr, true);
+        irs_status st3 = launch_level2_expand(p, c0, c1, cs, true);
         if (st3 != IRS_OK) return st3;
-        if (cs) {
-            cs->level2_expand_flops += fl;
-            cs->level2_flops += fl;
-        }
 #define IRS_L2L(U, PP)                                                                        \
     do {                                                                                      \
         if (cs && (st2 = cs->end(s)) != IRS_OK) return st2;                                  \
@@ -2953,7 +2963,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
             irs_status st = cs->begin(s, 1);
             if (st != IRS_OK) return st;
             cs->n_rays++;
-            cs->ray_flops += level3_flops(p, j0, j1);
+            cs->work.push_back({CallStats::kRays, 0, j0, j1});
         }
 #define IRS_L3(U, B)                                                                          \
     hipLaunchKernelGGL((k_level3<U, B>), dim3(nb3), dim3(kThreads), 0, s, m,                  \

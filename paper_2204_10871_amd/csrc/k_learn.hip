@@ -1584,20 +1584,40 @@ irs_status check_params(const irs_learn_params &lp, bool training)
 // gradient of the loss over n records (device) for parameters already packed
 // into wf/wb; fills grad (device) and loss (device, one double)
 struct TrainBufs {
-    DevBuf<uint16_t> act, dz;
-    DevBuf<float> part, loss_slot, loss_part;
+    uint16_t *act = nullptr, *dz = nullptr;
+    float *part = nullptr, *loss_slot = nullptr, *loss_part = nullptr;
     int32_t bn = 0, nchunk = 0;
-    irs_status alloc(int32_t batch)
+    size_t n_act = 0, n_dz = 0, n_part = 0, n_loss_part = 0;       // elements
+    // registers the buffers for `batch` slots
+    void plan(int32_t batch, DevArena &a)
     {
         bn = batch;
         const int32_t chunk = 1024;
         nchunk = (bn + chunk - 1) / chunk;
-        irs_status st = act.alloc((size_t)5 * kHd * bn);
-        if (st == IRS_OK) st = dz.alloc((size_t)(4 * kHd + kNO) * bn);
-        if (st == IRS_OK) st = part.alloc((size_t)nchunk * kNP);
-        if (st == IRS_OK) st = loss_slot.alloc((size_t)bn);
-        if (st == IRS_OK) st = loss_part.alloc((size_t)bn / 256 + 1);
-        return st;
+        n_act = (size_t)5 * kHd * bn;
+        n_dz = (size_t)(4 * kHd + kNO) * bn;
+        n_part = (size_t)nchunk * kNP;
+        n_loss_part = (size_t)bn / 256 + 1;
+        a.add(act, n_act);
+        a.add(dz, n_dz);
+        a.add(part, n_part);
+        a.add(loss_slot, (size_t)bn);
+        a.add(loss_part, n_loss_part);
+    }
+};
+
+// A DevArena's allocation, released with its owner.
+struct ArenaBuf {
+    DevArena a;
+    void *base = nullptr;
+    ~ArenaBuf() { dev_free(base); }
+    irs_status alloc()
+    {
+        if (a.alloc(&base) == hipSuccess) return IRS_OK;
+        (void)hipGetLastError();
+        base = nullptr;
+        set_error("cannot allocate device memory for the learned interpolant");
+        return IRS_E_NOMEM;
     }
 };
 
@@ -1613,10 +1633,10 @@ bool train_extents_ok(const TrainBufs &tb, int32_t n_valid)
     const int64_t chunk16 = (chunk + 15) / 16 * 16;
     static_assert(256 % kTrainCols == 0, "whole workgroups of k_mlp_train");
     return tb.bn > 0 && tb.bn % 256 == 0 && n_valid >= 0 && n_valid <= tb.bn &&
-           tb.act.n >= (size_t)5 * kHd * tb.bn &&
-           tb.dz.n >= (size_t)(4 * kHd + kNO) * tb.bn && tb.loss_slot.n >= (size_t)tb.bn &&
-           tb.loss_part.n >= (size_t)tb.bn / 256 &&
-           tb.part.n >= (size_t)tb.nchunk * kNP && chunk16 % 16 == 0 &&
+           tb.n_act >= (size_t)5 * kHd * tb.bn &&
+           tb.n_dz >= (size_t)(4 * kHd + kNO) * tb.bn &&
+           tb.n_loss_part >= (size_t)tb.bn / 256 &&
+           tb.n_part >= (size_t)tb.nchunk * kNP && chunk16 % 16 == 0 &&
            (int64_t)tb.nchunk * chunk16 >= tb.bn && tb.bn % 16 == 0;
 }
 
@@ -1630,14 +1650,14 @@ irs_status grad_step(hipStream_t s, TrainBufs &tb, const void *wf, const void *w
     }
     hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)(tb.bn / kTrainCols)), dim3(kThreads), 0, s,
                        (const uint4 *)wf, (const uint4 *)wb, theta, freq, samples, n_samples, base,
-                       mult, n_valid, tb.bn, tb.act.p, tb.dz.p, tb.loss_slot.p);
+                       mult, n_valid, tb.bn, tb.act, tb.dz, tb.loss_slot);
     const int32_t chunk = (tb.bn + tb.nchunk - 1) / tb.nchunk;
     const int32_t chunk16 = (chunk + 15) / 16 * 16, nloss = tb.bn / 256;
     hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kGradItems * tb.nchunk + nloss)), dim3(kW), 0, s,
-                       tb.act.p, tb.dz.p, tb.bn, chunk16, tb.nchunk, tb.loss_slot.p, tb.part.p,
-                       tb.loss_part.p);
+                       tb.act, tb.dz, tb.bn, chunk16, tb.nchunk, tb.loss_slot, tb.part,
+                       tb.loss_part);
     hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)((kNP + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       s, tb.part.p, tb.nchunk, tb.loss_part.p, nloss, grad, loss);
+                       s, tb.part, tb.nchunk, tb.loss_part, nloss, grad, loss);
     IRS_HIP(hipGetLastError());
     return IRS_OK;
 }
@@ -1857,12 +1877,14 @@ irs_status irs_learn(irs_plan_t p, const irs_learn_params *lpp, const float *fre
     DevBuf<float> grad, mom, var;
     DevBuf<double> losses;
     TrainBufs tb;
+    ArenaBuf tbuf;
+    tb.plan(lp.batch, tbuf.a);
     if ((st = wb.alloc((size_t)kFragBwd * 8)) != IRS_OK) return st;
     if ((st = grad.alloc(kNP)) != IRS_OK || (st = mom.alloc(kNP)) != IRS_OK ||
         (st = var.alloc(kNP)) != IRS_OK)
         return st;
     if ((st = losses.alloc((size_t)std::max(1, lp.steps))) != IRS_OK) return st;
-    if ((st = tb.alloc(lp.batch)) != IRS_OK) return st;
+    if ((st = tbuf.alloc()) != IRS_OK) return st;
     IRS_HIP(hipMemsetAsync(mom.p, 0, sizeof(float) * kNP, s));
     IRS_HIP(hipMemsetAsync(var.p, 0, sizeof(float) * kNP, s));
     const int64_t ne = (int64_t)(kFragFwd + kFragBwd) * 8;
@@ -2011,19 +2033,21 @@ irs_status irs_mlp_forward(int64_t n, const float *freqs, const float *theta, co
     }
     if (n == 0) return IRS_OK;
     const hipStream_t s = (hipStream_t)hip_stream;
-    DevBuf<float> dth, dfr;
-    DevBuf<uint4> wf;
-    irs_status st;
-    if ((st = dth.alloc(kNP)) != IRS_OK || (st = dfr.alloc(2 * kNF)) != IRS_OK ||
-        (st = wf.alloc(kFragFwd)) != IRS_OK)
-        return st;
-    IRS_HIP(hipMemcpyAsync(dth.p, theta, sizeof(float) * kNP, hipMemcpyHostToDevice, s));
-    IRS_HIP(hipMemcpyAsync(dfr.p, freqs, sizeof(float) * 2 * kNF, hipMemcpyHostToDevice, s));
+    float *dth = nullptr, *dfr = nullptr;
+    uint4 *wf = nullptr;
+    ArenaBuf buf;
+    buf.a.add(dth, kNP);
+    buf.a.add(dfr, 2 * kNF);
+    buf.a.add(wf, kFragFwd);
+    irs_status st = buf.alloc();
+    if (st != IRS_OK) return st;
+    IRS_HIP(hipMemcpyAsync(dth, theta, sizeof(float) * kNP, hipMemcpyHostToDevice, s));
+    IRS_HIP(hipMemcpyAsync(dfr, freqs, sizeof(float) * 2 * kNF, hipMemcpyHostToDevice, s));
     const int64_t ne = (int64_t)kFragFwd * 8;
     hipLaunchKernelGGL(k_mlp_pack, dim3((unsigned)((ne + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                       dth.p, (uint16_t *)wf.p, (uint16_t *)nullptr);
+                       dth, (uint16_t *)wf, (uint16_t *)nullptr);
     IRS_HIP(hipGetLastError());
-    if ((st = launch_mlp_fwd(s, wf.p, dth.p, dfr.p, n, h, y)) != IRS_OK) return st;
+    if ((st = launch_mlp_fwd(s, wf, dth, dfr, n, h, y)) != IRS_OK) return st;
     IRS_HIP(hipStreamSynchronize(s));
     return IRS_OK;
 }
@@ -2036,28 +2060,33 @@ irs_status irs_mlp_loss_grad(int64_t n, const float *freqs, const float *theta, 
         return IRS_E_INVALID;
     }
     const hipStream_t s = (hipStream_t)hip_stream;
-    DevBuf<float> dth, dfr, dg;
-    DevBuf<uint16_t> wf, wb;
-    DevBuf<double> dl;
-    TrainBufs tb;
-    irs_status st;
     const int32_t bn = (int32_t)((n + 255) / 256 * 256);
-    if ((st = dth.alloc(kNP)) != IRS_OK || (st = dfr.alloc(2 * kNF)) != IRS_OK ||
-        (st = dg.alloc(kNP)) != IRS_OK || (st = wf.alloc((size_t)kFragFwd * 8)) != IRS_OK ||
-        (st = wb.alloc((size_t)kFragBwd * 8)) != IRS_OK || (st = dl.alloc(1)) != IRS_OK ||
-        (st = tb.alloc(bn)) != IRS_OK)
-        return st;
-    IRS_HIP(hipMemcpyAsync(dth.p, theta, sizeof(float) * kNP, hipMemcpyHostToDevice, s));
-    IRS_HIP(hipMemcpyAsync(dfr.p, freqs, sizeof(float) * 2 * kNF, hipMemcpyHostToDevice, s));
+    // one allocation for the call
+    float *dth = nullptr, *dfr = nullptr, *dg = nullptr;
+    uint16_t *wf = nullptr, *wb = nullptr;
+    double *dl = nullptr;
+    TrainBufs tb;
+    ArenaBuf buf;
+    buf.a.add(dth, kNP);
+    buf.a.add(dfr, 2 * kNF);
+    buf.a.add(dg, kNP);
+    buf.a.add(wf, (size_t)kFragFwd * 8);
+    buf.a.add(wb, (size_t)kFragBwd * 8);
+    buf.a.add(dl, 1);
+    tb.plan(bn, buf.a);
+    irs_status st = buf.alloc();
+    if (st != IRS_OK) return st;
+    IRS_HIP(hipMemcpyAsync(dth, theta, sizeof(float) * kNP, hipMemcpyHostToDevice, s));
+    IRS_HIP(hipMemcpyAsync(dfr, freqs, sizeof(float) * 2 * kNF, hipMemcpyHostToDevice, s));
     const int64_t ne = (int64_t)(kFragFwd + kFragBwd) * 8;
     hipLaunchKernelGGL(k_mlp_pack, dim3((unsigned)((ne + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                       dth.p, wf.p, wb.p);
+                       dth, wf, wb);
     // slots i < n take sample i (base 0, multiplier 1)
-    if ((st = grad_step(s, tb, wf.p, wb.p, dth.p, dfr.p, samples, n, 0, 1, (int32_t)n, dg.p, dl.p)) != IRS_OK)
+    if ((st = grad_step(s, tb, wf, wb, dth, dfr, samples, n, 0, 1, (int32_t)n, dg, dl)) != IRS_OK)
         return st;
     double l = 0.0;
-    IRS_HIP(hipMemcpyAsync(&l, dl.p, sizeof(double), hipMemcpyDeviceToHost, s));
-    if (grad) IRS_HIP(hipMemcpyAsync(grad, dg.p, sizeof(float) * kNP, hipMemcpyDeviceToHost, s));
+    IRS_HIP(hipMemcpyAsync(&l, dl, sizeof(double), hipMemcpyDeviceToHost, s));
+    if (grad) IRS_HIP(hipMemcpyAsync(grad, dg, sizeof(float) * kNP, hipMemcpyDeviceToHost, s));
     IRS_HIP(hipStreamSynchronize(s));
     if (loss) *loss = l / (double)n;
     return IRS_OK;

@@ -219,7 +219,31 @@ irs_status pack_level1(irs_plan_s *p, const double *hx, const double *hy, const 
     const int32_t ncell = (int32_t)ncell64;
     hipStream_t s = p->stream;
 
-    IRS_HIP(dev_alloc(&p->d_cell_start, sizeof(int32_t) * (size_t)(ncell + 1)));
+    int bits = 0;
+    while (bits < 31 && ((ncell - 1) >> bits) != 0) ++bits;
+    // the index buffer that the sort's last pass writes is the plan's (the
+    // input index of every packed lens)
+    double *ux = nullptr, *uy = nullptr, *um = nullptr;
+    int32_t *key = nullptr, *val = nullptr, *key2 = nullptr, *val2 = nullptr;
+    int32_t *cnt = nullptr, *hist = nullptr, *sums = nullptr;
+    const bool odd = (bits + kRadixBits - 1) / kRadixBits % 2 != 0;
+    {
+        DevArena a;
+        a.add(p->d_landed, kLandedSlots);
+        a.add(p->d_cell_start, (size_t)ncell + 1);
+        IRS_HIP(a.alloc(&p->d_cells));
+    }
+    if (n > 0) {
+        DevArena a;
+        a.add(p->d_x, n);
+        a.add(p->d_y, n);
+        if (hm) a.add(p->d_m, n);
+        a.add(p->d_cxy, n);
+        a.add(p->d_xy, 2 * (size_t)n);
+        IRS_HIP(a.alloc(&p->d_lenses));
+        IRS_HIP(dev_alloc(&p->d_order, sizeof(int32_t) * (size_t)n));
+        (odd ? val2 : val) = p->d_order;
+    }
     p->h_cell_start.assign((size_t)ncell + 1, 0);
     if (n == 0) {
         IRS_HIP(hipMemsetAsync(p->d_cell_start, 0, sizeof(int32_t) * (size_t)(ncell + 1), s));
@@ -227,22 +251,12 @@ irs_status pack_level1(irs_plan_s *p, const double *hx, const double *hy, const 
         return IRS_OK;
     }
     const size_t nb = sizeof(double) * (size_t)n;
-    IRS_HIP(dev_alloc(&p->d_x, nb));
-    IRS_HIP(dev_alloc(&p->d_y, nb));
-    if (hm) IRS_HIP(dev_alloc(&p->d_m, nb));
-    IRS_HIP(dev_alloc(&p->d_cxy, sizeof(uint32_t) * (size_t)n));
-    IRS_HIP(dev_alloc(&p->d_xy, 2 * nb));
-
-    double *ux = nullptr, *uy = nullptr, *um = nullptr;
-    int32_t *key = nullptr, *val = nullptr, *key2 = nullptr, *val2 = nullptr;
-    int32_t *cnt = nullptr, *hist = nullptr, *sums = nullptr;
+    void *temp = nullptr, *sort = nullptr;
     irs_status st = IRS_OK;
     const int32_t nscan = ncell + 1;  // per-cell counts then a zero: cell_start[ncell] = n
     const int32_t nblk = (n + kSortBlock - 1) / kSortBlock;
     const int32_t nhist = kRadix * nblk;
     const int32_t nsums = (std::max(nscan, nhist) + kScanBlock - 1) / kScanBlock;
-    int bits = 0;
-    while (bits < 31 && ((ncell - 1) >> bits) != 0) ++bits;
 
     auto fail = [&](hipError_t e, const char *what) {
         st = hip_fail(e, what);
@@ -265,16 +279,20 @@ irs_status pack_level1(irs_plan_s *p, const double *hx, const double *hy, const 
         return hipGetLastError();
     };
 
-    IRS_TRY(dev_alloc(&ux, nb));
-    IRS_TRY(dev_alloc(&uy, nb));
-    if (hm) IRS_TRY(dev_alloc(&um, nb));
-    IRS_TRY(dev_alloc(&key, sizeof(int32_t) * (size_t)n));
-    IRS_TRY(dev_alloc(&val, sizeof(int32_t) * (size_t)n));
-    IRS_TRY(dev_alloc(&key2, sizeof(int32_t) * (size_t)n));
-    IRS_TRY(dev_alloc(&val2, sizeof(int32_t) * (size_t)n));
-    IRS_TRY(dev_alloc(&cnt, sizeof(int32_t) * (size_t)nscan));
-    IRS_TRY(dev_alloc(&hist, sizeof(int32_t) * (size_t)nhist));
-    IRS_TRY(dev_alloc(&sums, sizeof(int32_t) * (size_t)nsums));
+    {
+        DevArena a, b;
+        a.add(ux, n);
+        a.add(uy, n);
+        if (hm) a.add(um, n);
+        IRS_TRY(a.alloc(&temp));
+        b.add(key, n);
+        b.add(key2, n);
+        b.add(odd ? val : val2, n);
+        b.add(cnt, nscan);
+        b.add(hist, nhist);
+        b.add(sums, nsums);
+        IRS_TRY(b.alloc(&sort));
+    }
     IRS_TRY(hipMemcpyAsync(ux, hx, nb, hipMemcpyHostToDevice, s));
     IRS_TRY(hipMemcpyAsync(uy, hy, nb, hipMemcpyHostToDevice, s));
     if (hm) IRS_TRY(hipMemcpyAsync(um, hm, nb, hipMemcpyHostToDevice, s));
@@ -305,24 +323,14 @@ irs_status pack_level1(irs_plan_s *p, const double *hx, const double *hy, const 
         hipLaunchKernelGGL(k_gather, dim3(nbk), dim3(tb), 0, s, val, key, ux, uy, um, n,
                            p->dg.n1x, p->d_x, p->d_y, p->d_m, p->d_cxy, (double2 *)p->d_xy);
         IRS_TRY(hipGetLastError());
-        p->d_order = val;  // kept: the input index of every packed lens
-        val = nullptr;
         IRS_TRY(hipMemcpyAsync(p->h_cell_start.data(), p->d_cell_start,
                                sizeof(int32_t) * (size_t)(ncell + 1), hipMemcpyDeviceToHost, s));
         IRS_TRY(hipStreamSynchronize(s));
     }
 done:
 #undef IRS_TRY
-    dev_free(ux);
-    dev_free(uy);
-    dev_free(um);
-    dev_free(key);
-    dev_free(val);
-    dev_free(key2);
-    dev_free(val2);
-    dev_free(cnt);
-    dev_free(hist);
-    dev_free(sums);
+    dev_free(temp);
+    dev_free(sort);
     return st;
 }
 

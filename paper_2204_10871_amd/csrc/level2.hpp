@@ -24,12 +24,12 @@ int32_t level2_chunks(const irs_plan_s *p);
 // Lt_n of cell (cx, cy) at
 //   d_part[((((cy - c0) n1x + cx) nchunk + k) P + n) 2 + {0: Re, 1: Im}],
 // nchunk = level2_chunks(p); the cell expansion is the sum of its parts in
-// order.  Computes the super rows it needs that are not cached.  flops, if
-// not null, receives the algorithmic flops of the launches.  Grows the
-// buffers as needed.  Requires level2_order(p) > 0.
+// order.  Computes the tree rows it needs that are not cached.  cs, if not
+// null, records the launches.  Grows the buffers as needed.  Requires
+// level2_order(p) > 0.
 // fold_sheet: cells away from the rectangle's corners take the sheet's series
 // into their expansion (the level-2 points then add only -kappa_* conj(z0))
-irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, double *flops = nullptr,
+irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, CallStats *cs = nullptr,
                                 bool fold_sheet = false);
 
 // Forget the cached super rows (the next expansion recomputes them).

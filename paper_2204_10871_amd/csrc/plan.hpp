@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -61,14 +62,17 @@ struct irs_plan_s {
     int64_t coef_budget = (int64_t)2 << 30;   // bytes for one band of level-2 coefficients
 
     // Lenses packed into level-1 cells (row-major cell order; inside a cell in
-    // increasing input order).  FP64 positions and masses.
+    // increasing input order).  FP64 positions and masses.  d_cell_start and
+    // d_landed lie in one allocation, d_cells; the lens arrays in d_lenses.
+    void *d_cells = nullptr, *d_lenses = nullptr;
     double *d_x = nullptr, *d_y = nullptr, *d_m = nullptr;   // d_m null when unit masses
     int32_t *d_cell_start = nullptr;                         // n1x*n1y + 1
     uint32_t *d_cxy = nullptr;                               // per sorted lens: cy << 16 | cx
     int32_t *d_order = nullptr;                              // per sorted lens: input index
     double *d_xy = nullptr;                                  // (x, y) pairs, sorted order
     std::vector<int32_t> h_cell_start;                       // host copy (work counts)
-    std::vector<int64_t> h_cell_cols;                        // ray columns per cell column
+    std::vector<int32_t> h_sat;                              // lenses of cells [0, x) x [0, y)
+                                                             //   at y (n1x + 1) + x (work counts)
 
     // Level-2 coefficients of one band of level-1 rows: 10 doubles per point
     // (Re/Im of C0..C4), point (gx, gy) at ((gy - band_row0*q) * n1x*q + gx).
@@ -77,10 +81,12 @@ struct irs_plan_s {
     // change) or until level2_reset.
     int32_t tree_n = 0;                   // levels
     irs::TreeLevel tree[irs::kTreeLevels];
+    double *d_tree = nullptr;             // the levels' expansions
     double *d_tree_part = nullptr;        // partial expansions of a level's launch
     size_t tree_part_bytes = 0;
-    void *d_rows = nullptr;               // level-3 row table (ny entries of 32 B)
-    void *d_cols = nullptr;               // level-3 column table (nx entries of 48 B)
+    void *d_tables = nullptr;             // one allocation: the four tables below
+    void *d_rows = nullptr;               // level-3 row table (ny entries of 64 B)
+    void *d_cols = nullptr;               // level-3 column table (nx entries of 16 B)
     // level-3 tiles: column tiles of <= 64 ray columns, row tiles of <= 32 ray
     // rows, following the level-1 cells where cells are wide (tall) enough
     irs::TileSpan *d_tcol = nullptr, *d_trow = nullptr;
@@ -108,7 +114,7 @@ struct irs_plan_s {
 
     // Scratch for host-side outputs.
     uint32_t *d_counts = nullptr;  // npix^2, used when counts are on the host
-    unsigned long long *d_landed = nullptr;   // rays binned by the current call
+    unsigned long long *d_landed = nullptr;   // rays binned by the current call (in d_cells)
     void *d_tmp = nullptr;
     size_t tmp_bytes = 0;
 };
@@ -146,6 +152,32 @@ inline hipError_t dev_alloc(T **ptr, size_t bytes)
     return dev_alloc_bytes((void **)ptr, bytes);
 }
 
+// Several device arrays in one allocation (each starts on 256 bytes): add()
+// registers a pointer, alloc() allocates and sets them all; alloc() false:
+// nothing allocated, the pointers unchanged.  A hipMalloc and hipFree pair
+// costs tens of microseconds, a map's kernels often less.
+struct DevArena {
+    static constexpr int kMost = 16;
+    void **ptr[kMost];
+    size_t off[kMost];
+    int n = 0;
+    size_t bytes = 0;
+    template <class T>
+    void add(T *&p, size_t count)
+    {
+        ptr[n] = (void **)&p;
+        off[n++] = bytes;
+        bytes += (count * sizeof(T) + 255) / 256 * 256;
+    }
+    hipError_t alloc(void **base)
+    {
+        const hipError_t e = dev_alloc_bytes(base, std::max<size_t>(bytes, 256));
+        if (e == hipSuccess)
+            for (int k = 0; k < n; ++k) *ptr[k] = (char *)*base + off[k];
+        return e;
+    }
+};
+
 // Status plumbing shared by the launch wrappers and the C ABI.
 void set_error(const std::string &msg);
 irs_status hip_fail(hipError_t e, const char *what);
@@ -174,6 +206,15 @@ struct CallStats {
     int32_t n_level2 = 0, n_rays = 0;
     double ms_level2 = 0.0, ms_level2_expand = 0.0, ms_rays = 0.0;
     bool timed = false;
+    // What the call launched, for interp_account: the sums over cells that the
+    // statistics report are taken after the launches, while the GPU works.
+    enum WorkKind { kTreeRows, kCellExpansions, kPoints, kRays };
+    struct Work {
+        WorkKind kind;
+        int level;                    // kTreeRows
+        int64_t a, b;                 // rows [a, b] (kRays: ray rows [a, b))
+    };
+    std::vector<Work> work;
     std::vector<hipEvent_t> ev;       // start/stop pairs, in launch order
     std::vector<int> ev_kind;         // 0 = level-2 expansion, 2 = level-2 points, 1 = rays
     // Record the start event of a launch of kind k (no-op unless timed).
@@ -197,6 +238,8 @@ struct RaySel {
 irs_status launch_direct(irs_plan_s *p, const RaySel &sel);
 irs_status launch_interp(irs_plan_s *p, const RaySel &sel);
 irs_status launch_learned(irs_plan_s *p, const RaySel &sel);
+// Adds up the work of the interpolated launches recorded in cs.
+void interp_account(irs_plan_s *p, CallStats &cs);
 void learn_release(irs_plan_s *p);
 
 // FP32 direct tile shapes: rays per lane x lenses per LDS stage.
@@ -242,7 +285,8 @@ irs_status interp_maps_table(const void *args, int32_t n, void *d_maps, int64_t 
                              int64_t *d_cstart, hipStream_t s);
 irs_status launch_interp_maps(hipStream_t s, bool unit, const void *args, const void *d_maps,
                               const int64_t *d_start, const int64_t *d_cstart, int32_t n);
-// Fill kernel (graph-safe zeroing): n 32-bit words.
-irs_status launch_zero(hipStream_t s, void *ptr, size_t n_words);
+// Fill kernel (graph-safe zeroing): n 32-bit words, and m more at ptr2.
+irs_status launch_zero(hipStream_t s, void *ptr, size_t n_words, void *ptr2 = nullptr,
+                       size_t m_words = 0);
 
 }  // namespace irs
