@@ -919,22 +919,20 @@ constexpr int kRingRows = 2 * kRing + 1, kRingCols = kCellsPerBlock + 2 * kRing;
 constexpr int kRingSegs = (kRingRows - 3) + 2 * 3;
 
 // The ring lenses of a workgroup's four cells (one level-1 row), which lie in
-// one block of 7 rows x 10 columns of cells.  STAGED: the lenses are copied to
-// LDS; the host takes such an instance when no such block of the plan holds
-// more than kRingCap lenses (ring_fits).
-template <bool UNIT, bool STAGED>
+// one block of 7 rows x 10 columns of cells, copied to LDS; the host takes the
+// kernels that do so when no such block of the plan holds more than kRingCap
+// lenses (ring_fits).
+template <bool UNIT>
 struct RingLds {
-    static constexpr int kCap = STAGED ? kRingCap : 1;
-    double rx[kCap], ry[kCap], rm[UNIT ? 1 : kCap];
+    double rx[kRingCap], ry[kRingCap], rm[UNIT ? 1 : kRingCap];
     int32_t cs[kRingRows][kRingCols + 1];     // cell_start over the block
     int32_t rb[kRingRows + 1];                // LDS offset of each row
-    int2 seg[kCellsPerBlock][kRingSegs];      // STAGED: each cell's runs in LDS
-    int32_t ya, yb, ua;                       // the block's rows and first column
+    int2 seg[kCellsPerBlock][kRingSegs];      // each cell's runs in LDS
 };
 
 // Fills it (every thread of the workgroup; ends synchronised).
-template <bool UNIT, bool STAGED>
-__device__ __forceinline__ void stage_ring(RingLds<UNIT, STAGED> &sm, const DevGeom &g,
+template <bool UNIT>
+__device__ __forceinline__ void stage_ring(RingLds<UNIT> &sm, const DevGeom &g,
                                            const double *__restrict__ lx,
                                            const double *__restrict__ ly,
                                            const double *__restrict__ lm,
@@ -946,11 +944,6 @@ __device__ __forceinline__ void stage_ring(RingLds<UNIT, STAGED> &sm, const DevG
     const int32_t ya = max(0, cy - kRing), yb = min(g.n1y - 1, cy + kRing);
     const int32_t ua = max(0, cx0 - kRing), ub = min(g.n1x - 1, cx0 + kCellsPerBlock - 1 + kRing);
     const int nrow = yb - ya + 1, ncol = ub - ua + 1;
-    if (tid == 0) {
-        sm.ya = ya;
-        sm.yb = yb;
-        sm.ua = ua;
-    }
     for (int e = tid; e < nrow * (ncol + 1); e += kThreads) {
         const int r = e / (ncol + 1), c = e % (ncol + 1);
         sm.cs[r][c] = cell_start[(int64_t)(ya + r) * g.n1x + ua + c];
@@ -961,52 +954,209 @@ __device__ __forceinline__ void stage_ring(RingLds<UNIT, STAGED> &sm, const DevG
         for (int r = 0; r < nrow; ++r) sm.rb[r + 1] = sm.rb[r] + (sm.cs[r][ncol] - sm.cs[r][0]);
     }
     __syncthreads();
-    if constexpr (STAGED) {
-        const int total = min(sm.rb[nrow], kRingCap);               // == rb[nrow] (ring_fits)
-        for (int i = tid; i < total; i += kThreads) {
-            int r = 0;
-            while (sm.rb[r + 1] <= i) ++r;
-            const int32_t src = sm.cs[r][0] + (i - sm.rb[r]);
-            sm.rx[i] = lx[src];
-            sm.ry[i] = ly[src];
-            if (!UNIT) sm.rm[i] = lm[src];
-        }
-        // each cell's runs of ring cells as ranges of the staged lenses, in
-        // row order (rows cy - kRing .. cy + kRing; left run before right)
-        if (tid < kCellsPerBlock * kRingSegs) {
-            const int w = tid / kRingSegs, sg = tid % kRingSegs;
-            const int outer = kRing - 1;                      // outer rows on each side
-            int dr, kind;                                     // kind 0: whole, 1: left, 2: right
-            if (sg < outer) { dr = sg - kRing; kind = 0; }
-            else if (sg < outer + 6) { dr = (sg - outer) / 2 - 1; kind = 1 + ((sg - outer) & 1); }
-            else { dr = sg - outer - 6 + 2; kind = 0; }
-            const int32_t row = cy + dr, ccx = cx0 + w;
-            int2 be = {0, 0};
-            if (row >= ya && row <= yb && ccx < g.n1x) {
-                int32_t xa = kind == 2 ? ccx + 2 : ccx - kRing;
-                int32_t xb = kind == 1 ? ccx - 2 : ccx + kRing;
-                xa = max(xa, 0);
-                xb = min(xb, g.n1x - 1);
-                if (xa <= xb) {
-                    const int r = row - ya;
-                    const int32_t off = sm.rb[r] - sm.cs[r][0];
-                    be.x = min(sm.cs[r][xa - ua] + off, kRingCap);
-                    be.y = min(sm.cs[r][xb + 1 - ua] + off, kRingCap);
-                }
+    const int total = min(sm.rb[nrow], kRingCap);               // == rb[nrow] (ring_fits)
+    for (int i = tid; i < total; i += kThreads) {
+        int r = 0;
+        while (sm.rb[r + 1] <= i) ++r;
+        const int32_t src = sm.cs[r][0] + (i - sm.rb[r]);
+        sm.rx[i] = lx[src];
+        sm.ry[i] = ly[src];
+        if (!UNIT) sm.rm[i] = lm[src];
+    }
+    // each cell's runs of ring cells as ranges of the staged lenses, in
+    // row order (rows cy - kRing .. cy + kRing; left run before right)
+    if (tid < kCellsPerBlock * kRingSegs) {
+        const int w = tid / kRingSegs, sg = tid % kRingSegs;
+        const int outer = kRing - 1;                      // outer rows on each side
+        int dr, kind;                                     // kind 0: whole, 1: left, 2: right
+        if (sg < outer) { dr = sg - kRing; kind = 0; }
+        else if (sg < outer + 6) { dr = (sg - outer) / 2 - 1; kind = 1 + ((sg - outer) & 1); }
+        else { dr = sg - outer - 6 + 2; kind = 0; }
+        const int32_t row = cy + dr, ccx = cx0 + w;
+        int2 be = {0, 0};
+        if (row >= ya && row <= yb && ccx < g.n1x) {
+            int32_t xa = kind == 2 ? ccx + 2 : ccx - kRing;
+            int32_t xb = kind == 1 ? ccx - 2 : ccx + kRing;
+            xa = max(xa, 0);
+            xb = min(xb, g.n1x - 1);
+            if (xa <= xb) {
+                const int r = row - ya;
+                const int32_t off = sm.rb[r] - sm.cs[r][0];
+                be.x = min(sm.cs[r][xa - ua] + off, kRingCap);
+                be.y = min(sm.cs[r][xb + 1 - ua] + off, kRingCap);
             }
-            sm.seg[w][sg] = be;
         }
+        sm.seg[w][sg] = be;
     }
     __syncthreads();
 }
 
+// c_k = s^-(k+1) sum_n C(n,k) Lt_n d^(n-k): the polynomial sum_n Lt_n d^n and its
+// derivatives over k! by one Horner pass from n = P-1 down (D_k <- D_k d +
+// D_(k-1), D_0 <- D_0 d + Lt_n).
+template <int P>
+__device__ __forceinline__ void cell_series(const double (*L)[2], double dr, double di, double isc,
+                                            cplx c[5])
+{
+    double cr[5] = {0, 0, 0, 0, 0}, ci[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+    for (int n = P - 1; n >= 0; --n) {
+#pragma unroll
+        for (int k = 4; k >= 0; --k) {
+            const double ar = k > 0 ? cr[k - 1] : L[n][0];
+            const double ai = k > 0 ? ci[k - 1] : L[n][1];
+            const double nr = fma(cr[k], dr, fma(-ci[k], di, ar));
+            ci[k] = fma(cr[k], di, fma(ci[k], dr, ai));
+            cr[k] = nr;
+        }
+    }
+    double sk = isc;                                  // 1/s^(k+1)
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        c[k] = {cr[k] * sk, ci[k] * sk};
+        sk *= isc;
+    }
+}
+
+// One ring lens (inside the (2R+1)^2 block, outside the 3 x 3 block) at offset
+// (wr, wi) from the point; 1/|w|^2 is the reciprocal estimate after one Newton
+// step (~2^-48).
+template <bool UNIT>
+__device__ __forceinline__ void add_ring_lens(double wr, double wi, double M, cplx c[5])
+{
+    const double rr = fma(wr, wr, wi * wi);
+    double inv = __builtin_amdgcn_rcp(rr);
+    inv = fma(inv, fma(-rr, inv, 1.0), inv);
+    const cplx u = {wr * inv, -wi * inv};
+    cplx t1 = UNIT ? u : cplx{M * u.r, M * u.i};
+    c[0].r += t1.r; c[0].i += t1.i;
+    cplx t2 = cmul(t1, u);
+    c[1].r -= t2.r; c[1].i -= t2.i;
+    cplx t3 = cmul(t2, u);
+    c[2].r += t3.r; c[2].i += t3.i;
+    cplx t4 = cmul(t3, u);
+    c[3].r -= t4.r; c[3].i -= t4.i;
+    cplx t5 = cmul(t4, u);
+    c[4].r += t5.r; c[4].i += t5.i;
+}
+
+// The runs [pb, pe) of a cell's ring lenses in the sorted order, row by row,
+// left run before right.
+template <class F>
+__device__ __forceinline__ void ring_runs(const DevGeom &g, const int32_t *__restrict__ cell_start,
+                                          int32_t cx, int32_t cy, F run)
+{
+    const int32_t ya = max(0, cy - kRing), yb = min(g.n1y - 1, cy + kRing);
+    for (int32_t row = ya; row <= yb; ++row) {
+        const bool mid = abs(row - cy) <= 1;
+        for (int seg = 0; seg < (mid ? 2 : 1); ++seg) {
+            int32_t xa, xb;
+            if (!mid) { xa = cx - kRing; xb = cx + kRing; }
+            else if (seg == 0) { xa = cx - kRing; xb = cx - 2; }
+            else { xa = cx + 2; xb = cx + kRing; }
+            xa = max(xa, 0);
+            xb = min(xb, g.n1x - 1);
+            if (xa > xb) continue;
+            run(cell_start[(int64_t)row * g.n1x + xa], cell_start[(int64_t)row * g.n1x + xb + 1]);
+        }
+    }
+}
+
+// Level-2 point (gx, row gyl of the cell's q) of a cell that takes the sheet's
+// closed form: L: its expansion.
+template <bool UNIT, int P>
+__device__ __forceinline__ void closed_point(const DevGeom &g, const double *__restrict__ lx,
+                                             const double *__restrict__ ly,
+                                             const double *__restrict__ lm,
+                                             const int32_t *__restrict__ cell_start,
+                                             const double (*L)[2], int32_t cx, int32_t cy,
+                                             int32_t cy0, int pt, double *__restrict__ coef)
+{
+    const int q = g.q;
+    const int64_t gx = (int64_t)cx * q + pt % q, gyl = pt / q;
+    const double x0 = level2_x(g, gx), y0 = level2_y(g, (int64_t)cy * q + gyl);
+    const double isc = 1.0 / fmax(g.w1, g.h1);
+    const double czr = g.a1 + ((double)cx + 0.5) * g.w1, czi = g.b1 + ((double)cy + 0.5) * g.h1;
+    cplx c[5], sh[5];
+    cell_series<P>(L, (x0 - czr) * isc, (y0 - czi) * isc, isc, c);
+    ring_runs(g, cell_start, cx, cy, [&](int32_t pb, int32_t pe) {
+        for (int32_t pl = pb; pl < pe; ++pl)
+            add_ring_lens<UNIT>(x0 - lx[pl], y0 - ly[pl], UNIT ? 1.0 : lm[pl], c);
+    });
+    sheet_coeffs(g, x0, y0, sh);
+    double2 *dst = (double2 *)(coef + (((int64_t)(cy - cy0) * q + gyl) * ((int64_t)g.n1x * q) + gx) * 10);
+#pragma unroll
+    for (int o = 0; o < 5; ++o) dst[o] = make_double2(c[o].r + sh[o].r, c[o].i + sh[o].i);
+}
+
+// A cell's expansion, its parts summed in chunk order, into L.
+template <int P>
+__device__ __forceinline__ void load_series(const DevGeom &g, const double *__restrict__ part,
+                                            int32_t cx, int32_t cy, int32_t cy0, int32_t nchunk,
+                                            double (*L)[2])
+{
+    for (int e = threadIdx.x; e < P * 2; e += kThreads) {
+        const double *src = part + ((int64_t)(cy - cy0) * g.n1x + cx) * nchunk * P * 2 + e;
+        double acc = 0.0;
+        for (int k = 0; k < nchunk; ++k) acc += src[(int64_t)k * P * 2];
+        L[e / 2][e % 2] = acc;
+    }
+}
+
+// The cells of a band that take the closed form, 256 points a workgroup: with
+// the sheet folded into the cell expansions they lie within a few cells of the
+// rectangle's corners (nbx x nby cells at each, closed_extent), otherwise
+// anywhere (nbx, nby: half the grid).  blockIdx.x - b0 counts points' blocks,
+// columns, rows and corners.
+template <bool UNIT, int P>
+__device__ __forceinline__ void closed_block(const DevGeom &g, const double *__restrict__ lx,
+                                             const double *__restrict__ ly,
+                                             const double *__restrict__ lm,
+                                             const int32_t *__restrict__ cell_start, int32_t cy0,
+                                             int32_t rows, uint32_t b, int32_t nbx, int32_t nby,
+                                             int32_t nchunk, int32_t fold,
+                                             const double *__restrict__ part,
+                                             double *__restrict__ coef, double (*L)[2])
+{
+    const int npts = g.q * g.q;
+    const uint32_t split = (uint32_t)(npts + kThreads - 1) / kThreads;
+    const int p0 = (int)(b % split) * kThreads;
+    b /= split;
+    const int32_t dx = (int32_t)(b % (uint32_t)nbx);
+    b /= (uint32_t)nbx;
+    const int32_t dy = (int32_t)(b % (uint32_t)nby);
+    b /= (uint32_t)nby;
+    const bool right = b & 1u, top = b & 2u;
+    const int32_t cx = right ? g.n1x - 1 - dx : dx, cy = top ? g.n1y - 1 - dy : dy;
+    // each cell from its nearer corner only
+    if (cx < 0 || cx >= g.n1x || cy < cy0 || cy >= cy0 + rows) return;
+    if (right ? 2 * cx < g.n1x : 2 * cx >= g.n1x) return;
+    if (top ? 2 * cy < g.n1y : 2 * cy >= g.n1y) return;
+    if (!sheet_closed_form(g, fold, cx, cy)) return;                  // block-uniform
+    load_series<P>(g, part, cx, cy, cy0, nchunk, L);
+    __syncthreads();
+    const int pt = p0 + (int)threadIdx.x;
+    if (pt < npts) closed_point<UNIT, P>(g, lx, ly, lm, cell_start, L, cx, cy, cy0, pt, coef);
+}
+
+template <bool UNIT, int P>
+__global__ __launch_bounds__(kThreads) void k_level2_closed(
+    DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
+    const double *__restrict__ lm, const int32_t *__restrict__ cell_start, int32_t cy0,
+    int32_t rows, int32_t nbx, int32_t nby, int32_t nchunk, int32_t fold,
+    const double *__restrict__ part, double *__restrict__ coef)
+{
+    __shared__ double s_L[P][2];
+    closed_block<UNIT, P>(g, lx, ly, lm, cell_start, cy0, rows, blockIdx.x, nbx, nby, nchunk, fold,
+                          part, coef, s_L);
+}
+
 // The level-2 points of four cells, one a lane: the cell expansion by one
-// Horner pass and the ring lenses one by one.  Takes what k_level2_cells does
-// not: CLOSED: the cells whose sheet takes the closed form (a workgroup with
-// none returns at once; its logarithms would otherwise set every point's
-// register budget); STAGED = false: plans with denser rings than kRingCap; and
-// coarse grids of fewer points than that kernel's lanes.
-template <bool UNIT, int P, bool CLOSED, bool STAGED>
+// Horner pass and the ring lenses one by one, for plans with denser rings than
+// kRingCap (STAGED = false) and coarse grids of fewer points than
+// k_level2_cells' lanes; cells whose sheet takes the closed form are
+// k_level2_closed's.
+template <bool UNIT, int P, bool STAGED>
 __global__ __launch_bounds__(kThreads) void k_level2_points(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
     const double *__restrict__ lm, const int32_t *__restrict__ cell_start, int32_t cy0,
@@ -1014,125 +1164,48 @@ __global__ __launch_bounds__(kThreads) void k_level2_points(
     double *__restrict__ coef)
 {
     __shared__ double s_L[kCellsPerBlock][P][2];
-    __shared__ RingLds<UNIT, STAGED> ring;
+    __shared__ RingLds<UNIT> ring;                 // STAGED
     const int tid = threadIdx.x;
     const int32_t cy = cy0 + (int32_t)(blockIdx.x / (uint32_t)nxb);
     const int32_t cx0 = (int32_t)(blockIdx.x % (uint32_t)nxb) * kCellsPerBlock;
-    if constexpr (CLOSED) {                                  // block-uniform
-        bool any = false;
-        for (int w = 0; w < kCellsPerBlock; ++w)
-            any = any || (cx0 + w < g.n1x && sheet_closed_form(g, fold, cx0 + w, cy));
-        if (!any) return;
-    }
-    const double sc = fmax(g.w1, g.h1), isc = 1.0 / sc;
+    const double isc = 1.0 / fmax(g.w1, g.h1);
     const double zci = g.b1 + ((double)cy + 0.5) * g.h1;
-    // sum the chunks' partial expansions, in chunk order
-    for (int e = tid; e < kCellsPerBlock * P * 2; e += kThreads) {
-        const int w = e / (P * 2), n = (e / 2) % P, comp = e % 2;
-        const int32_t ccx = cx0 + w;
-        double acc = 0.0;
-        if (ccx < g.n1x) {
-            const double *src = part + (((int64_t)(cy - cy0) * g.n1x + ccx) * nchunk * P + n) * 2 + comp;
-            for (int k = 0; k < nchunk; ++k) acc += src[(int64_t)k * P * 2];
-        }
-        s_L[w][n][comp] = acc;
-    }
-    stage_ring(ring, g, lx, ly, lm, cell_start, cy, cx0);
-
-    // ---- phase B: the level-2 points of the four cells
+    for (int w = 0; w < kCellsPerBlock; ++w)
+        if (cx0 + w < g.n1x) load_series<P>(g, part, cx0 + w, cy, cy0, nchunk, s_L[w]);
+    if constexpr (STAGED) stage_ring(ring, g, lx, ly, lm, cell_start, cy, cx0);
+    else __syncthreads();
     const int q = g.q, npts = q * q;
     const int64_t nxq = (int64_t)g.n1x * q;
     for (int pp = tid; pp < kCellsPerBlock * npts; pp += kThreads) {
         const int w = pp / npts, pt = pp % npts;
         const int32_t ccx = cx0 + w;
-        if (ccx >= g.n1x || sheet_closed_form(g, fold, ccx, cy) != CLOSED) continue;
+        if (ccx >= g.n1x || sheet_closed_form(g, fold, ccx, cy)) continue;
         const int64_t gx = (int64_t)ccx * q + pt % q;
         const int64_t gyl = pt / q;
         const double x0 = level2_x(g, gx), y0 = level2_y(g, (int64_t)cy * q + gyl);
         const double czr = g.a1 + ((double)ccx + 0.5) * g.w1;
-        const double dr = (x0 - czr) * isc, di = (y0 - zci) * isc;
-        // c_k = s^-(k+1) sum_n C(n,k) Lt_n d^(n-k): the polynomial sum_n Lt_n d^n
-        // and its derivatives over k! by one Horner pass from n = P-1 down
-        // (D_k <- D_k d + D_(k-1), D_0 <- D_0 d + Lt_n)
-        double cr[5] = {0, 0, 0, 0, 0}, ci[5] = {0, 0, 0, 0, 0};
-#pragma unroll
-        for (int n = P - 1; n >= 0; --n) {
-#pragma unroll
-            for (int k = 4; k >= 0; --k) {
-                const double ar = k > 0 ? cr[k - 1] : s_L[w][n][0];
-                const double ai = k > 0 ? ci[k - 1] : s_L[w][n][1];
-                const double nr = fma(cr[k], dr, fma(-ci[k], di, ar));
-                ci[k] = fma(cr[k], di, fma(ci[k], dr, ai));
-                cr[k] = nr;
-            }
-        }
         cplx c[5];
-        double sk = isc;                                  // 1/s^(k+1)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            c[k] = {cr[k] * sk, ci[k] * sk};
-            sk *= isc;
-        }
-        // ring lenses: inside the (2R+1)^2 block, outside the 3 x 3 block
-        auto ring_lens = [&](double X, double Y, double M) {
-            const double wr = x0 - X, wi = y0 - Y;
-            // 1/|w|^2: reciprocal estimate and one Newton step (~2^-48)
-            const double rr = fma(wr, wr, wi * wi);
-            double inv = __builtin_amdgcn_rcp(rr);
-            inv = fma(inv, fma(-rr, inv, 1.0), inv);
-            const cplx u = {wr * inv, -wi * inv};
-            cplx t1 = UNIT ? u : cplx{M * u.r, M * u.i};
-            c[0].r += t1.r; c[0].i += t1.i;
-            cplx t2 = cmul(t1, u);
-            c[1].r -= t2.r; c[1].i -= t2.i;
-            cplx t3 = cmul(t2, u);
-            c[2].r += t3.r; c[2].i += t3.i;
-            cplx t4 = cmul(t3, u);
-            c[3].r -= t4.r; c[3].i -= t4.i;
-            cplx t5 = cmul(t4, u);
-            c[4].r += t5.r; c[4].i += t5.i;
-        };
+        cell_series<P>(s_L[w], (x0 - czr) * isc, (y0 - zci) * isc, isc, c);
         if constexpr (STAGED) {
             for (int sg = 0; sg < kRingSegs; ++sg) {
                 const int2 be = ring.seg[w][sg];
                 for (int32_t pl = be.x; pl < be.y; ++pl)
-                    ring_lens(ring.rx[pl], ring.ry[pl], UNIT ? 1.0 : ring.rm[pl]);
+                    add_ring_lens<UNIT>(x0 - ring.rx[pl], y0 - ring.ry[pl], UNIT ? 1.0 : ring.rm[pl], c);
             }
         } else {
-            for (int32_t row = ring.ya; row <= ring.yb; ++row) {
-                const bool mid = abs(row - cy) <= 1;
-                for (int seg = 0; seg < (mid ? 2 : 1); ++seg) {
-                    int32_t xa, xb;
-                    if (!mid) { xa = ccx - kRing; xb = ccx + kRing; }
-                    else if (seg == 0) { xa = ccx - kRing; xb = ccx - 2; }
-                    else { xa = ccx + 2; xb = ccx + kRing; }
-                    xa = max(xa, 0);
-                    xb = min(xb, g.n1x - 1);
-                    if (xa > xb) continue;
-                    const int r = row - ring.ya;
-                    const int32_t pb = ring.cs[r][xa - ring.ua], pe = ring.cs[r][xb + 1 - ring.ua];
-                    for (int32_t pl = pb; pl < pe; ++pl) ring_lens(lx[pl], ly[pl], UNIT ? 1.0 : lm[pl]);
-                }
-            }
+            ring_runs(g, cell_start, ccx, cy, [&](int32_t pb, int32_t pe) {
+                for (int32_t pl = pb; pl < pe; ++pl)
+                    add_ring_lens<UNIT>(x0 - lx[pl], y0 - ly[pl], UNIT ? 1.0 : lm[pl], c);
+            });
         }
         if (g.sheet && !corner_cell(g, ccx, cy)) {
-            if constexpr (!CLOSED) {
-                // G's series came with the cell expansion; F = conj(z) + G
-                c[0].r -= g.kappa_star * x0;
-                c[0].i += g.kappa_star * y0;
-            } else {
-                cplx sh[5];
-                sheet_coeffs(g, x0, y0, sh);
-#pragma unroll
-                for (int o = 0; o < 5; ++o) { c[o].r += sh[o].r; c[o].i += sh[o].i; }
-            }
+            // G's series came with the cell expansion; F = conj(z) + G
+            c[0].r -= g.kappa_star * x0;
+            c[0].i += g.kappa_star * y0;
         }
-        double *dst = coef + (((int64_t)(cy - cy0) * q + gyl) * nxq + gx) * 10;
+        double2 *dst = (double2 *)(coef + (((int64_t)(cy - cy0) * q + gyl) * nxq + gx) * 10);
 #pragma unroll
-        for (int o = 0; o < 5; ++o) {
-            dst[2 * o] = c[o].r;
-            dst[2 * o + 1] = c[o].i;
-        }
+        for (int o = 0; o < 5; ++o) dst[o] = make_double2(c[o].r, c[o].i);
     }
 }
 
@@ -1171,17 +1244,25 @@ template <bool UNIT, int P>
 __global__ __launch_bounds__(kThreads, 3) void k_level2_cells(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
     const double *__restrict__ lm, const int32_t *__restrict__ cell_start, int32_t cy0,
-    int32_t nxb, int32_t nchunk, int32_t fold, int32_t pe, const double *__restrict__ part,
-    double *__restrict__ coef)
+    int32_t nxb, int32_t rows, int32_t nbx, int32_t nby, int32_t nchunk, int32_t fold, int32_t pe,
+    const double *__restrict__ part, double *__restrict__ coef)
 {
-    __shared__ RingLds<UNIT, true> ring;
+    __shared__ RingLds<UNIT> ring;
     __shared__ uint16_t s_idx[kCellsPerBlock][kRingCap];              // a cell's ring lenses
     __shared__ double2 s_pow[kCellsPerBlock][kRingStep][16 + 1];      // m u (-u)^j, j < 16; (-u)^16
     __shared__ double2 s_A[kCellsPerBlock][kPEMax + 4];
     const int lane = threadIdx.x % kWave;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int32_t cy = cy0 + (int32_t)(blockIdx.x / (uint32_t)nxb);
-    const int32_t cx0 = (int32_t)(blockIdx.x % (uint32_t)nxb) * kCellsPerBlock;
+    // the first workgroups take the cells with the sheet's closed form, whose
+    // logarithms last longest
+    const uint32_t nclosed = gridDim.x - (uint32_t)(nxb * rows);
+    if (blockIdx.x < nclosed) {
+        closed_block<UNIT, P>(g, lx, ly, lm, cell_start, cy0, rows, blockIdx.x, nbx, nby, nchunk,
+                              fold, part, coef, reinterpret_cast<double (*)[2]>(&s_A[0][0]));
+        return;
+    }
+    const int32_t cy = cy0 + (int32_t)((blockIdx.x - nclosed) / (uint32_t)nxb);
+    const int32_t cx0 = (int32_t)((blockIdx.x - nclosed) % (uint32_t)nxb) * kCellsPerBlock;
     stage_ring(ring, g, lx, ly, lm, cell_start, cy, cx0);
     const int32_t cx = cx0 + w;
     if (cx >= g.n1x || sheet_closed_form(g, fold, cx, cy)) return;    // wave-uniform; no barrier below
@@ -2363,6 +2444,19 @@ bool ring_fits(irs_plan_s *p)
     return p->ring_fit == 1;
 }
 
+// Cells at each corner of the rectangle among which those with the sheet's
+// closed form lie (sheet_fold_ok fails where the cell's centre is nearer than
+// five half diagonals to the corner; without folding, the whole quarter).
+void closed_extent(const DevGeom &g, int32_t fold, int32_t &nbx, int32_t &nby)
+{
+    nbx = (g.n1x + 1) / 2;
+    nby = (g.n1y + 1) / 2;
+    if (!fold || g.sheet != 1) return;
+    const double reach = 2.5 * std::sqrt(g.w1 * g.w1 + g.h1 * g.h1);
+    nbx = std::min<int32_t>(nbx, (int32_t)std::min(1e9, std::ceil(reach / g.w1 + 0.5) + 1.0));
+    nby = std::min<int32_t>(nby, (int32_t)std::min(1e9, std::ceil(reach / g.h1 + 0.5) + 1.0));
+}
+
 // Terms of the cell expansions with the ring lenses (k_level2_cells): the order
 // rule of level2_order at the ratio of the furthest level-2 point from the
 // cell's centre to the nearest lens outside the 3 x 3 block; 0: the ring lenses
@@ -2878,6 +2972,12 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
         // from the super-cell path (launch_level2_expand folds it)
         const int32_t fold = super_order(p) > 0 ? 1 : 0;
         const int32_t pe = ring_order(p);
+        // the cells with the sheet's closed form: workgroups of 256 points over
+        // nbx x nby cells at each corner
+        const int32_t rows = (int32_t)(c1 - c0 + 1);
+        int32_t nbx = 0, nby = 0;
+        if (g.sheet) closed_extent(g, fold, nbx, nby);
+        const unsigned nbC = (unsigned)((int64_t)4 * nbx * nby * ((q * q + kThreads - 1) / kThreads));
         const unsigned nbB = (unsigned)((c1 - c0 + 1) * nxb);
         irs_status st3 = launch_level2_expand(p, c0, c1, cs, true);
         if (st3 != IRS_OK) return st3;
@@ -2886,21 +2986,21 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
         if (cs && (st2 = cs->end(s)) != IRS_OK) return st2;                                  \
         if (cs && (st2 = cs->begin(s, 2)) != IRS_OK) return st2;                             \
         if (pe > 0)                                                                           \
-            hipLaunchKernelGGL((k_level2_cells<U, PP>), dim3(nbB), dim3(kThreads), 0, s, g,     \
-                               p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, nxb,      \
-                               nchunk, fold, pe, p->d_part, coef);                           \
+            hipLaunchKernelGGL((k_level2_cells<U, PP>), dim3(nbB + nbC), dim3(kThreads), 0, s, g, \
+                               p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, nxb, rows, \
+                               nbx, nby, nchunk, fold, pe, p->d_part, coef);                 \
         else if (ring_fits(p))                                                                \
-            hipLaunchKernelGGL((k_level2_points<U, PP, false, true>), dim3(nbB), dim3(kThreads), \
-                               0, s, g, p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, \
-                               nxb, nchunk, fold, p->d_part, coef);                          \
+            hipLaunchKernelGGL((k_level2_points<U, PP, true>), dim3(nbB), dim3(kThreads), 0, s, g, \
+                               p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, nxb,     \
+                               nchunk, fold, p->d_part, coef);                               \
         else                                                                                  \
-            hipLaunchKernelGGL((k_level2_points<U, PP, false, false>), dim3(nbB), dim3(kThreads), \
-                               0, s, g, p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, \
-                               nxb, nchunk, fold, p->d_part, coef);                          \
-        if (g.sheet)                                                                          \
-            hipLaunchKernelGGL((k_level2_points<U, PP, true, false>), dim3(nbB), dim3(kThreads), 0, \
-                               s, g, p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0,    \
-                               nxb, nchunk, fold, p->d_part, coef);                          \
+            hipLaunchKernelGGL((k_level2_points<U, PP, false>), dim3(nbB), dim3(kThreads), 0, s, g, \
+                               p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, nxb,     \
+                               nchunk, fold, p->d_part, coef);                               \
+        if (pe <= 0 && nbC > 0)                                                               \
+            hipLaunchKernelGGL((k_level2_closed<U, PP>), dim3(nbC), dim3(kThreads), 0, s, g,  \
+                               p->d_x, p->d_y, p->d_m, p->d_cell_start, (int32_t)c0, rows,   \
+                               nbx, nby, nchunk, fold, p->d_part, coef);                     \
     } while (0)
         irs_status st2 = IRS_OK;
         if (p->unit_mass) {
