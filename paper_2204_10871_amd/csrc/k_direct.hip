@@ -6,14 +6,15 @@
 // N_rays * N_* (Eq. 12).
 //
 // Two kernels:
-//   k_direct_f64  -- plain double precision, one ray per lane, lens tiles in LDS.
-//   k_direct_f32  -- the FP32 VALU-bound form: each workgroup owns a compact
-//                    64 x 32 tile of rays; ray-lens offsets are rounded to
-//                    FP32 once from their FP64 values (d1 per column and
-//                    lens, d2 per row and lens through LDS), eight rays per
-//                    lane share every d1, and each ray's sum is compensated:
-//                    32 lenses are summed plainly, then added with Kahan's
-//                    correction.  The lenses
+//   k_direct_f64  -- plain double precision, one ray per lane or four, lens tiles
+//                    in LDS.
+//   k_direct_f32  -- the FP32 VALU-bound form: each wave owns 64 columns of up
+//                    to eight ray rows (four or sixteen in the other shapes);
+//                    ray-lens offsets are rounded to FP32 once from their FP64
+//                    values (d1 per column and lens, d2 per row and lens
+//                    through LDS), the lane's rays share every d1, and each
+//                    ray's sum is compensated: 32 lenses are summed plainly,
+//                    then added with Kahan's correction.  The lenses
 //                    of the 3 x 3 level-1 cells around the ray are then
 //                    re-evaluated in FP64 and the difference to their FP32
 //                    terms is added (FP32 quantisation of a lens at distance d
@@ -357,37 +358,119 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float x)
 
 }  // namespace
 
-// The FP32 tile: RPT ray rows per lane (RPT * 4 rows per tile), LT lenses per
-// LDS stage.  Every shape computes each ray with the same operations in the
-// same order (LT is a multiple of kChunk), so all shapes give identical bits.
+// The FP32 tile, bound by its arithmetic (five FMAs and a reciprocal per ray and
+// lens, 29 cycles a wave; 4e6 rays and 1e5 lenses: 74.7 ms, 74.3 by that count
+// at 2.4 GHz).  A wave takes up to RPT ray rows of 64 columns, a workgroup's
+// four waves share stages of LT lenses in LDS.  Every shape and every number of
+// rows computes each ray with the same operations in the same order (LT is a
+// multiple of kChunk), so all of them give identical bits.
 template <bool UNIT, int RPT, int LT>
 struct DirectTile {
     static constexpr int TY = RPT * kWaves;
+    // row counts the lens loop is compiled for: 1 to RPT, in steps for RPT > 8
+    static constexpr int STEP = RPT > 8 ? RPT / 8 : 1;
     struct Smem {
         double X[LT], Y[LT];
         float4 m4[UNIT ? 1 : LT / 4];
-        float4 d24[TY][LT / 4];          // d2 per (tile row, lens)
+        float4 d24[TY][LT / 4];          // d2 per (row, lens), each wave its own RPT rows
+    };
+    struct Acc {
+        float in1[RPT], in2[RPT], s1[RPT], c1[RPT], s2[RPT], c2[RPT];
     };
 
-    __device__ static void run(Smem &sm, const DirectArgs &a, int64_t tx, int64_t ty)
+    // one stage's lenses into R rows
+    template <int R>
+    __device__ __forceinline__ static void stage(const Smem &sm, const float4 (*d24)[LT / 4],
+                                                 double t1, int cnt, Acc &A)
+    {
+        const float *s_m = reinterpret_cast<const float *>(sm.m4);
+        const int full = cnt - cnt % kChunk;
+        for (int c = 0; c < full; c += kChunk) {
+#pragma unroll 2
+            for (int t = 0; t < kChunk; t += 4) {
+                float d1[4], d1sq[4], ms[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    d1[u] = (float)(t1 - sm.X[c + t + u]);
+                    d1sq[u] = fmaf(d1[u], d1[u], kTiny);
+                    ms[u] = UNIT ? 1.0f : s_m[c + t + u];
+                }
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    const float4 D = d24[k][(c + t) / 4];
+                    const float d2s[4] = {D.x, D.y, D.z, D.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        float w = inv_r2(d1sq[u], d2s[u]);
+                        if (!UNIT) w = ms[u] * w;
+                        A.in1[k] = fmaf(d1[u], w, A.in1[k]);
+                        A.in2[k] = fmaf(d2s[u], w, A.in2[k]);
+                    }
+                }
+            }
+            fold<R>(A);
+        }
+        if (full < cnt) {
+            for (int t = full; t < cnt; ++t) {
+                const float d1 = (float)(t1 - sm.X[t]);
+                const float d1sq = fmaf(d1, d1, kTiny);
+                const float m = UNIT ? 1.0f : s_m[t];
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    const float d2 = reinterpret_cast<const float *>(d24[k])[t];
+                    float w = inv_r2(d1sq, d2);
+                    if (!UNIT) w = m * w;
+                    A.in1[k] = fmaf(d1, w, A.in1[k]);
+                    A.in2[k] = fmaf(d2, w, A.in2[k]);
+                }
+            }
+            fold<R>(A);
+        }
+    }
+
+    template <int R>
+    __device__ __forceinline__ static void fold(Acc &A)
+    {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            kahan_add(A.s1[k], A.c1[k], A.in1[k]);
+            kahan_add(A.s2[k], A.c2[k], A.in2[k]);
+            A.in1[k] = A.in2[k] = 0.0f;
+        }
+    }
+
+    // the smallest compiled count that holds nr rows (nr is the wave's)
+    template <int R>
+    __device__ __forceinline__ static void stage_rows(int nr, const Smem &sm,
+                                                      const float4 (*d24)[LT / 4], double t1,
+                                                      int cnt, Acc &A)
+    {
+        if constexpr (R > STEP) {
+            if (nr <= R - STEP) {
+                stage_rows<R - STEP>(nr, sm, d24, t1, cnt, A);
+                return;
+            }
+        }
+        stage<R>(sm, d24, t1, cnt, A);
+    }
+
+    // rays of columns 64 tx .. and rows j0 .. j0 + nr - 1, tx, j0 and nr <= RPT
+    // the calling wave's own; all waves of the workgroup call it
+    __device__ static void run(Smem &sm, const DirectArgs &a, int64_t tx, int64_t j0, int nr)
     {
         const DevGeom &g = a.g;
-        {
-            // skip a tile none of whose rays is asked for (block-uniform)
-            const int64_t jA = max(ty * TY, a.row0), jB = min(ty * TY + TY - 1, a.row1 - 1);
-            const int64_t iA = tx * kTX, iB = min(tx * kTX + kTX - 1, g.nx - 1);
-            if (jA > jB || jB * g.nx + iB < a.ray_first || jA * g.nx + iA >= a.ray_last) return;
-        }
         float *s_m = reinterpret_cast<float *>(sm.m4);
         const int tid = threadIdx.x;
         const int lane = tid % kWave, wave = tid / kWave;
         const int64_t i = tx * kTX + lane;
         const double t1 = ray_x(g, i);
         const int32_t nl = a.nl;
+        float4(*d24)[LT / 4] = sm.d24 + wave * RPT;
 
-        float in1[RPT], in2[RPT], s1[RPT], c1[RPT], s2[RPT], c2[RPT];
+        Acc A;
 #pragma unroll
-        for (int k = 0; k < RPT; ++k) in1[k] = in2[k] = s1[k] = c1[k] = s2[k] = c2[k] = 0.0f;
+        for (int k = 0; k < RPT; ++k)
+            A.in1[k] = A.in2[k] = A.s1[k] = A.c1[k] = A.s2[k] = A.c2[k] = 0.0f;
 
         for (int32_t base = 0; base < nl; base += LT) {
             __syncthreads();
@@ -401,81 +484,31 @@ struct DirectTile {
             }
             __syncthreads();
             const int cnt = min(LT, nl - base);
-            for (int e = tid; e < TY * LT; e += kThreads) {
-                const int row = e / LT, t = e % LT;
-                if (t < cnt) {
-                    const double t2r = ray_y(g, ty * TY + row);
-                    reinterpret_cast<float *>(sm.d24[row])[t] = (float)(t2r - sm.Y[t]);
-                }
+            for (int k = 0; k < nr; ++k) {
+                const double t2r = ray_y(g, j0 + k);
+                for (int t = lane; t < cnt; t += kWave)
+                    reinterpret_cast<float *>(d24[k])[t] = (float)(t2r - sm.Y[t]);
             }
-            __syncthreads();
-            const int full = cnt - cnt % kChunk;
-            for (int c = 0; c < full; c += kChunk) {
-#pragma unroll 2
-                for (int t = 0; t < kChunk; t += 4) {
-                    float d1[4], d1sq[4], ms[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        d1[u] = (float)(t1 - sm.X[c + t + u]);
-                        d1sq[u] = fmaf(d1[u], d1[u], kTiny);
-                        ms[u] = UNIT ? 1.0f : s_m[c + t + u];
-                    }
-#pragma unroll
-                    for (int k = 0; k < RPT; ++k) {
-                        const float4 D = sm.d24[wave * RPT + k][(c + t) / 4];
-                        const float d2s[4] = {D.x, D.y, D.z, D.w};
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            float w = inv_r2(d1sq[u], d2s[u]);
-                            if (!UNIT) w = ms[u] * w;
-                            in1[k] = fmaf(d1[u], w, in1[k]);
-                            in2[k] = fmaf(d2s[u], w, in2[k]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < RPT; ++k) {
-                    kahan_add(s1[k], c1[k], in1[k]);
-                    kahan_add(s2[k], c2[k], in2[k]);
-                    in1[k] = in2[k] = 0.0f;
-                }
-            }
-            if (full < cnt) {
-                for (int t = full; t < cnt; ++t) {
-                    const float d1 = (float)(t1 - sm.X[t]);
-                    const float d1sq = fmaf(d1, d1, kTiny);
-                    const float m = UNIT ? 1.0f : s_m[t];
-#pragma unroll
-                    for (int k = 0; k < RPT; ++k) {
-                        const float d2 = reinterpret_cast<const float *>(sm.d24[wave * RPT + k])[t];
-                        float w = inv_r2(d1sq, d2);
-                        if (!UNIT) w = m * w;
-                        in1[k] = fmaf(d1, w, in1[k]);
-                        in2[k] = fmaf(d2, w, in2[k]);
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < RPT; ++k) {
-                    kahan_add(s1[k], c1[k], in1[k]);
-                    kahan_add(s2[k], c2[k], in2[k]);
-                    in1[k] = in2[k] = 0.0f;
-                }
-            }
+            // the wave's own rows: its LDS writes before its reads
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (nr > 0) stage_rows<RPT>(nr, sm, d24, t1, cnt, A);
         }
 
-        // FP64 near-lens residual, assembly and output, ray by ray
+        // FP64 near-lens residual, assembly and output, ray by ray; one body,
+        // with the next row's sums moved to index 0 after each
         const int64_t cx = ((2 * i + 1) * (int64_t)g.n1x) / (2 * g.nx);
         const int64_t cxl = cx > 0 ? cx - 1 : 0;
         const int64_t cxh = cx < g.n1x - 1 ? cx + 1 : g.n1x - 1;
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
-            const int64_t j = ty * TY + wave * RPT + k;
+#pragma unroll 1
+        for (int k = 0; k < nr; ++k) {
+            const int64_t j = j0 + k;
             const int64_t r = j * g.nx + i;
             const bool valid = i < g.nx && j >= a.row0 && j < a.row1 && r >= a.ray_first &&
                                r < a.ray_last;
             const double t2 = ray_y(g, j);
-            double sum1 = (double)s1[k] - (double)c1[k];
-            double sum2 = (double)s2[k] - (double)c2[k];
+            double sum1 = (double)A.s1[0] - (double)A.c1[0];
+            double sum2 = (double)A.s2[0] - (double)A.c2[0];
             if (valid) {
                 const int64_t cy = ((2 * j + 1) * (int64_t)g.n1y) / (2 * g.ny);
                 const int64_t cyl = cy > 0 ? cy - 1 : 0;
@@ -507,18 +540,86 @@ struct DirectTile {
             int32_t pix;
             assemble(g, t1, t2, sum1, sum2, a1, a2, pix);
             emit(valid, r - a.ray_first, a1, a2, pix, a.a1o, a.a2o, a.pixo, a.counts, a.landed);
+#pragma unroll
+            for (int h = 0; h + 1 < RPT; ++h) {
+                A.s1[h] = A.s1[h + 1];
+                A.c1[h] = A.c1[h + 1];
+                A.s2[h] = A.s2[h + 1];
+                A.c2[h] = A.c2[h + 1];
+            }
         }
     }
 };
 
+// One launch's rays as pieces, one per wave: tile columns of 64 rays, `split`
+// of them cut into p + 1 runs of rows and the others into p, each column as
+// evenly as its rows allow, so the runs of a column differ by one row at most.
+// The longer runs come first, which leaves the SIMDs that get the grid's waves
+// in turn about equally loaded.
+struct DirectSplit {
+    int64_t tx0, ntx;                    // tile columns
+    int64_t j0;                          // first row
+    int32_t rows;
+    int32_t p;
+    int64_t split;
+    int64_t end[4];                      // ends of the classes: long runs of the columns
+                                         // with p and p + 1, then their short runs
+};
+
 namespace {
 
+// waves per SIMD of a tile with RPT rows a wave: what its registers and LDS allow
+constexpr int direct_waves(int64_t rpt) { return rpt == 8 ? 4 : rpt < 8 ? 3 : 2; }
+// Pieces per SIMD and round, on 1024 SIMDs.  Whole tiles of 32 rows leave a last
+// round nearly empty (1067 workgroups of three a compute unit: 53.2 ms for 2e6
+// rays and 1e5 lenses; 39.6 ms in equal pieces; 560: 1575 against 1033 us for
+// 1e6 rays and 4450 lenses).  Six a SIMD where four are resident: the pieces
+// that start later keep the SIMD busy while the first ones stage and end
+// (four: 40.6 ms and 1130 us; 1e6 rays, 1e5 lenses: 20.9 against 22.0 ms).
+constexpr int64_t direct_round(int64_t rpt) { return 1024 * (rpt == 8 ? 6 : rpt < 8 ? 3 : 2); }
+
+DirectSplit direct_split(int64_t tx0, int64_t ntx, int64_t j0, int64_t rows, int64_t rpt)
+{
+    const int64_t round = direct_round(rpt);
+    // the least number of pieces in whole rounds, of one row at least
+    const int64_t need = ntx * ((rows + rpt - 1) / rpt);
+    int64_t total = (need + round - 1) / round * round;
+    total = std::min(total, ntx * rows);
+    DirectSplit d{};
+    d.tx0 = tx0;
+    d.ntx = ntx;
+    d.j0 = j0;
+    d.rows = (int32_t)rows;
+    d.p = (int32_t)(total / ntx);
+    d.split = d.p < rows ? total % ntx : 0;
+    const int64_t np[2] = {d.p, d.p + 1}, nc[2] = {ntx - d.split, d.split};
+    int64_t e = 0;
+    for (int c = 0; c < 2; ++c) d.end[c] = e += nc[c] * (rows % np[c]);
+    for (int c = 0; c < 2; ++c) d.end[2 + c] = e += nc[c] * (np[c] - rows % np[c]);
+    return d;
+}
+
 template <bool UNIT, int RPT, int LT>
-__global__ __launch_bounds__(kThreads) void k_direct_f32(DirectArgs a, int64_t ntx, int64_t ty0)
+__global__ __launch_bounds__(kThreads, direct_waves(RPT)) void k_direct_f32(DirectArgs a, DirectSplit d)
 {
     using T = DirectTile<UNIT, RPT, LT>;
     __shared__ typename T::Smem sm;
-    T::run(sm, a, (int64_t)blockIdx.x % ntx, ty0 + (int64_t)blockIdx.x / ntx);
+    const int64_t w = (int64_t)blockIdx.x * kWaves +
+                      __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int64_t tx = d.tx0, j0 = d.j0;
+    int nr = 0;
+    if (w < d.end[3]) {
+        const int c = w < d.end[0] ? 0 : w < d.end[1] ? 1 : w < d.end[2] ? 2 : 3;
+        const int32_t np = d.p + (c & 1);
+        const int32_t len = d.rows / np, nlong = d.rows % np;
+        const uint32_t v = (uint32_t)(w - (c ? d.end[c - 1] : 0));
+        const uint32_t per = (uint32_t)(c < 2 ? nlong : np - nlong);
+        const uint32_t col = v / per, q = v - col * per;
+        tx += col + ((c & 1) ? 0 : d.split);
+        nr = len + (c < 2);
+        j0 += c < 2 ? (int64_t)q * nr : (int64_t)nlong * (len + 1) + (int64_t)q * len;
+    }
+    T::run(sm, a, tx, j0, nr);
 }
 
 // Persistent form for batches: workgroups pull (map, tile) items from a
@@ -526,7 +627,7 @@ __global__ __launch_bounds__(kThreads) void k_direct_f32(DirectArgs a, int64_t n
 // order the host chose (longest-processing-time first); item_start[m] is the
 // first item of map m and item_start[nmaps] the total.
 template <bool UNIT, int RPT, int LT>
-__global__ __launch_bounds__(kThreads) void k_direct_f32_queue(
+__global__ __launch_bounds__(kThreads, direct_waves(RPT)) void k_direct_f32_queue(
     const DirectArgs *__restrict__ maps, const int64_t *__restrict__ item_start, int32_t nmaps,
     unsigned long long *cursor)
 {
@@ -548,7 +649,10 @@ __global__ __launch_bounds__(kThreads) void k_direct_f32_queue(
         }
         const DirectArgs &a = maps[lo];
         const int64_t t = item - item_start[lo];
-        T::run(sm, a, t % a.ntx, a.ty0 + t / a.ntx);
+        const int64_t j0 = (t / a.ntx) * T::TY +
+                           RPT * __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        T::run(sm, a, t % a.ntx, j0,
+               (int)max((int64_t)0, min((int64_t)RPT, a.row1 - j0)));
     }
 }
 
@@ -602,11 +706,18 @@ irs_status launch_direct(irs_plan_s *p, const RaySel &sel)
     }
 
     const int v = p->direct_variant;
-    const int64_t TY = direct_variant_rows(v);
-    const int64_t ntx = (g.nx + kTX - 1) / kTX;
-    const int64_t ty_lo = sel.row0 / TY;
-    const int64_t ty_hi = (sel.row1 - 1) / TY;          // inclusive
-    const int64_t max_rows_of_tiles = std::max<int64_t>(1, ((int64_t)1 << 22) / ntx);
+    const int64_t rpt = direct_variant_rows(v) / kWaves;
+    // rows that hold rays asked for, and the columns if it is one row
+    const int64_t jA = std::max(sel.row0, sel.ray_first / g.nx);
+    const int64_t jB = std::min(sel.row1, (sel.ray_last + g.nx - 1) / g.nx);
+    if (jB <= jA || sel.ray_last <= sel.ray_first) return IRS_OK;
+    int64_t tx0 = 0, tx1 = (g.nx + kTX - 1) / kTX;
+    if (jB - jA == 1) {
+        tx0 = std::max<int64_t>(0, sel.ray_first - jA * g.nx) / kTX;
+        tx1 = (std::min(g.nx, sel.ray_last - jA * g.nx) + kTX - 1) / kTX;
+    }
+    const int64_t ntx = tx1 - tx0;
+    const int64_t max_rows = std::max<int64_t>(1, ((int64_t)1 << 22) / ntx) * rpt * kWaves;
     if (sel.stats) {
         const int64_t r0 = std::max(sel.row0 * g.nx, sel.ray_first);
         const int64_t r1 = std::min(sel.row1 * g.nx, sel.ray_last);
@@ -629,15 +740,15 @@ irs_status launch_direct(irs_plan_s *p, const RaySel &sel)
     a.pixo = sel.pixel;
     a.counts = sel.counts;
     a.landed = sel.landed;
-    for (int64_t t0 = ty_lo; t0 <= ty_hi; t0 += max_rows_of_tiles) {
-        const int64_t t1 = std::min(ty_hi + 1, t0 + max_rows_of_tiles);
-        const unsigned nb = (unsigned)((t1 - t0) * ntx);
+    for (int64_t j0 = jA; j0 < jB; j0 += max_rows) {
+        const DirectSplit d = direct_split(tx0, ntx, j0, std::min(max_rows, jB - j0), rpt);
+        const unsigned nb = (unsigned)((d.end[3] + kWaves - 1) / kWaves);
         if (sel.stats) {
             irs_status st = sel.stats->begin(s, 1);
             if (st != IRS_OK) return st;
             sel.stats->n_rays++;
         }
-#define IRS_DF32(U, R, L) hipLaunchKernelGGL((k_direct_f32<U, R, L>), dim3(nb), dim3(kThreads), 0, s, a, ntx, t0)
+#define IRS_DF32(U, R, L) hipLaunchKernelGGL((k_direct_f32<U, R, L>), dim3(nb), dim3(kThreads), 0, s, a, d)
         if (unit) {
             if (v == 0) IRS_DF32(true, 4, 512);
             else if (v == 1) IRS_DF32(true, 8, 256);
