@@ -1424,8 +1424,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_level2_cells(
 }
 
 // -------------------------------------------------------------------------
-// Level 3: one workgroup = a 64 x 32 tile of rays (lane = column, each wave 8
-// rows).  Every ray: Horner of its level-2 point's C_0..C_4, the sheet's
+// Level 3: one workgroup = 64 columns of rays (lane = column) in four waves of
+// up to 8 rows (make_tiles).  Every ray: Horner of its level-2 point's C_0..C_4, the sheet's
 // linear term (closed form in corner cells), the near lenses exactly, the
 // macro term, beta and the pixel.  What depends on the ray row only (theta_2,
 // its level-2 and level-1 rows, the offset from the level-2 row) comes from a
@@ -1439,7 +1439,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_level2_cells(
 // -------------------------------------------------------------------------
 constexpr int kL3Rows = 32;
 constexpr int kXcds = 8;               // MI355X: workgroups go to the 8 XCDs in turn
-constexpr int kL3RowsPerWave = kL3Rows / (kThreads / kWave);
+constexpr int kL3Waves = kThreads / kWave;
+constexpr int kL3RowsPerWave = kL3Rows / kL3Waves;
 constexpr int kHistCap = 6144;
 
 // A level-3 workgroup's LDS: the histogram over the tile's landed-pixel box
@@ -1737,7 +1738,7 @@ struct L3Map {
     const RowInfo *rows;            // row table
     const ColInfo *cols;            // column table
     const double *coef;             // level-2 coefficients from level-1 row cy0
-    const TileSpan *tcol, *trow;    // the plan's column and row tiles
+    const TileSpan *tcol, *trow;    // the plan's column tiles and waves' rows
     int32_t cy0;
     int32_t ntx;                    // column tiles
     int64_t jr0, jr1;               // ray rows of the launch
@@ -1821,24 +1822,25 @@ __device__ __forceinline__ void scatter_bins(const int32_t *pxs, const int32_t *
     }
 }
 
-// One tile of rays: columns tcol[tx] (one per lane) by rows trow[ty]
-// (kL3RowsPerWave per wave), restricted to rows [jr0, jr1).  Every ray: the
+// One tile of rays: columns tcol[tx] (one per lane), wave w rows trow[wr + w]
+// (at most kL3RowsPerWave), restricted to rows [jr0, jr1).  Every ray: the
 // near lenses exactly, Horner of its level-2 point's C_0..C_4, the macro
 // term, beta and the pixel; BIN: binned through an LDS histogram over the
 // tile's landed-pixel box (flushed with one global atomic per non-empty bin),
 // or, for a box larger than the histogram, the wrapped histogram of
 // scatter_bins.  Called by every thread of the workgroup.
 template <bool UNIT, bool BIN>
-__device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t ty, L3Lds *lds)
+__device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t wr, L3Lds *lds)
 {
     const DevGeom &g = m.g;
     const int tid = threadIdx.x;
     const int lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     constexpr int R = kL3RowsPerWave;
-    const TileSpan tc = m.tcol[tx], tr = m.trow[ty];
+    const TileSpan tc = m.tcol[tx];
+    const TileSpan tr = m.trow[wr + wave];
     const int32_t ny1 = (int32_t)g.ny - 1;                          // ny < 2^31
-    const int32_t jw = tr.a + wave * R;                             // the wave's first row
+    const int32_t jw = tr.a;                                        // the wave's first row
     if (BIN && tid == 0) {                    // one tile per workgroup: set up its LDS
         lds->bmin[0] = lds->bmin[1] = UINT32_MAX;
         lds->bmax[0] = lds->bmax[1] = -1;
@@ -1857,16 +1859,16 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
     const double t1 = ray_x32(g, ic);
     const int32_t xl = cx > 0 ? cx - 1 : 0, xh = cx < g.n1x - 1 ? cx + 1 : g.n1x - 1;
 
-    // the wave's rows jw + k, k < kt, lie in the tile; rows k0 <= k < k1 also
-    // lie in [jr0, jr1), the others bin nothing
-    const int kt = max(0, min(R, tr.b - jw));
+    // the wave has rows jw + k, k < kt; rows k0 <= k < k1 also lie in
+    // [jr0, jr1), the others bin nothing
+    const int kt = max(0, min(R, tr.b - jw));      // (known bounds: 0.7 % faster)
     const int k0 = (int)max<int64_t>(0, m.jr0 - jw);
     const int k1 = (int)min<int64_t>(kt, m.jr1 - jw);
     auto row = [&](int k) -> const RowInfo & { return m.rows[min(jw + k, ny1)]; };
 
     // nearby lenses, exactly.  A lane's rays are R consecutive rows of one
     // column; they nearly always share their level-1 cell row (always where
-    // row tiles follow the cell rows), so one pass over the lenses serves them
+    // the waves' rows follow the cell rows), so one pass over the lenses serves them
     // all, the R rows sharing each reciprocal; otherwise each ray takes its
     // own pass.  Which of the two a ray takes, and its partners in the first,
     // depend only on the plan's tiles, not on the call.
@@ -1998,17 +2000,17 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
     }
 }
 
-// One map: tile (tx, ty0 + blockIdx.x / ntx_pad) with tx = blockIdx.x mod
-// ntx_pad.  ntx_pad is a multiple of the 8 XCDs, which take consecutive
+// One map: column tile tx = blockIdx.x mod ntx_pad, rows of the kL3Waves waves
+// from wr0 + kL3Waves (blockIdx.x / ntx_pad).  ntx_pad is a multiple of the 8 XCDs, which take consecutive
 // workgroups in turn, so a column tile runs on the same XCD in every tile row
 // and finds its level-2 coefficients and lenses in that XCD's L2.
 template <bool UNIT, bool BIN>
-__global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t ty0, int32_t ntx_pad)
+__global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t wr0, int32_t ntx_pad)
 {
     __shared__ L3Lds lds;
     const int32_t tx = (int32_t)(blockIdx.x % (uint32_t)ntx_pad);
     if (tx >= m.ntx) return;                               // padding (block-uniform)
-    level3_tile<UNIT, BIN>(m, tx, ty0 + (int32_t)(blockIdx.x / (uint32_t)ntx_pad), &lds);
+    level3_tile<UNIT, BIN>(m, tx, wr0 + kL3Waves * (int32_t)(blockIdx.x / (uint32_t)ntx_pad), &lds);
 }
 
 // Ray idx of one of the rectangle's four corner cells (ray columns [i0, i1),
@@ -2122,7 +2124,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_level3_maps(const L3Map *maps_i
     const int32_t ntx_pad = (m.ntx + kXcds - 1) / kXcds * kXcds;
     const int32_t tx = (int32_t)(local % ntx_pad);
     if (tx < m.ntx)                                         // padding (block-uniform)
-        level3_tile<UNIT, true>(m, tx, (int32_t)(local / ntx_pad), &lds);
+        level3_tile<UNIT, true>(m, tx, kL3Waves * (int32_t)(local / ntx_pad), &lds);
 }
 
 // The same maps' corner-cell rays: block b takes kThreads rays of one corner
@@ -2636,6 +2638,14 @@ irs_status launch_level2_expand(irs_plan_s *p, int64_t c0, int64_t c1, CallStats
 // extra lenses of tiles that straddle cells), tiles follow the cells (each
 // cell's rays cut into tiles of at most `tile` rays from its first ray), so
 // no wave straddles two cells; otherwise tiles of `tile` rays from ray 0.
+// Tiles of rows are one wave's rows each, four to a workgroup in their order,
+// whatever cells they belong to.  They follow the cells wherever every cell
+// holds a row: a wave whose rows lie in two cell rows takes each ray's lenses
+// by itself, without shared reciprocals, which costs more than two waves with
+// rows to spare (level 3 at 1.8 rows a cell: 110 us against 48, at 4.4: 237
+// against 192, at 129: 10.09 against 9.66 ms).  Workgroups that follow the
+// cells (and leave waves without rows at each cell's end) took 10.17 ms there,
+// 597 against 563 us at 143 rows a cell.
 // Either way every ray takes the same near lenses with the same arithmetic
 // (a straddling wave's lanes give the lenses outside their own cells mass 0).
 std::vector<TileSpan> make_tiles(const irs_geometry_info &gi, int axis, int32_t tile,
@@ -2662,6 +2672,7 @@ std::vector<TileSpan> make_tiles(const irs_geometry_info &gi, int axis, int32_t 
         const double extra = 0.55 * ((double)(tile - 1) / cols) / 3.0;
         follow = idle <= extra;
     }
+    out.reserve((size_t)(follow ? slots / tile : (n + tile - 1) / tile));
     if (follow) {
         for (int64_t c = 0; c < ncell; ++c) {
             int64_t a, b;
@@ -2685,14 +2696,15 @@ irs_status ensure_rows(irs_plan_s *p)
     if (st != IRS_OK) return st;
     const DevGeom &g = p->dg;
     // column tiles follow the cells when a cell holds >= 1.5 waves of
-    // columns and the idle lanes cost less than straddling; row tiles when a
-    // cell holds a whole tile of rows
+    // columns and the idle lanes cost less than straddling
     p->h_tcol = make_tiles(p->geo.info, 0, kWave, kWave + kWave / 2, true);
-    p->h_trow = make_tiles(p->geo.info, 1, kL3Rows, kL3Rows, false);
+    p->h_trow = make_tiles(p->geo.info, 1, kL3RowsPerWave, 1, false);
     // the tiles in one copy: the rows' follow the columns'
-    const size_t ntc = p->h_tcol.size(), nt = ntc + p->h_trow.size();
-    std::vector<TileSpan> tiles(p->h_tcol);
-    tiles.insert(tiles.end(), p->h_trow.begin(), p->h_trow.end());
+    // the last workgroup's waves without rows read empty entries
+    const size_t ntc = p->h_tcol.size(), nt = ntc + p->h_trow.size() + kL3Waves - 1;
+    std::vector<TileSpan> tiles(nt, TileSpan{0, 0});
+    std::copy(p->h_tcol.begin(), p->h_tcol.end(), tiles.begin());
+    std::copy(p->h_trow.begin(), p->h_trow.end(), tiles.begin() + ntc);
     RowInfo *rows = nullptr;
     ColInfo *cols = nullptr;
     dev_free(p->d_tables);
@@ -3038,7 +3050,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     CallStats *cs = sel.stats;
     const int64_t ntx = (int64_t)p->h_tcol.size();
     const int64_t ntx_pad = (ntx + kXcds - 1) / kXcds * kXcds;
-    // the row tiles that meet rows [jA, jB)
+    // the waves' row spans that meet rows [jA, jB), kL3Waves a tile from the first
     const std::vector<TileSpan> &tr = p->h_trow;
     const int64_t ta = std::upper_bound(tr.begin(), tr.end(), jA,
                                         [](int64_t v, const TileSpan &t) { return v < t.b; }) -
@@ -3046,7 +3058,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     const int64_t tb = std::lower_bound(tr.begin(), tr.end(), jB,
                                         [](const TileSpan &t, int64_t v) { return t.a < v; }) -
                        tr.begin();
-    const int64_t nty = tb - ta;
+    const int64_t nty = (tb - ta + kL3Waves - 1) / kL3Waves;
     L3Map m = map_args(p, sel, (int32_t)cy0, 0, 0);
     m.coef = coef;
     // at most 2^23 workgroups (2^31 work-items) per launch: the dispatch's
@@ -3055,8 +3067,8 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     for (int64_t t0 = 0; t0 < nty; t0 += max_ty) {
         const int64_t t1 = std::min(nty, t0 + max_ty);
         const unsigned nb3 = (unsigned)((t1 - t0) * ntx_pad);
-        const int64_t j0 = std::max(jA, (int64_t)tr[ta + t0].a);
-        const int64_t j1 = std::min(jB, (int64_t)tr[ta + t1 - 1].b);
+        const int64_t j0 = std::max(jA, (int64_t)tr[ta + kL3Waves * t0].a);
+        const int64_t j1 = std::min(jB, (int64_t)tr[std::min(tb, ta + kL3Waves * t1) - 1].b);
         m.jr0 = j0;
         m.jr1 = j1;
         if (cs) {
@@ -3067,7 +3079,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
         }
 #define IRS_L3(U, B)                                                                          \
     hipLaunchKernelGGL((k_level3<U, B>), dim3(nb3), dim3(kThreads), 0, s, m,                  \
-                       (int32_t)(ta + t0), (int32_t)ntx_pad)
+                       (int32_t)(ta + kL3Waves * t0), (int32_t)ntx_pad)
         const bool bin = sel.counts != nullptr;
         if (p->unit_mass) {
             if (bin) IRS_L3(true, true);
@@ -3177,7 +3189,7 @@ irs_status interp_map_args(irs_plan_s *p, uint32_t *counts, unsigned long long *
     sel.counts = counts;
     sel.landed = landed;
     L3Map m = map_args(p, sel, 0, 0, p->dg.ny);
-    m.nty = (int32_t)p->h_trow.size();
+    m.nty = (int32_t)((p->h_trow.size() + kL3Waves - 1) / kL3Waves);
     m.tiles = (int64_t)m.nty * ((m.ntx + kXcds - 1) / kXcds * kXcds);
     m.ncorner = corner_blocks(p, 0, p->dg.ny, m.corner);
     m.corner_items[0] = 0;
