@@ -174,23 +174,6 @@ __device__ __forceinline__ void landed_add(unsigned long long *landed, unsigned 
     atomicAdd(landed + (blockIdx.x & (kLandedSlots - 1)), v);
 }
 
-// Wavefront-aggregated histogram update: lanes hitting the same pixel are
-// merged (ballot on the leader's pixel) and one lane issues a single atomic
-// with the group's count.  Must be called by every lane of the wave
-// (pix = -1 for lanes with nothing to add).
-__device__ __forceinline__ void bin_wave(uint32_t *__restrict__ counts, int32_t pix)
-{
-    uint64_t todo = __ballot(pix >= 0);
-    const int lane = (int)__lane_id();
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int32_t lp = __shfl(pix, leader);
-        const uint64_t same = __ballot(pix == lp) & todo;
-        if (lane == leader) atomicAdd(&counts[lp], (uint32_t)__popcll(same));
-        todo &= ~same;
-    }
-}
-
 // Histogram update by runs: the wave's lanes hold consecutive rays of one
 // row, which mostly share a pixel with their neighbours; each run of equal
 // pixels in lane order adds its length once, from its last lane.  A pixel the

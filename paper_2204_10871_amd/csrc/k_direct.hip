@@ -36,16 +36,17 @@ constexpr int kWaves = kThreads / kWave;
 // -------------------------------------------------------------------------
 // Epilogue shared by both kernels: macro term + sheet + beta + pixel.
 // -------------------------------------------------------------------------
+// have: I1, I2 are the rectangle's sheet integrals.
 __device__ __forceinline__ void assemble(const DevGeom &g, double t1, double t2, double s1,
-                                         double s2, double &a1, double &a2, int32_t &pix)
+                                         double s2, double &a1, double &a2, int32_t &pix,
+                                         bool have = false, double I1 = 0.0, double I2 = 0.0)
 {
     double h1 = 0.0, h2 = 0.0;
     if (g.sheet == 2) {                      // circular plane: -kappa_* theta (Eq. 9)
         h1 = -g.kappa_star * t1;
         h2 = -g.kappa_star * t2;
     } else if (g.sheet) {
-        double I1, I2;
-        sheet_unit(g, t1, t2, I1, I2);
+        if (!have) sheet_unit(g, t1, t2, I1, I2);
         const double f = -g.kappa_star / M_PI;
         h1 = f * I1;
         h2 = f * I2;
@@ -55,14 +56,17 @@ __device__ __forceinline__ void assemble(const DevGeom &g, double t1, double t2,
     pix = pixel_of(g, t1 - a1, t2 - a2);
 }
 
-// Per-ray output or binning, called by every lane.
+// Per-ray output or binning, called by every lane: the wave's lanes hold rays in
+// order, so runs of equal pixels are added once each (a pass over the wave's
+// distinct pixels instead, up to 64 of them: 311 against 303 us for 2048^2 FP64
+// rays, 1026 against 1010 for 1e6 FP32 rays of 4450 lenses).
 __device__ __forceinline__ void emit(bool valid, int64_t out_idx, double a1, double a2,
                                      int32_t pix, double *a1o, double *a2o, int64_t *pixo,
                                      uint32_t *counts, unsigned long long *landed)
 {
     if (counts) {
         const int32_t pv = valid ? pix : -1;
-        bin_wave(counts, pv);
+        bin_runs(counts, pv);
         const uint64_t got = __ballot(pv >= 0);
         if (__lane_id() == 0 && got) landed_add(landed, (unsigned long long)__popcll(got));
     } else if (valid) {
@@ -191,7 +195,7 @@ __device__ __forceinline__ void row_lens(const Stage64<UNIT> &sm, int t, const d
 // slots (a slot: one FMA) of offsets and r^2, 5.75 of the quotient (one
 // reciprocal for four rays) and 2 of the sums, against about 24 with the IEEE
 // division and one ray a lane.  2048^2 rays, 105 lenses: kernel 479 -> 320 us (one ray a
-// lane 362), of which the sheet's closed form, once a ray, is about 90.
+// lane 362) with the sheet's closed form, once a ray, about 90 of it; 268 now.
 template <bool UNIT, int R>
 __device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const DevGeom &g,
                                           const double *__restrict__ lx,
@@ -247,6 +251,118 @@ __device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const DevGeom &g,
     }
 }
 
+// The rectangle's sheet integrals along a ray row, as a series about a point
+// (x0, y) of it (T_0 in two parts, the larger at T[kSheetTerms]): with w = z - corner, S = I2 + i I1 has d^2 S/dx^2 = sum +-1/w and
+// dS/dx = sum +-(ln|w| + i atan(v/u)) (signs and terms of sheet_unit), so
+//     S(x0 + s d) = sum_n T_n d^n,   T_n = -s/(n (n-1)) sum +-(-s/w)^(n-1), n >= 2.
+// Lane = 16 corner + m takes its corner's terms and the powers m, m + 16, m + 32.
+// Returns the number of terms that leave less than 2^-57 of s (4 s rho^n with
+// rho = s/(distance to the nearest corner)), 0 for rho > 0.4.  Called by whole
+// waves; x0, y, s wave-uniform; T: the wave's LDS.
+//
+// The closed form (four logarithms and arctangents) is 560 of the 1940 VALU
+// instructions of a ray in a map of 105 lenses; the series is about 150 where a
+// wave's 256 rays are one row.  2048^2 rays, 105 lenses: 303 -> 263 us.  The
+// closed form's rounding (corner terms of 100 and more that cancel) is most of a
+// deflection's error; T_0 carries its roundings along, so the error against 64
+// more bits falls: mean 2.4e-14 -> 1.0e-14 (1.2e6 rays, 915 lenses).
+constexpr int kSheetTerms = 48;
+
+__device__ __forceinline__ double over_corners(double v)
+{
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
+}
+
+// a + b and what its rounding lost, added to lo
+__device__ __forceinline__ double sum_err(double a, double b, double &lo)
+{
+    const double s = a + b, t = s - a;
+    lo += (a - (s - t)) + (b - t);
+    return s;
+}
+
+// (hi, lo) += a * b
+__device__ __forceinline__ void add_product(double a, double b, double &hi, double &lo)
+{
+    const double p = a * b;
+    lo += fma(a, b, -p);
+    hi = sum_err(hi, p, lo);
+}
+
+// the corners' (hi, lo) summed
+__device__ __forceinline__ void over_corners2(double &hi, double &lo)
+{
+#pragma unroll
+    for (int b = 16; b <= 32; b *= 2) {
+        const double h = __shfl_xor(hi, b), l = __shfl_xor(lo, b);
+        lo += l;
+        hi = sum_err(hi, h, lo);
+    }
+}
+
+__device__ __forceinline__ int sheet_row_series(const DevGeom &g, double x0, double y, double s,
+                                                double2 *T)
+{
+    const int lane = threadIdx.x % kWave, c = lane / 16, m = lane % 16;
+    const double ca = (c == 0 || c == 3) ? g.a1 : g.a2, cb = c < 2 ? g.b1 : g.b2;
+    const double sgn = (c == 0 || c == 2) ? 1.0 : -1.0;
+    double ul = 0.0, vl = 0.0;
+    const double u = sum_err(x0, -ca, ul), v = sum_err(y, -cb, vl);
+    const double r2 = u * u + v * v, inv = 1.0 / r2;
+    double rho2 = s * s * inv, big = r2;
+    rho2 = fmax(rho2, __shfl_xor(rho2, 16));
+    rho2 = fmax(rho2, __shfl_xor(rho2, 32));
+    if (!(rho2 <= 0.16)) return 0;
+    big = fmax(big, __shfl_xor(big, 16));
+    big = fmax(big, __shfl_xor(big, 32));
+    // T_0 and T_1 with what their roundings lose: the logarithms scaled by a
+    // power of two (the same in all corners, which leaves the sums unchanged)
+    const double l = 0.5 * sgn * log(ldexp(r2, -__builtin_amdgcn_frexp_exp(big)));
+    const bool steep = fabs(u) < fabs(v);
+    const double q = steep ? u / v : v / u, t = atan(q);
+    double ol = copysign(kHalfPiLo, q);
+    const double o = sum_err(copysign(M_PI_2, q), -t, ol);            // pi/2 - t
+    const double tu = sgn * (steep ? o : t), tv = sgn * (steep ? t : o);    // atan(v/u), atan(u/v)
+    double h1 = v * l, e1 = fma(v, l, -h1), h2 = u * l, e2 = fma(u, l, -h2);
+    add_product(u, tu, h1, e1);
+    add_product(v, tv, h2, e2);
+    e1 += ul * tu + vl * (l + sgn) + (steep ? sgn * u * ol : 0.0);
+    e2 += vl * tv + ul * (l + sgn) + (steep ? 0.0 : sgn * v * ol);
+    over_corners2(h1, e1);
+    over_corners2(h2, e2);
+    const double g1 = over_corners(tu), g2 = over_corners(l);
+    // (-s/w)^m, then steps of 16
+    double qr = -s * u * inv, qi = s * v * inv, er = sgn, ei = 0.0;
+#pragma unroll
+    for (int b = 1; b < 16; b <<= 1) {
+        const double tr = er * qr - ei * qi, ti = er * qi + ei * qr;
+        er = (m & b) ? tr : er;
+        ei = (m & b) ? ti : ei;
+        const double sr = qr * qr - qi * qi;
+        qi = 2.0 * qr * qi;
+        qr = sr;
+    }
+#pragma unroll
+    for (int h = 0; h < kSheetTerms / 16; ++h) {
+        const int n = 16 * h + m + 1;
+        const double sr = over_corners(er), si = over_corners(ei);
+        const double f = -s / ((double)n * (double)(n - 1));
+        double2 t = n == 1 ? make_double2(s * g2, s * g1) : make_double2(f * sr, f * si);
+        if (c == 0 && n < kSheetTerms) T[n] = t;
+        if (lane == 0 && h == 0) {
+            T[0] = make_double2(e2, e1);
+            T[kSheetTerms] = make_double2(h2, h1);
+        }
+        const double tr = er * qr - ei * qi;
+        ei = er * qi + ei * qr;
+        er = tr;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const float bits = -0.5f * __log2f((float)rho2);        // of one more term; >= 1.32
+    return __builtin_amdgcn_readfirstlane(min(kSheetTerms, 2 + (int)ceilf(59.0f / fmaxf(bits, 1.0f))));
+}
+
 // A workgroup takes kThreads R consecutive rays, a wave 64 R of them.
 template <bool UNIT, int R>
 __global__ __launch_bounds__(kThreads) void k_direct_f64(
@@ -275,12 +391,43 @@ __global__ __launch_bounds__(kThreads) void k_direct_f64(
         t2[k] = ray_y(g, j);
     }
     lens_sums<UNIT, R>(sm, g, lx, ly, lm, nl, tame, t1, t2, one_row, s1, s2);
+    double I1[R] = {}, I2[R] = {};
+    int terms = 0;                                         // wave-uniform
+    if constexpr (R == 4) {
+        __shared__ double2 s_T[kWaves][kSheetTerms + 1];
+        // (deflections keep the closed form, so that a ray's do not depend on the
+        // range they are asked in)
+        if (counts && g.sheet == 1 && one_row) {
+            const double x0 = ray_x(g, i0 + kWave * R / 2), s = kWave * R / 2 * g.ray_dx;
+            terms = sheet_row_series(g, x0, t2[0], s, s_T[wave]);
+            if (terms) {
+                const double is = 1.0 / s;
+                double d[R];
+#pragma unroll
+                for (int k = 0; k < R; ++k) d[k] = (t1[k] - x0) * is;
+                for (int n = terms - 1; n >= 0; --n) {
+                    const double2 T = s_T[wave][n];
+#pragma unroll
+                    for (int k = 0; k < R; ++k) {
+                        I1[k] = fma(I1[k], d[k], T.y);
+                        I2[k] = fma(I2[k], d[k], T.x);
+                    }
+                }
+                const double2 T = s_T[wave][kSheetTerms];
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    I1[k] += T.y;
+                    I2[k] += T.x;
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int64_t r = w0 + lane + kWave * k;
         double a1, a2;
         int32_t pix;
-        assemble(g, t1[k], t2[k], s1[k], s2[k], a1, a2, pix);
+        assemble(g, t1[k], t2[k], s1[k], s2[k], a1, a2, pix, terms > 0, I1[k], I2[k]);
         emit(r < r_end, r - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
     }
 }
