@@ -1655,14 +1655,13 @@ struct L3Lane {
 // real hi.
 // FULL: every ray of these rows lies in [ray_first, ray_last).  BIN: pixels
 // into pxs/pys (-1 for rays not binned); otherwise the per-ray outputs.
-template <bool BIN, bool FULL>
+template <bool BIN, bool FULL, int R>
 __device__ __forceinline__ void level3_rows(
     const DevGeom &g, const RowInfo *__restrict__ rows, const double *__restrict__ coef,
     int32_t cy0, int64_t nxq, const L3Lane &ln, int32_t jw, int k0, int k1, int64_t ray_first,
     int64_t ray_last, const double *n1s, const double *n2s, double *a1o, double *a2o,
     int64_t *pixo, int32_t *pxs, int32_t *pys)
 {
-    constexpr int R = kL3RowsPerWave;
     const int32_t ny1 = (int32_t)g.ny - 1;
     double2 C[5] = {};
     int32_t cgy = -1;                                     // level-2 row held in C
@@ -1774,11 +1773,11 @@ constexpr int kWrapBits = 6, kWrap = 1 << kWrapBits, kWrapBins = kWrap * kWrap;
 static_assert(kWrapBins / 2 + kWrapBins <= kHistCap, "counts and tags share the histogram");
 static_assert(kWave * kL3Rows < 65536, "16-bit counts");
 
+template <int R>
 __device__ __forceinline__ void scatter_bins(const int32_t *pxs, const int32_t *pys, int bx0,
                                              int by0, int32_t npix, uint32_t *counts,
                                              uint32_t *hist)
 {
-    constexpr int R = kL3RowsPerWave;
     uint32_t *cnt = hist, *tag = hist + kWrapBins / 2;
     for (int b = (int)threadIdx.x; b < kWrapBins / 2; b += kThreads) cnt[b] = 0u;
     auto bin_of = [&](int k) {
@@ -1822,25 +1821,28 @@ __device__ __forceinline__ void scatter_bins(const int32_t *pxs, const int32_t *
     }
 }
 
-// One tile of rays: columns tcol[tx] (one per lane), wave w rows trow[wr + w]
-// (at most kL3RowsPerWave), restricted to rows [jr0, jr1).  Every ray: the
+// One tile of rays: columns tcol[tx] (one per lane), kL3Waves R / kL3RowsPerWave
+// entries of trow from wr, R rows a wave (the first or second half of an entry's
+// for R = 4; the rows that share a reciprocal are the same), restricted to rows
+// [jr0, jr1).  Every ray: the
 // near lenses exactly, Horner of its level-2 point's C_0..C_4, the macro
 // term, beta and the pixel; BIN: binned through an LDS histogram over the
 // tile's landed-pixel box (flushed with one global atomic per non-empty bin),
 // or, for a box larger than the histogram, the wrapped histogram of
 // scatter_bins.  Called by every thread of the workgroup.
-template <bool UNIT, bool BIN>
+template <bool UNIT, bool BIN, int R>
 __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t wr, L3Lds *lds)
 {
     const DevGeom &g = m.g;
     const int tid = threadIdx.x;
     const int lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    constexpr int R = kL3RowsPerWave;
+    constexpr int H = kL3RowsPerWave / R;                           // waves an entry
+    static_assert(R % kNearGroup == 0, "whole groups");
     const TileSpan tc = m.tcol[tx];
-    const TileSpan tr = m.trow[wr + wave];
+    const TileSpan tr = m.trow[wr + wave / H];
     const int32_t ny1 = (int32_t)g.ny - 1;                          // ny < 2^31
-    const int32_t jw = tr.a;                                        // the wave's first row
+    const int32_t jw = tr.a + wave % H * R;                         // the wave's first row
     if (BIN && tid == 0) {                    // one tile per workgroup: set up its LDS
         lds->bmin[0] = lds->bmin[1] = UINT32_MAX;
         lds->bmax[0] = lds->bmax[1] = -1;
@@ -1886,8 +1888,8 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
         const int32_t cxb = m.cols[tc.b - 1].cx;
         const int32_t cl = cxa > 0 ? cxa - 1 : 0, ch = cxb < g.n1x - 1 ? cxb + 1 : g.n1x - 1;
         const bool straddle = cxa != cxb;
-        const int32_t cy0r = row(0).cy;
-        if (row(kt - 1).cy == cy0r) {                     // rows sorted: all share cy0r
+        const int32_t cy0r = m.rows[tr.a].cy;
+        if (m.rows[tr.b - 1].cy == cy0r) {                // rows sorted: all share cy0r
             if (straddle)
                 near_pass<UNIT, R, true>(g, m.lxy, m.lm, m.cell_start, cy0r, cl, ch, true, xl, xh,
                                          t1, t2s, n1s, n2s);
@@ -1916,10 +1918,10 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
     const L3Lane ln{i, i32, in_col, corner_col, wave_corner, t1, hr, c1, s1, col->coff};
     int32_t pxs[R], pys[R];
     if (full)
-        level3_rows<BIN, true>(g, m.rows, m.coef, m.cy0, nxq, ln, jw, k0, k1, m.ray_first,
+        level3_rows<BIN, true, R>(g, m.rows, m.coef, m.cy0, nxq, ln, jw, k0, k1, m.ray_first,
                                m.ray_last, n1s, n2s, m.a1o, m.a2o, m.pixo, pxs, pys);
     else
-        level3_rows<BIN, false>(g, m.rows, m.coef, m.cy0, nxq, ln, jw, k0, k1, m.ray_first,
+        level3_rows<BIN, false, R>(g, m.rows, m.coef, m.cy0, nxq, ln, jw, k0, k1, m.ray_first,
                                 m.ray_last, n1s, n2s, m.a1o, m.a2o, m.pixo, pxs, pys);
     if (!BIN) return;
 
@@ -1961,7 +1963,7 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
     uint32_t *counts = m.counts;
     if (area > kHistCap) {
         // rays scattered, as near a lens (block-uniform): a wrapped histogram
-        scatter_bins(pxs, pys, bx0, by0, g.npix, counts, lds->hist);
+        scatter_bins<R>(pxs, pys, bx0, by0, g.npix, counts, lds->hist);
         return;
     }
     const int nbin = (int)area;
@@ -2001,16 +2003,17 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
 }
 
 // One map: column tile tx = blockIdx.x mod ntx_pad, rows of the kL3Waves waves
-// from wr0 + kL3Waves (blockIdx.x / ntx_pad).  ntx_pad is a multiple of the 8 XCDs, which take consecutive
+// from wr0 + kL3Waves (blockIdx.x / ntx_pad) (half as many entries for R = 4).  ntx_pad is a multiple of the 8 XCDs, which take consecutive
 // workgroups in turn, so a column tile runs on the same XCD in every tile row
 // and finds its level-2 coefficients and lenses in that XCD's L2.
-template <bool UNIT, bool BIN>
+template <bool UNIT, bool BIN, int R>
 __global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t wr0, int32_t ntx_pad)
 {
     __shared__ L3Lds lds;
     const int32_t tx = (int32_t)(blockIdx.x % (uint32_t)ntx_pad);
     if (tx >= m.ntx) return;                               // padding (block-uniform)
-    level3_tile<UNIT, BIN>(m, tx, wr0 + kL3Waves * (int32_t)(blockIdx.x / (uint32_t)ntx_pad), &lds);
+    level3_tile<UNIT, BIN, R>(m, tx, wr0 + kL3Waves * R / kL3RowsPerWave *
+                                               (int32_t)(blockIdx.x / (uint32_t)ntx_pad), &lds);
 }
 
 // Ray idx of one of the rectangle's four corner cells (ray columns [i0, i1),
@@ -2124,7 +2127,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_level3_maps(const L3Map *maps_i
     const int32_t ntx_pad = (m.ntx + kXcds - 1) / kXcds * kXcds;
     const int32_t tx = (int32_t)(local % ntx_pad);
     if (tx < m.ntx)                                         // padding (block-uniform)
-        level3_tile<UNIT, true>(m, tx, kL3Waves * (int32_t)(local / ntx_pad), &lds);
+        level3_tile<UNIT, true, kL3RowsPerWave>(m, tx, kL3Waves * (int32_t)(local / ntx_pad), &lds);
 }
 
 // The same maps' corner-cell rays: block b takes kThreads rays of one corner
@@ -3036,6 +3039,13 @@ irs_status level2_band(irs_plan_s *p, int64_t c0, int64_t c1, double *coef, Call
 
 namespace {
 
+// Launches of at most this many waves of eight rows (what the chip holds at once:
+// five a SIMD) take waves of four: with slots to spare a wave's own length counts.
+// 3e5 per-ray outputs (1,400 waves) 26.5 -> 24.1 us a call, 4e6 48.7 -> 46.4; level
+// 3 of a map of 240 waves 24.2 -> 19.9 us, 2,000 25.9 -> 24.3, 4,800 27.2 -> 26.3,
+// but 8,200 33.2 -> 34.1 and 17,000 46.0 -> 49.8.
+constexpr int64_t kHalfTiles = 5 * 1024;
+
 // Level 3 of one band of level-1 rows [c0, c1] whose coefficients are in
 // coef (from level-1 row cy0), on stream s: the band's row tiles, then its
 // rays in the rectangle's corner cells.
@@ -3050,7 +3060,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     CallStats *cs = sel.stats;
     const int64_t ntx = (int64_t)p->h_tcol.size();
     const int64_t ntx_pad = (ntx + kXcds - 1) / kXcds * kXcds;
-    // the waves' row spans that meet rows [jA, jB), kL3Waves a tile from the first
+    // the waves' row spans that meet rows [jA, jB), `per` a workgroup from the first
     const std::vector<TileSpan> &tr = p->h_trow;
     const int64_t ta = std::upper_bound(tr.begin(), tr.end(), jA,
                                         [](int64_t v, const TileSpan &t) { return v < t.b; }) -
@@ -3058,7 +3068,9 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     const int64_t tb = std::lower_bound(tr.begin(), tr.end(), jB,
                                         [](const TileSpan &t, int64_t v) { return t.a < v; }) -
                        tr.begin();
-    const int64_t nty = (tb - ta + kL3Waves - 1) / kL3Waves;
+    const bool half = (tb - ta) * ntx <= kHalfTiles;
+    const int64_t per = half ? kL3Waves / 2 : kL3Waves;
+    const int64_t nty = (tb - ta + per - 1) / per;
     L3Map m = map_args(p, sel, (int32_t)cy0, 0, 0);
     m.coef = coef;
     // at most 2^23 workgroups (2^31 work-items) per launch: the dispatch's
@@ -3067,8 +3079,8 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     for (int64_t t0 = 0; t0 < nty; t0 += max_ty) {
         const int64_t t1 = std::min(nty, t0 + max_ty);
         const unsigned nb3 = (unsigned)((t1 - t0) * ntx_pad);
-        const int64_t j0 = std::max(jA, (int64_t)tr[ta + kL3Waves * t0].a);
-        const int64_t j1 = std::min(jB, (int64_t)tr[std::min(tb, ta + kL3Waves * t1) - 1].b);
+        const int64_t j0 = std::max(jA, (int64_t)tr[ta + per * t0].a);
+        const int64_t j1 = std::min(jB, (int64_t)tr[std::min(tb, ta + per * t1) - 1].b);
         m.jr0 = j0;
         m.jr1 = j1;
         if (cs) {
@@ -3077,9 +3089,14 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
             cs->n_rays++;
             cs->work.push_back({CallStats::kRays, 0, j0, j1});
         }
+#define IRS_L3R(U, B, R)                                                                      \
+    hipLaunchKernelGGL((k_level3<U, B, R>), dim3(nb3), dim3(kThreads), 0, s, m,               \
+                       (int32_t)(ta + per * t0), (int32_t)ntx_pad)
 #define IRS_L3(U, B)                                                                          \
-    hipLaunchKernelGGL((k_level3<U, B>), dim3(nb3), dim3(kThreads), 0, s, m,                  \
-                       (int32_t)(ta + kL3Waves * t0), (int32_t)ntx_pad)
+    do {                                                                                      \
+        if (half) IRS_L3R(U, B, kL3RowsPerWave / 2);                                          \
+        else IRS_L3R(U, B, kL3RowsPerWave);                                                   \
+    } while (0)
         const bool bin = sel.counts != nullptr;
         if (p->unit_mass) {
             if (bin) IRS_L3(true, true);
@@ -3089,6 +3106,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
             else IRS_L3(false, false);
         }
 #undef IRS_L3
+#undef IRS_L3R
         IRS_HIP(hipGetLastError());
         if (t1 == nty) {
             // the band's rays in the rectangle's corner cells (launched on

@@ -38,3 +38,23 @@ def test_ray_rows(rows, mass):
     assert np.mean(px == ref["pix"]) >= 1 - 1e-5
     assert st["rays_landed"] == (px >= 0).sum()
     assert np.array_equal(np.bincount(px[px >= 0], minlength=48 * 48), counts.ravel())
+
+
+@pytest.mark.parametrize("mass", ["unit", "salpeter"])
+def test_half_waves(mass):
+    """A call of few rays takes waves of four rows, the whole grid (5740 waves of
+    eight) does not: the same bits, the map's counts the rays' pixels."""
+    kw = dict(kappa_star=0.45, kappa_c=0.05, gamma=0.2, source_side=12.0, npix=256)
+    g = orc.geometry(**kw, n_rays=2_960_000)
+    c = Case(**kw, n_rays=2_960_000, lenses=synth.uniform_lenses(g.n_stars_expected, g.rect, 7,
+                                                                 mass=mass))
+    with c.plan("interp", "fp64") as pl:
+        nx, ny, n = pl.geometry["nx"], pl.geometry["ny"], pl.n_rays
+        a1, a2, px = pl.deflect_grid(0, n)
+        counts, _ = pl.shoot_map()
+        for f, l in ((0, 3), (n - 700, n), (81 * nx - 5, 81 * nx + 5), (ny // 2 * nx + 11, ny // 2 * nx + 9 * nx),
+                     (7 * nx, 8 * nx), (300 * nx + nx // 2, 340 * nx)):
+            b1, b2, bx = pl.deflect_grid(f, l - f)
+            assert np.array_equal(a1[f:l], b1) and np.array_equal(a2[f:l], b2) and \
+                np.array_equal(px[f:l], bx), (f, l)
+    assert np.array_equal(np.bincount(px[px >= 0], minlength=256 * 256), counts.ravel())
