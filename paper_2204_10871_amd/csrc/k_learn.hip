@@ -1052,7 +1052,10 @@ constexpr int kL3Threads = 768;            // one workgroup a CU (its table), th
 constexpr int kL3CornerThreads = 384;
 constexpr int kLearnRows = 4;
 constexpr int kLearnItem = 8;
-static_assert(kLearnItem % kLearnRows == 0, "whole groups");
+// rows of an item of the corner cells, whose few rays fill a part of the chip: one
+// group of rows (9822 lenses, 103 rows a cell: 53 -> 34 us; of eight rows before)
+constexpr int kLearnCornerItem = kLearnRows;
+static_assert(kLearnItem % kLearnRows == 0 && kLearnCornerItem % kLearnRows == 0, "whole groups");
 
 // a range of rays: columns [i0, i1), rows [j0, j1)
 struct RaySpan {
@@ -1086,11 +1089,11 @@ __device__ __forceinline__ void learned_rays(IRS_LEARNED_RAY_ARGS, const RaySpan
     const int lane = threadIdx.x % kW;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kW);   // items are wave-uniform
     constexpr int kWaves = THREADS / kW;
-    constexpr int R = kLearnRows;
+    constexpr int R = kLearnRows, Item = CORNER ? kLearnCornerItem : kLearnItem;
     static_assert(R == kNearGroup, "a lane's rows share a reciprocal");
     const int64_t ntx = (sp.i1 - sp.i0 + kW - 1) / kW;
     const int64_t jb = sp.j0 / R * R;                         // the first group's first row
-    const int64_t items = (sp.j1 - jb + kLearnItem - 1) / kLearnItem * ntx;
+    const int64_t items = (sp.j1 - jb + Item - 1) / Item * ntx;
     const int q1 = lg.qc + 1;
     const int32_t ny1 = (int32_t)g.ny - 1;
     unsigned long long nland = 0;
@@ -1109,11 +1112,11 @@ __device__ __forceinline__ void learned_rays(IRS_LEARNED_RAY_ARGS, const RaySpan
         float D[16];
         double sig = 0.0, C[4][4];
         int32_t cgy = -1;                                     // the square row they hold
-        const int32_t je = (int32_t)min<int64_t>(sp.j1, jb + (ig + 1) * kLearnItem);
+        const int32_t je = (int32_t)min<int64_t>(sp.j1, jb + (ig + 1) * Item);
         // rows jg .. jg + R - 1 of one column per lane; those outside the
         // range [j0, j1) bin nothing
 #pragma unroll 1
-        for (int32_t jg = (int32_t)(jb + ig * kLearnItem); jg < je; jg += R) {
+        for (int32_t jg = (int32_t)(jb + ig * Item); jg < je; jg += R) {
             auto row = [&](int k) -> const LearnRow & { return lrow[min(jg + k, ny1)]; };
             double t2s[R], n1[R], n2[R];
 #pragma unroll
@@ -1759,8 +1762,8 @@ irs_status launch_learned(irs_plan_s *p, const RaySel &sel)
             cs->n_rays++;
         }
         // workgroups of `threads` for a range: one a CU at most (the table)
-        auto blocks = [&](const RaySpan &sp, int threads) {
-            const int64_t items = (sp.j1 - sp.j0 / kLearnRows * kLearnRows + kLearnItem - 1) / kLearnItem *
+        auto blocks = [&](const RaySpan &sp, int threads, int item) {
+            const int64_t items = (sp.j1 - sp.j0 / kLearnRows * kLearnRows + item - 1) / item *
                                   ((sp.i1 - sp.i0 + kW - 1) / kW);
             return (unsigned)std::max<int64_t>(
                 1, std::min<int64_t>(ncu, (items + threads / kW - 1) / (threads / kW)));
@@ -1773,8 +1776,8 @@ irs_status launch_learned(irs_plan_s *p, const RaySel &sel)
                        (const LearnRow *)p->d_lcol, sel.ray_first, sel.ray_last, sel.alpha1,    \
                        sel.alpha2, sel.pixel, sel.counts, sel.landed, SPANS)
         const RaySpan all{0, g.nx, jA, jB};
-        if (p->unit_mass) IRS_L3L(k_level3_learned<true>, dim3(blocks(all, kL3Threads)), kL3Threads, all);
-        else IRS_L3L(k_level3_learned<false>, dim3(blocks(all, kL3Threads)), kL3Threads, all);
+        if (p->unit_mass) IRS_L3L(k_level3_learned<true>, dim3(blocks(all, kL3Threads, kLearnItem)), kL3Threads, all);
+        else IRS_L3L(k_level3_learned<false>, dim3(blocks(all, kL3Threads, kLearnItem)), kL3Threads, all);
         if (g.sheet) {
             // the rectangle's corner cells (distinct ones) that meet these
             // rows, in one launch
@@ -1790,7 +1793,7 @@ irs_status launch_learned(irs_plan_s *p, const RaySel &sel)
                     c.j1 = std::min(c.j1, jB);
                     if (c.i0 >= c.i1 || c.j0 >= c.j1) continue;
                     sps.s[ns++] = c;
-                    nb = std::max(nb, blocks(c, kL3CornerThreads));
+                    nb = std::max(nb, blocks(c, kL3CornerThreads, kLearnCornerItem));
                 }
             if (ns) {
                 if (p->unit_mass) IRS_L3L(k_level3_learned_corner<true>, dim3(nb, ns), kL3CornerThreads, sps);
