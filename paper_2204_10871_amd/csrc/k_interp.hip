@@ -2002,20 +2002,6 @@ __device__ __forceinline__ void level3_tile(const L3Map &m, int32_t tx, int32_t 
     }
 }
 
-// One map: column tile tx = blockIdx.x mod ntx_pad, rows of the kL3Waves waves
-// from wr0 + kL3Waves (blockIdx.x / ntx_pad) (half as many entries for R = 4).  ntx_pad is a multiple of the 8 XCDs, which take consecutive
-// workgroups in turn, so a column tile runs on the same XCD in every tile row
-// and finds its level-2 coefficients and lenses in that XCD's L2.
-template <bool UNIT, bool BIN, int R>
-__global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t wr0, int32_t ntx_pad)
-{
-    __shared__ L3Lds lds;
-    const int32_t tx = (int32_t)(blockIdx.x % (uint32_t)ntx_pad);
-    if (tx >= m.ntx) return;                               // padding (block-uniform)
-    level3_tile<UNIT, BIN, R>(m, tx, wr0 + kL3Waves * R / kL3RowsPerWave *
-                                               (int32_t)(blockIdx.x / (uint32_t)ntx_pad), &lds);
-}
-
 // Ray idx of one of the rectangle's four corner cells (ray columns [i0, i1),
 // rows [j0, j1)), which k_level3 leaves out: the sheet's series does not
 // converge over a corner cell, so these rays take its closed form.  Nearby
@@ -2084,6 +2070,43 @@ __device__ __forceinline__ void level3_corner_ray(const L3Map &m, int64_t i0, in
 }
 
 // The corner cells' rays of a map, one per lane (blockIdx.y: the corner).
+// One map: column tile tx = blockIdx.x mod ntx_pad, rows of the kL3Waves waves
+// from wr0 + kL3Waves (blockIdx.x / ntx_pad) (half as many entries for R = 4).
+// R = 4 maps have the corner cells' rays in their first workgroups, ncb a cell:
+// one launch fewer where launches count (a map of 1.2e5 rays 136 -> 129 us; with
+// per-ray outputs the registers it takes cost more, 22.9 against 20.7 us).  ntx_pad is a multiple of the 8 XCDs, which take consecutive
+// workgroups in turn, so a column tile runs on the same XCD in every tile row
+// and finds its level-2 coefficients and lenses in that XCD's L2.
+// workgroups of n corner cells at ncb each, padded to whole rounds of the XCDs
+__host__ __device__ constexpr uint32_t corner_grid(uint32_t ncb, int32_t n)
+{
+    return (ncb * (uint32_t)n + kXcds - 1) / kXcds * kXcds;
+}
+
+template <bool UNIT, bool BIN, int R>
+__global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t wr0, int32_t ntx_pad,
+                                                         uint32_t ncb)
+{
+    __shared__ L3Lds lds;
+    uint32_t b = blockIdx.x;
+    if constexpr (BIN && R < kL3RowsPerWave) {
+        const uint32_t nc = corner_grid(ncb, m.ncorner);
+        if (b < nc) {
+            const uint32_t c = b / ncb;
+            if (c < (uint32_t)m.ncorner)
+                level3_corner_ray<UNIT, BIN>(m, m.corner[c][0], m.corner[c][1], m.corner[c][2],
+                                             m.corner[c][3],
+                                             (int64_t)(b - c * ncb) * kThreads + threadIdx.x);
+            return;
+        }
+        b -= nc;
+    }
+    const int32_t tx = (int32_t)(b % (uint32_t)ntx_pad);
+    if (tx >= m.ntx) return;                               // padding (block-uniform)
+    level3_tile<UNIT, BIN, R>(m, tx, wr0 + kL3Waves * R / kL3RowsPerWave *
+                                               (int32_t)(b / (uint32_t)ntx_pad), &lds);
+}
+
 template <bool UNIT, bool BIN>
 __global__ __launch_bounds__(kThreads) void k_level3_corner(L3Map m)
 {
@@ -2910,15 +2933,22 @@ int corner_blocks(const irs_plan_s *p, int64_t jA, int64_t jB, int64_t c[4][4])
 
 // k_level3_corner over the rays of rows [jA, jB) in the rectangle's corner
 // cells (m: the band's launch arguments)
-irs_status launch_corners(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
+// most workgroups that a corner cell's rays of rows [jA, jB) take; sets m.corner
+unsigned corner_groups(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
 {
     m.ncorner = corner_blocks(p, jA, jB, m.corner);
     int64_t most = 0;
     for (int k = 0; k < m.ncorner; ++k)
         most = std::max(most, (m.corner[k][1] - m.corner[k][0]) * (m.corner[k][3] - m.corner[k][2]));
-    if (most == 0) return IRS_OK;
+    return (unsigned)((most + kThreads - 1) / kThreads);
+}
+
+irs_status launch_corners(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
+{
+    const unsigned nb = corner_groups(p, m, jA, jB);
+    if (nb == 0) return IRS_OK;
     const bool bin = m.counts != nullptr;
-    const dim3 grid((unsigned)((most + kThreads - 1) / kThreads), (unsigned)m.ncorner);
+    const dim3 grid(nb, (unsigned)m.ncorner);
 #define IRS_L3C(U, B) hipLaunchKernelGGL((k_level3_corner<U, B>), grid, dim3(kThreads), 0, p->stream, m)
     if (p->unit_mass) {
         if (bin) IRS_L3C(true, true);
@@ -3073,12 +3103,16 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
     const int64_t nty = (tb - ta + per - 1) / per;
     L3Map m = map_args(p, sel, (int32_t)cy0, 0, 0);
     m.coef = coef;
+    // half a map: one launch (max_ty below), with the corner cells
+    const bool with_corners = half && sel.counts;
+    const unsigned ncb = with_corners ? corner_groups(p, m, jA, jB) : 0;
+    const unsigned nc = corner_grid(ncb, m.ncorner);
     // at most 2^23 workgroups (2^31 work-items) per launch: the dispatch's
     // grid size in work-items is a 32-bit number
     const int64_t max_ty = std::max<int64_t>(1, ((int64_t)1 << 23) / ntx_pad);
     for (int64_t t0 = 0; t0 < nty; t0 += max_ty) {
         const int64_t t1 = std::min(nty, t0 + max_ty);
-        const unsigned nb3 = (unsigned)((t1 - t0) * ntx_pad);
+        const unsigned nb3 = nc + (unsigned)((t1 - t0) * ntx_pad);
         const int64_t j0 = std::max(jA, (int64_t)tr[ta + per * t0].a);
         const int64_t j1 = std::min(jB, (int64_t)tr[std::min(tb, ta + per * t1) - 1].b);
         m.jr0 = j0;
@@ -3091,7 +3125,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
         }
 #define IRS_L3R(U, B, R)                                                                      \
     hipLaunchKernelGGL((k_level3<U, B, R>), dim3(nb3), dim3(kThreads), 0, s, m,               \
-                       (int32_t)(ta + per * t0), (int32_t)ntx_pad)
+                       (int32_t)(ta + per * t0), (int32_t)ntx_pad, ncb)
 #define IRS_L3(U, B)                                                                          \
     do {                                                                                      \
         if (half) IRS_L3R(U, B, kL3RowsPerWave / 2);                                          \
@@ -3108,7 +3142,7 @@ irs_status level3_band(irs_plan_s *p, const RaySel &sel, int64_t c0, int64_t c1,
 #undef IRS_L3
 #undef IRS_L3R
         IRS_HIP(hipGetLastError());
-        if (t1 == nty) {
+        if (t1 == nty && !with_corners) {
             // the band's rays in the rectangle's corner cells (launched on
             // the plan's stream, which is s here)
             irs_status st = launch_corners(p, m, jA, jB);
