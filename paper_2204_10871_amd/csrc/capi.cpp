@@ -380,7 +380,7 @@ irs_status irs_plan(const irs_params *params, int64_t n_lens, const double *x, c
         return st;
     }
     // extents for irs_plan_s::tame: with squared distances of 1e-70 .. 1e41
-    // products of four of them, quotients of a mass by one and their
+    // products of two of them, quotients of a mass by one and their
     // remainders are normal numbers (all of it is checked without branches,
     // and lens by lens only if something lies outside)
     int wild = !(std::max(hg.info.ix, hg.info.iy) < 1e20);

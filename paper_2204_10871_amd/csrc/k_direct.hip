@@ -6,8 +6,9 @@
 // N_rays * N_* (Eq. 12).
 //
 // Two kernels:
-//   k_direct_f64  -- plain double precision, one ray per lane or four, lens tiles
-//                    in LDS.
+//   k_direct_f64  -- plain double precision, lens tiles in LDS: one ray per lane
+//                    or, in plans of many rays (k_direct_f64_blocks), blocks of
+//                    256 columns of a ray row, four rays per lane.
 //   k_direct_f32  -- the FP32 VALU-bound form: each wave owns 64 columns of up
 //                    to eight ray rows (four or sixteen in the other shapes);
 //                    ray-lens offsets are rounded to FP32 once from their FP64
@@ -80,10 +81,10 @@ __device__ __forceinline__ void emit(bool valid, int64_t out_idx, double a1, dou
 // FP64
 // -------------------------------------------------------------------------
 constexpr int kLens64 = 256;
-constexpr int64_t kRays4 = (int64_t)1 << 20;    // calls of at least this many rays: four a lane
+constexpr int kBlock = 4 * kWave;               // columns of a block (k_direct_f64_blocks)
 
 // Below this |theta_2 - y_i| a term takes the IEEE division: r^2 may be 0,
-// subnormal or too small for the refined reciprocals (a product of four r^2
+// subnormal or too small for the refined reciprocals (a product of two r^2
 // has to stay a normal number).
 constexpr double kNear64 = 1e-35;
 
@@ -113,25 +114,21 @@ __device__ __forceinline__ double quotient(double m, double r2)
     return fma(v, fma(-r2, q, m), q);
 }
 
-// m / r2[k] for four r2: the four estimates come from one reciprocal of their
-// product (refined once, 2^-48) by back-substitution through its prefixes;
-// each is then corrected with its own remainder as in quotient(), so the
-// quotients are rounded alike.
+// m / r2[k] for two r2: both estimates come from one reciprocal of their product
+// (refined once, 2^-48); each is then corrected with its own remainder as in
+// quotient(), so the quotients are rounded alike.  Groups of two, so that a wave
+// of two rays a lane has them whole: four r2 a reciprocal take half a slot less a
+// quotient and give 2048^2 rays and 105 lenses no less time (261 us against 260),
+// but calls of 1e5 rays and 1e4 lenses 2.5 ms instead of 1.1.
 template <bool UNIT>
-__device__ __forceinline__ void quotient4(double m, const double *r2, double *w)
+__device__ __forceinline__ void quotient2(double m, const double *r2, double *w)
 {
-    const double p1 = r2[0] * r2[1], p2 = p1 * r2[2], p = p2 * r2[3];
+    const double p = r2[0] * r2[1];
     double v = __builtin_amdgcn_rcp(p);
     v = fma(v, fma(-p, v, 1.0), v);
-    double e[4];
-    e[3] = v * p2;
-    v *= r2[3];
-    e[2] = v * p1;
-    v *= r2[2];
-    e[1] = v * r2[0];
-    e[0] = v * r2[1];
+    const double e[2] = {v * r2[1], v * r2[0]};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 2; ++k) {
         const double q = UNIT ? e[k] : m * e[k];
         w[k] = fma(e[k], fma(-r2[k], q, m), q);
     }
@@ -144,7 +141,8 @@ struct Stage64 {
     double m[UNIT ? 1 : kLens64];
 };
 
-// One lens for a lane's R rays of one row at d2 = theta_2 - y, |d2| >= kNear64.
+// One lens for a lane's R rays of one row at d2 = theta_2 - y, |d2| >= kNear64;
+// rays 2 h and 2 h + 1 share a reciprocal.
 template <bool UNIT, int R>
 __device__ __forceinline__ void row_lens_far(double x, double d2, double m, const double *t1,
                                              double *s1, double *s2)
@@ -156,10 +154,10 @@ __device__ __forceinline__ void row_lens_far(double x, double d2, double m, cons
         d1[k] = t1[k] - x;
         r2[k] = fma(d1[k], d1[k], q2);
     }
-    if constexpr (R == 4) quotient4<UNIT>(m, r2, w);
+    if constexpr (R == 1) w[0] = quotient<UNIT>(m, r2[0]);
     else
 #pragma unroll
-        for (int k = 0; k < R; ++k) w[k] = quotient<UNIT>(m, r2[k]);
+        for (int k = 0; k < R; k += 2) quotient2<UNIT>(m, r2 + k, w + k);
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         s1[k] = fma(w[k], d1[k], s1[k]);
@@ -186,27 +184,71 @@ __device__ __forceinline__ void row_lens(const Stage64<UNIT> &sm, int t, const d
     }
 }
 
-// The lens sums of a lane's R rays (r0 + 64 k, k < R; R = 1 or 4), every lens
-// in packed order.  tame: the plan's lenses and masses allow quotient()
-// (irs_plan).  Where all the wave's rays lie in one row, theta_2 - y_i and its
-// square are taken once for the lane's R rays.
-//
-// Bound by FP64 issue: with four rays a lane, per ray and lens about 2.5
-// slots (a slot: one FMA) of offsets and r^2, 5.75 of the quotient (one
-// reciprocal for four rays) and 2 of the sums, against about 24 with the IEEE
-// division and one ray a lane.  2048^2 rays, 105 lenses: kernel 479 -> 320 us (one ray a
-// lane 362) with the sheet's closed form, once a ray, about 90 of it; 268 now.
+// The staged lenses for a lane's R rays (1, or pairs) of the row t2, where the
+// plan is tame (irs_plan_s::tame: lenses and masses allow quotient()):
+// theta_2 - y_i and its square are taken once for the R rays.  Four lenses a step,
+// against two: 1,000 to 65,000 rays and 1e4 lenses 750 against 1,020 us.
 template <bool UNIT, int R>
-__device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const DevGeom &g,
-                                          const double *__restrict__ lx,
-                                          const double *__restrict__ ly,
-                                          const double *__restrict__ lm, int32_t nl, bool tame,
-                                          const double *t1, const double *t2, bool one_row,
-                                          double *s1, double *s2)
+__device__ __forceinline__ void row_lenses(const Stage64<UNIT> &sm, int cnt, const double *t1,
+                                           double t2, double *s1, double *s2)
+{
+    constexpr int S = 4;
+    int t = 0;
+    for (; t + S <= cnt; t += S) {
+        double2 z[S];
+        double d[S], m[S], least = INFINITY;
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            z[u] = sm.xy[t + u];
+            m[u] = UNIT ? 1.0 : sm.m[t + u];
+            d[u] = t2 - z[u].y;
+            least = fmin(least, fabs(d[u]));
+        }
+        if (__builtin_expect(least < kNear64, 0)) {
+#pragma unroll 1
+            for (int u = 0; u < S; ++u) row_lens<UNIT, R>(sm, t + u, t1, t2, s1, s2);
+        } else {
+#pragma unroll
+            for (int u = 0; u < S; ++u) row_lens_far<UNIT, R>(z[u].x, d[u], m[u], t1, s1, s2);
+        }
+    }
+    for (; t < cnt; ++t) row_lens<UNIT, R>(sm, t, t1, t2, s1, s2);
+}
+
+// The staged lenses for the first n of a lane's R rays (t1[k], t2), each with
+// its own quotient (what row_lenses<UNIT, 1> gives it, bit for bit).
+template <bool UNIT, int R>
+__device__ __forceinline__ void ray_lenses(const Stage64<UNIT> &sm, int cnt, bool tame, int n,
+                                           const double *t1, double t2, double *s1, double *s2)
+{
+    for (int t = 0; t < cnt; ++t) {
+        const double2 z = sm.xy[t];
+        const double m = UNIT ? 1.0 : sm.m[t];
+        const double d2 = t2 - z.y;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            if (k >= n) break;
+            const double d1 = t1[k] - z.x;
+            const double r2 = fma(d1, d1, d2 * d2);
+            if (__builtin_expect(tame && fabs(d2) >= kNear64, 1)) {
+                const double w = quotient<UNIT>(m, r2);
+                s1[k] = fma(w, d1, s1[k]);
+                s2[k] = fma(w, d2, s2[k]);
+            } else {
+                term_any(d1, r2, d2, m, s1[k], s2[k]);
+            }
+        }
+    }
+}
+
+// Every lens in packed order, kLens64 at a time through LDS: take(cnt) after
+// each stage.  Called by the whole workgroup.
+template <bool UNIT, class F>
+__device__ __forceinline__ void lens_stages(Stage64<UNIT> &sm, const double *__restrict__ lx,
+                                            const double *__restrict__ ly,
+                                            const double *__restrict__ lm, int32_t nl, F take)
 {
     const int tid = threadIdx.x;
-#pragma unroll
-    for (int k = 0; k < R; ++k) s1[k] = s2[k] = 0.0;
     for (int32_t base = 0; base < nl; base += kLens64) {
         __syncthreads();
         if (base + tid < nl) {
@@ -214,45 +256,13 @@ __device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const DevGeom &g,
             if (!UNIT) sm.m[tid] = lm[base + tid];
         }
         __syncthreads();
-        const int cnt = min(kLens64, nl - base);
-        if (tame && one_row) {                               // wave-uniform
-            int t = 0;
-            // two lenses a step: their chains overlap
-            for (; t + 1 < cnt; t += 2) {
-                const double2 za = sm.xy[t], zb = sm.xy[t + 1];
-                const double da = t2[0] - za.y, db = t2[0] - zb.y;
-                if (__builtin_expect(fmin(fabs(da), fabs(db)) < kNear64, 0)) {
-                    row_lens<UNIT, R>(sm, t, t1, t2[0], s1, s2);
-                    row_lens<UNIT, R>(sm, t + 1, t1, t2[0], s1, s2);
-                } else {
-                    row_lens_far<UNIT, R>(za.x, da, UNIT ? 1.0 : sm.m[t], t1, s1, s2);
-                    row_lens_far<UNIT, R>(zb.x, db, UNIT ? 1.0 : sm.m[t + 1], t1, s1, s2);
-                }
-            }
-            if (t < cnt) row_lens<UNIT, R>(sm, t, t1, t2[0], s1, s2);
-        } else {
-            for (int t = 0; t < cnt; ++t) {
-                const double2 z = sm.xy[t];
-                const double m = UNIT ? 1.0 : sm.m[t];
-#pragma unroll
-                for (int k = 0; k < R; ++k) {
-                    const double d1 = t1[k] - z.x, d2 = t2[k] - z.y;
-                    const double r2 = fma(d1, d1, d2 * d2);
-                    if (__builtin_expect(tame && fabs(d2) >= kNear64, 1)) {
-                        const double w = quotient<UNIT>(m, r2);
-                        s1[k] = fma(w, d1, s1[k]);
-                        s2[k] = fma(w, d2, s2[k]);
-                    } else {
-                        term_any(d1, r2, d2, m, s1[k], s2[k]);
-                    }
-                }
-            }
-        }
+        take(min(kLens64, nl - base));
     }
 }
 
 // The rectangle's sheet integrals along a ray row, as a series about a point
-// (x0, y) of it (T_0 in two parts, the larger at T[kSheetTerms]): with w = z - corner, S = I2 + i I1 has d^2 S/dx^2 = sum +-1/w and
+// (x0, y) of it (T_0 in two parts, the larger at T[kSheetTerms]): with
+// w = z - corner, S = I2 + i I1 has d^2 S/dx^2 = sum +-1/w and
 // dS/dx = sum +-(ln|w| + i atan(v/u)) (signs and terms of sheet_unit), so
 //     S(x0 + s d) = sum_n T_n d^n,   T_n = -s/(n (n-1)) sum +-(-s/w)^(n-1), n >= 2.
 // Lane = 16 corner + m takes its corner's terms and the powers m, m + 16, m + 32.
@@ -262,7 +272,7 @@ __device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const DevGeom &g,
 //
 // The closed form (four logarithms and arctangents) is 560 of the 1940 VALU
 // instructions of a ray in a map of 105 lenses; the series is about 150 where a
-// wave's 256 rays are one row.  2048^2 rays, 105 lenses: 303 -> 263 us.  The
+// wave takes a block of 256 rays.  2048^2 rays, 105 lenses: 303 -> 263 us.  The
 // closed form's rounding (corner terms of 100 and more that cancel) is most of a
 // deflection's error; T_0 carries its roundings along, so the error against 64
 // more bits falls: mean 2.4e-14 -> 1.0e-14 (1.2e6 rays, 915 lenses).
@@ -363,82 +373,171 @@ __device__ __forceinline__ int sheet_row_series(const DevGeom &g, double x0, dou
     return __builtin_amdgcn_readfirstlane(min(kSheetTerms, 2 + (int)ceilf(59.0f / fmaxf(bits, 1.0f))));
 }
 
-// A workgroup takes kThreads R consecutive rays, a wave 64 R of them.
-template <bool UNIT, int R>
-__global__ __launch_bounds__(kThreads) void k_direct_f64(
+// One ray a lane, a workgroup's rays consecutive ones from r0 (clamped to r1 - 1).
+// A ray's sums do not depend on which rays share its wave.
+template <bool UNIT>
+__device__ __forceinline__ void direct_rays(Stage64<UNIT> &sm, const DevGeom &g,
+                                            const double *__restrict__ lx,
+                                            const double *__restrict__ ly,
+                                            const double *__restrict__ lm, int32_t nl, bool tame,
+                                            int64_t r0, int64_t r1, int64_t out_base, double *a1o,
+                                            double *a2o, int64_t *pixo, uint32_t *counts,
+                                            unsigned long long *landed)
+{
+    const int lane = threadIdx.x % kWave;
+    const int64_t w0 = r0 + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) * kWave;
+    // the wave's first ray's row; most waves stay in it
+    const int64_t j0 = w0 / g.nx, i0 = w0 - j0 * g.nx;
+    const bool one_row = i0 + kWave <= g.nx;
+    int64_t i = i0 + lane, j = j0;
+    if (!one_row) {
+        const int64_t r = min(w0 + lane, r1 - 1);
+        j = r / g.nx;
+        i = r - j * g.nx;
+    }
+    const double t1 = ray_x(g, i), t2 = ray_y(g, j);
+    double s1 = 0.0, s2 = 0.0;
+    lens_stages<UNIT>(sm, lx, ly, lm, nl, [&](int cnt) {
+        if (tame && one_row) row_lenses<UNIT, 1>(sm, cnt, &t1, t2, &s1, &s2);   // wave-uniform
+        else ray_lenses<UNIT, 1>(sm, cnt, tame, 1, &t1, t2, &s1, &s2);
+    });
+    double a1, a2;
+    int32_t pix;
+    assemble(g, t1, t2, s1, s2, a1, a2, pix);
+    emit(w0 + lane < r1, w0 + lane - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
+}
+
+template <bool UNIT>
+__global__ __launch_bounds__(kThreads, 7) void k_direct_f64(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
     const double *__restrict__ lm, int32_t nl, bool tame, int64_t r_begin, int64_t r_end,
     int64_t out_base, double *a1o, double *a2o, int64_t *pixo, uint32_t *counts,
     unsigned long long *landed)
 {
     __shared__ Stage64<UNIT> sm;
+    direct_rays<UNIT>(sm, g, lx, ly, lm, nl, tame, r_begin + (int64_t)blockIdx.x * kThreads, r_end,
+                      out_base, a1o, a2o, pixo, counts, landed);
+}
+
+// Blocks: the kBlock columns from a multiple of kBlock of one ray row, in four
+// groups of 64 (lane: columns lane + 64 k).  Rays of groups 0 and 1, and of 2 and
+// 3, share a reciprocal where both groups hold columns of the grid, the others
+// take their own, and all take the sheet as the series about the block's middle
+// where sheet_row_series allows it, else in closed form.  Which of these a ray
+// takes, and its partner, depend on the plan and the ray alone, so that maps,
+// bands of rows, ranges of deflections and batches agree bit for bit.
+//
+// A wave takes R of a block's groups: all four, or, for calls of few blocks
+// (kFewBlocks), two.  Bound by FP64 issue: with four rays a lane, per ray and lens
+// about 2.5 slots (a slot: one FMA) of offsets and r^2, 6.2 of the quotient and 2 of
+// the sums, against about 24 with the IEEE division and one ray a lane.  2048^2
+// rays, 105 lenses, whole call: 425 us with one ray a lane, the division and the
+// sheet in closed form, 260 now; 275 with waves of 256 consecutive rays, of which
+// those that pass a row's end do without the series and the shared distances.
+struct BlockLds {
+    double2 T[kWaves][kSheetTerms + 1];
+};
+
+// unit: the wave's, of those [.., u1) counted along the rows, 4/R a block; of its
+// rays those in [r_begin, r_end) are put out
+template <bool UNIT, int R>
+__device__ __forceinline__ void direct_block(Stage64<UNIT> &sm, BlockLds &bl, const DevGeom &g,
+                                             const double *__restrict__ lx,
+                                             const double *__restrict__ ly,
+                                             const double *__restrict__ lm, int32_t nl, bool tame,
+                                             int64_t unit, int64_t u1, int64_t r_begin,
+                                             int64_t r_end, int64_t out_base, double *a1o,
+                                             double *a2o, int64_t *pixo, uint32_t *counts,
+                                             unsigned long long *landed)
+{
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
-    const int64_t w0 = r_begin + ((int64_t)blockIdx.x * kWaves + wave) * (kWave * R);
-    double t1[R], t2[R], s1[R], s2[R];
-    // the wave's first ray's row; most waves stay in it
-    const int64_t j0 = w0 / g.nx, i0 = w0 - j0 * g.nx;
-    const bool one_row = i0 + kWave * R <= g.nx;
+    const int64_t blk = unit / (4 / R), nb = (g.nx + kBlock - 1) / kBlock;
+    const int64_t j = blk / nb, b0 = (blk - j * nb) * kBlock;
+    const int64_t c0 = b0 + unit % (4 / R) * (kWave * R);  // the wave's first column
+    // the wave's groups that hold columns; wave-uniform (every wave meets the barriers)
+    const int n = unit < u1 ? (int)max<int64_t>(0, min<int64_t>(R, (g.nx - c0 + kWave - 1) / kWave)) : 0;
+    const double t2 = ray_y(g, j);
+    double t1[R], s1[R], s2[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-        int64_t i = i0 + lane + kWave * k, j = j0;
-        if (!one_row) {
-            const int64_t r = min(w0 + lane + kWave * k, r_end - 1);
-            j = r / g.nx;
-            i = r - j * g.nx;
-        }
-        t1[k] = ray_x(g, i);
-        t2[k] = ray_y(g, j);
+        t1[k] = ray_x(g, c0 + kWave * k + lane);
+        s1[k] = s2[k] = 0.0;
     }
-    lens_sums<UNIT, R>(sm, g, lx, ly, lm, nl, tame, t1, t2, one_row, s1, s2);
+    lens_stages<UNIT>(sm, lx, ly, lm, nl, [&](int cnt) {
+        if (!tame) {
+            ray_lenses<UNIT, R>(sm, cnt, tame, n, t1, t2, s1, s2);
+        } else if (n == R) {
+            row_lenses<UNIT, R>(sm, cnt, t1, t2, s1, s2);
+        } else {
+            if (R > 2 && n >= 2) row_lenses<UNIT, 2>(sm, cnt, t1, t2, s1, s2);
+            if (n == 1) row_lenses<UNIT, 1>(sm, cnt, t1, t2, s1, s2);
+            if (R > 2 && n == 3) row_lenses<UNIT, 1>(sm, cnt, t1 + R - 2, t2, s1 + R - 2, s2 + R - 2);
+        }
+    });
+    if (n == 0) return;
     double I1[R] = {}, I2[R] = {};
     int terms = 0;                                         // wave-uniform
-    if constexpr (R == 4) {
-        __shared__ double2 s_T[kWaves][kSheetTerms + 1];
-        // (deflections keep the closed form, so that a ray's do not depend on the
-        // range they are asked in)
-        if (counts && g.sheet == 1 && one_row) {
-            const double x0 = ray_x(g, i0 + kWave * R / 2), s = kWave * R / 2 * g.ray_dx;
-            terms = sheet_row_series(g, x0, t2[0], s, s_T[wave]);
-            if (terms) {
-                const double is = 1.0 / s;
-                double d[R];
+    if (g.sheet == 1) {
+        const double x0 = ray_x(g, b0 + kBlock / 2), s = kBlock / 2 * g.ray_dx;
+        double2 *T = bl.T[wave];
+        terms = sheet_row_series(g, x0, t2, s, T);
+        if (terms) {
+            const double is = 1.0 / s;
+            double d[R];
 #pragma unroll
-                for (int k = 0; k < R; ++k) d[k] = (t1[k] - x0) * is;
-                for (int n = terms - 1; n >= 0; --n) {
-                    const double2 T = s_T[wave][n];
-#pragma unroll
-                    for (int k = 0; k < R; ++k) {
-                        I1[k] = fma(I1[k], d[k], T.y);
-                        I2[k] = fma(I2[k], d[k], T.x);
-                    }
-                }
-                const double2 T = s_T[wave][kSheetTerms];
+            for (int k = 0; k < R; ++k) d[k] = (t1[k] - x0) * is;
+            for (int m = terms - 1; m >= 0; --m) {
+                const double2 t = T[m];
 #pragma unroll
                 for (int k = 0; k < R; ++k) {
-                    I1[k] += T.y;
-                    I2[k] += T.x;
+                    I1[k] = fma(I1[k], d[k], t.y);
+                    I2[k] = fma(I2[k], d[k], t.x);
                 }
+            }
+            const double2 t = T[kSheetTerms];
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                I1[k] += t.y;
+                I2[k] += t.x;
             }
         }
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-        const int64_t r = w0 + lane + kWave * k;
+        const int64_t c = c0 + kWave * k + lane, r = j * g.nx + c;
         double a1, a2;
         int32_t pix;
-        assemble(g, t1[k], t2[k], s1[k], s2[k], a1, a2, pix, terms > 0, I1[k], I2[k]);
-        emit(r < r_end, r - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
+        assemble(g, t1[k], t2, s1[k], s2[k], a1, a2, pix, terms > 0, I1[k], I2[k]);
+        emit(c < g.nx && r >= r_begin && r < r_end, r - out_base, a1, a2, pix, a1o, a2o, pixo,
+             counts, landed);
     }
 }
 
-// Persistent FP64 form for batches: item = 256 consecutive rays of a map.
+template <bool UNIT, int R>
+__global__ __launch_bounds__(kThreads) void k_direct_f64_blocks(
+    DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
+    const double *__restrict__ lm, int32_t nl, bool tame, int64_t u0, int64_t u1, int64_t r_begin,
+    int64_t r_end, int64_t out_base, double *a1o, double *a2o, int64_t *pixo, uint32_t *counts,
+    unsigned long long *landed)
+{
+    __shared__ Stage64<UNIT> sm;
+    __shared__ BlockLds bl;
+    const int64_t unit = u0 + (int64_t)blockIdx.x * kWaves +
+                         __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    direct_block<UNIT, R>(sm, bl, g, lx, ly, lm, nl, tame, unit, u1, r_begin, r_end, out_base, a1o,
+                          a2o, pixo, counts, landed);
+}
+
+// Persistent FP64 form for batches: item = four blocks, or 256 consecutive rays, of
+// a map (direct_items).
 template <bool UNIT>
-__global__ __launch_bounds__(kThreads) void k_direct_f64_queue(
+__global__ __launch_bounds__(kThreads, 4) void k_direct_f64_queue(
     const DirectArgs *__restrict__ maps, const int64_t *__restrict__ item_start, int32_t nmaps,
     unsigned long long *cursor)
 {
     __shared__ Stage64<UNIT> sm;
+    __shared__ BlockLds bl;
     __shared__ long long s_item;
     const int tid = threadIdx.x;
     const int64_t total = item_start[nmaps];
@@ -455,19 +554,36 @@ __global__ __launch_bounds__(kThreads) void k_direct_f64_queue(
             else hi = mid - 1;
         }
         const DirectArgs &a = maps[lo];
-        const DevGeom &g = a.g;
-        const int64_t r = (item - item_start[lo]) * kThreads + tid;
-        const bool valid = r < g.nx * g.ny;
-        const int64_t rr = valid ? r : 0;
-        const double t1 = ray_x(g, rr % g.nx), t2 = ray_y(g, rr / g.nx);
-        double s1, s2;
-        lens_sums<UNIT, 1>(sm, g, a.lx, a.ly, a.lm, a.nl, a.tame != 0, &t1, &t2, false, &s1, &s2);
-        double a1, a2;
-        int32_t pix;
-        assemble(g, t1, t2, s1, s2, a1, a2, pix);
-        emit(valid, 0, a1, a2, pix, nullptr, nullptr, nullptr, a.counts, a.landed);
+        const int64_t n = item - item_start[lo];
+        if (a.blocks)
+            direct_block<UNIT, 4>(sm, bl, a.g, a.lx, a.ly, a.lm, a.nl, a.tame != 0,
+                                      n * kWaves + __builtin_amdgcn_readfirstlane(tid / kWave),
+                                      a.blocks, a.ray_first, a.ray_last, 0, nullptr, nullptr,
+                                      nullptr, a.counts, a.landed);
+        else
+            direct_rays<UNIT>(sm, a.g, a.lx, a.ly, a.lm, a.nl, a.tame != 0, n * kThreads,
+                              a.ray_last, 0, nullptr, nullptr, nullptr, a.counts, a.landed);
     }
 }
+
+// Blocks of the whole map, for plans of 2^20 rays and more in rows of more than 192
+// rays; 0: one ray a lane.  A property of the plan, so that every call on it and
+// every batch with it takes a ray in one way.  With fewer rays four a lane
+// would be under four waves a SIMD, and a row of 193 rays is the shortest that
+// fills four groups: blocks then leave at most a third of their lanes idle.
+int64_t direct_blocks(const irs_plan_s *p)
+{
+    const DevGeom &g = p->dg;
+    if (p->params.precision != IRS_FP64 || g.nx <= 3 * kWave || g.nx * g.ny < ((int64_t)1 << 20))
+        return 0;
+    return (g.nx + kBlock - 1) / kBlock * g.ny;
+}
+
+// Calls of at most this many blocks (four waves a SIMD) take two of a block's groups
+// a wave: 4e5 rays (1,600 blocks) and 1e4 lenses 2.05 against 2.21 ms, 1.3e6 rays of a
+// map of 262 rows (5,240) 1137 lenses 643 against 688 us, but 4e6 rays (16,800),
+// 105 lenses 275 against 260.
+constexpr int64_t kFewBlocks = 4096;
 
 // -------------------------------------------------------------------------
 // FP32 with compensation
@@ -816,33 +932,50 @@ irs_status launch_direct(irs_plan_s *p, const RaySel &sel)
     if (p->params.precision == IRS_FP64) {
         const int64_t rb = std::max(sel.row0 * g.nx, sel.ray_first);
         const int64_t re = std::min(sel.row1 * g.nx, sel.ray_last);
-        const int64_t chunk = (int64_t)kThreads << 22;   // rays per launch
-        const bool tame = p->tame;
-        // four rays a lane share the lens loads, theta_2 - y and a reciprocal
-        // (2048^2 rays: 320 against 362 us); with fewer than 2^20 rays that
-        // would be under four waves a SIMD
-        const int64_t per = re - rb >= kRays4 ? 4 : 1;
         if (sel.stats) sel.stats->direct_pairs += std::max<int64_t>(0, re - rb) * (int64_t)nl;
-        for (int64_t c0 = rb; c0 < re; c0 += chunk) {
-            const int64_t c1 = std::min(re, c0 + chunk);
-            const unsigned nb = (unsigned)((c1 - c0 + kThreads * per - 1) / (kThreads * per));
+        if (re <= rb) return IRS_OK;
+        const bool tame = p->tame;
+        // the call's units: blocks, half blocks or rays
+        const bool blocks = direct_blocks(p) > 0;
+        const int64_t nb = (g.nx + kBlock - 1) / kBlock;
+        int64_t u0 = rb, u1 = re;
+        bool few = false;
+        if (blocks) {
+            u0 = rb / g.nx * nb + rb % g.nx / kBlock;
+            u1 = (re - 1) / g.nx * nb + (re - 1) % g.nx / kBlock + 1;
+            few = u1 - u0 <= kFewBlocks;
+            if (few) {
+                u0 *= 2;
+                u1 *= 2;
+            }
+        }
+        const int64_t chunk = (int64_t)1 << (blocks ? 22 : 30);      // units a launch
+        const int64_t per = blocks ? kWaves : kThreads;              // ... a workgroup
+        for (int64_t c0 = u0; c0 < u1; c0 += chunk) {
+            const int64_t c1 = std::min(u1, c0 + chunk);
+            const unsigned grid = (unsigned)((c1 - c0 + per - 1) / per);
             if (sel.stats) {
                 irs_status st = sel.stats->begin(s, 1);
                 if (st != IRS_OK) return st;
                 sel.stats->n_rays++;
             }
-#define IRS_D64(U, R)                                                                          \
-    hipLaunchKernelGGL((k_direct_f64<U, R>), dim3(nb), dim3(kThreads), 0, s, g, p->d_x, p->d_y, \
-                       p->d_m, nl, tame, c0, c1, sel.ray_first, sel.alpha1, sel.alpha2,        \
-                       sel.pixel, sel.counts, sel.landed)
-            if (unit) {
-                if (per == 4) IRS_D64(true, 4);
-                else IRS_D64(true, 1);
-            } else {
-                if (per == 4) IRS_D64(false, 4);
-                else IRS_D64(false, 1);
-            }
+#define IRS_OUT sel.ray_first, sel.alpha1, sel.alpha2, sel.pixel, sel.counts, sel.landed
+#define IRS_D64(U)                                                                             \
+    do {                                                                                       \
+        if (few)                                                                               \
+            hipLaunchKernelGGL((k_direct_f64_blocks<U, 2>), dim3(grid), dim3(kThreads), 0, s, \
+                               g, p->d_x, p->d_y, p->d_m, nl, tame, c0, c1, rb, re, IRS_OUT);  \
+        else if (blocks)                                                                       \
+            hipLaunchKernelGGL((k_direct_f64_blocks<U, 4>), dim3(grid), dim3(kThreads), 0, s, \
+                               g, p->d_x, p->d_y, p->d_m, nl, tame, c0, c1, rb, re, IRS_OUT);  \
+        else                                                                                   \
+            hipLaunchKernelGGL(k_direct_f64<U>, dim3(grid), dim3(kThreads), 0, s, g, p->d_x,   \
+                               p->d_y, p->d_m, nl, tame, c0, c1, IRS_OUT);                     \
+    } while (0)
+            if (unit) IRS_D64(true);
+            else IRS_D64(false);
 #undef IRS_D64
+#undef IRS_OUT
             IRS_HIP(hipGetLastError());
             if (sel.stats) {
                 irs_status st = sel.stats->end(s);
@@ -925,7 +1058,10 @@ const char *direct_variant_name(int v)
 int64_t direct_items(const irs_plan_s *p, int variant)
 {
     const DevGeom &g = p->dg;
-    if (p->params.precision == IRS_FP64) return (g.nx * g.ny + kThreads - 1) / kThreads;
+    if (p->params.precision == IRS_FP64) {
+        const int64_t nb = direct_blocks(p);
+        return nb > 0 ? (nb + kWaves - 1) / kWaves : (g.nx * g.ny + kThreads - 1) / kThreads;
+    }
     const int64_t TY = direct_variant_rows(variant);
     return ((g.nx + kTX - 1) / kTX) * ((g.ny + TY - 1) / TY);
 }
@@ -942,7 +1078,7 @@ DirectArgs direct_args_full(const irs_plan_s *p, int variant, uint32_t *counts,
     a.nl = (int32_t)p->n_lens;
     a.tame = p->tame ? 1 : 0;
     a.ntx = (p->dg.nx + kTX - 1) / kTX;
-    a.ty0 = 0;
+    a.blocks = direct_blocks(p);
     a.row0 = 0;
     a.row1 = p->dg.ny;
     a.ray_first = 0;

@@ -35,7 +35,8 @@ struct DirectArgs {
     const int32_t *cell_start;
     int32_t nl;
     int32_t tame;                        // irs_plan_s::tame (FP64 sums)
-    int64_t ntx, ty0;                    // tiles per row; first tile row (queue kernels)
+    int64_t ntx;                         // tiles per row (FP32 queue kernels)
+    int64_t blocks;                      // blocks of the map (FP64; 0: one ray a lane)
     int64_t row0, row1;                  // ray rows computed
     int64_t ray_first, ray_last;         // ray index range computed
     double *a1o, *a2o;                   // per-ray outputs (indexed r - ray_first) or
