@@ -563,7 +563,6 @@ static irs_status shoot(irs_plan_t plan, int64_t row0, int64_t nrows, uint32_t *
     sel.landed = plan->d_landed;
     st = run(plan, sel);
     if (st != IRS_OK) return st;
-    timer.stop();
     if (stats) interp_account(plan, cs);  // while the GPU works
     unsigned long long slots[kLandedSlots];
     IRS_HIP(hipMemcpyAsync(slots, plan->d_landed, sizeof slots, hipMemcpyDeviceToHost, s));
@@ -575,6 +574,7 @@ static irs_status shoot(irs_plan_t plan, int64_t row0, int64_t nrows, uint32_t *
         IRS_HIP(hipStreamSynchronize(s));
         for (size_t k = 0; k < tmp.size(); ++k) counts[k] += tmp[k];
     }
+    timer.stop();                         // ms_total covers the copies to the host
     IRS_HIP(hipStreamSynchronize(s));
     unsigned long long landed = 0;
     for (unsigned long long v : slots) landed += v;
