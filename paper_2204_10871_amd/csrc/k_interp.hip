@@ -2797,9 +2797,13 @@ irs_status interp_prepare(irs_plan_s *p)
 }
 
 // The sums over cells of the work recorded in cs.  Algorithmic FP64 flops:
-// expansions 10 + 8 P per lens and 8 PS P per re-expansion; level-2 points 44
-// per (point, ring lens) or, in the paper's form, distant lens, and 60 P for
-// the cell expansion's translation; level-3 rays 46 (Horner of C_0..C_4: 32,
+// expansions 10 + 8 P per lens and 8 PS P per re-expansion; level-2 points in
+// k_level2_cells 10 + 8 PE per ring lens of a cell, 48 PE per point of a cell's
+// quarter (the powers' step 8, four sums for each of five derivatives) and 58 per
+// point (its five values from the sums 40, the step to the rounded point 14, the
+// sheet 4), else 44 per (point, ring lens) or, in the paper's form, distant lens,
+// and 60 P for the cell expansion's translation (the few cells with the sheet's
+// closed form are counted like the others); level-3 rays 46 (Horner of C_0..C_4: 32,
 // sheet 2, macro term 6, beta 2, pixel 4) plus 10 per nearby lens (offsets 2,
 // r^2 3, m/r^2 1, products 2, sums 2).
 void interp_account(irs_plan_s *p, CallStats &cs)
@@ -2807,7 +2811,7 @@ void interp_account(irs_plan_s *p, CallStats &cs)
     if (cs.work.empty()) return;
     const DevGeom &g = p->dg;
     build_sat(p);
-    const int P = level2_order(p), PS = super_order(p);
+    const int P = level2_order(p), PS = super_order(p), PE = P > 0 ? ring_order(p) : 0;
     auto block = [&](int64_t cx, int64_t cy, int64_t r) {   // lenses in a (2r+1)^2 block
         return lenses_in(p, cx - r, cx + r + 1, cy - r, cy + r + 1);
     };
@@ -2838,13 +2842,16 @@ void interp_account(irs_plan_s *p, CallStats &cs)
             cs.level2_expand_flops += fl;
             cs.level2_flops += fl;
         } else if (w.kind == CallStats::kPoints) {
-            const int64_t q2 = (int64_t)g.q * g.q;
+            const int64_t q2 = (int64_t)g.q * g.q, hq = (g.q + 1) / 2;
             for (int64_t cy = w.a; cy <= w.b; ++cy)
                 for (int64_t cx = 0; cx < g.n1x; ++cx) {
                     const int64_t b3 = block(cx, cy, 1);
                     cs.level2_pairs += q2 * (p->n_lens - b3);
+                    const double ring = (double)(block(cx, cy, kRing) - b3);
                     if (P == 0) fl += 44.0 * (double)(q2 * (p->n_lens - b3));
-                    else fl += (double)q2 * (44.0 * (double)(block(cx, cy, kRing) - b3) + 60.0 * P);
+                    else if (PE > 0)
+                        fl += ring * (10.0 + 8.0 * PE) + (double)(hq * hq) * 48.0 * PE + 58.0 * (double)q2;
+                    else fl += (double)q2 * (44.0 * ring + 60.0 * P);
                 }
             if (P == 0) cs.level2_expand_flops += fl;
             cs.level2_flops += fl;
