@@ -2489,11 +2489,12 @@ void closed_extent(const DevGeom &g, int32_t fold, int32_t &nbx, int32_t &nby)
 // rule of level2_order at the ratio of the furthest level-2 point from the
 // cell's centre to the nearest lens outside the 3 x 3 block; 0: the ring lenses
 // are summed at every point instead (grids coarser than kCellsMinQ, denser
-// rings than the staging holds, or no order up to kPEMax).
+// rings than the staging holds, no order up to kPEMax, or masses near the ends of
+// the exponent range: n! times a term of the series overflows from 1e225 on).
 int32_t ring_order(irs_plan_s *p)
 {
     const DevGeom &g = p->dg;
-    if (g.q < kCellsMinQ || !ring_fits(p)) return 0;
+    if (g.q < kCellsMinQ || !p->tame || !ring_fits(p)) return 0;
     const double e = 0.5 * (double)(g.q - 1) / (double)g.q;
     const double rho = e * std::sqrt(g.w1 * g.w1 + g.h1 * g.h1) / (1.5 * std::min(g.w1, g.h1));
     for (int P = 48; P <= kPEMax; P += 4) {
