@@ -620,7 +620,9 @@ irs_status irs_shoot_map(irs_plan_t plan, uint32_t *counts, irs_map_stats *stats
         set_error("irs_shoot_map: NULL plan");
         return IRS_E_INVALID;
     }
-    level2_reset(plan);          // a whole map computes every far-field expansion itself
+    // a whole map computes every expansion and level-2 coefficient itself; a learned
+    // plan's corner table, which is the plan's own data, stays (launch_learned)
+    level2_reset(plan);
     return shoot(plan, 0, plan->geo.info.ny, counts, stats, flags, true, "irs_shoot_map");
 }
 

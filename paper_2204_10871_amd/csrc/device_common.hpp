@@ -43,18 +43,6 @@ __device__ __forceinline__ double ray_y(const DevGeom &g, int64_t j)
     return g.b1 + ((double)j + 0.5) * g.ray_dy;
 }
 
-// Level-2 column/row of ray column i / row j: the level-2 grid splits the
-// rectangle into n1x*q columns, so the ray at (i + 1/2) ray_dx lies in column
-// floor((2i+1) n1x q / (2 nx)) -- exact integer arithmetic, no rounding.
-__device__ __forceinline__ int64_t level2_col(const DevGeom &g, int64_t i)
-{
-    return ((2 * i + 1) * (int64_t)g.n1x * g.q) / (2 * g.nx);
-}
-__device__ __forceinline__ int64_t level2_row(const DevGeom &g, int64_t j)
-{
-    return ((2 * j + 1) * (int64_t)g.n1y * g.q) / (2 * g.ny);
-}
-
 // floor(num / den) for 0 <= num < 2^53, den > 0, without 64-bit integer division
 __device__ __forceinline__ int64_t floor_div(int64_t num, int64_t den)
 {

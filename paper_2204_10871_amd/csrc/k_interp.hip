@@ -2069,20 +2069,20 @@ __device__ __forceinline__ void level3_corner_ray(const L3Map &m, int64_t i0, in
     }
 }
 
-// The corner cells' rays of a map, one per lane (blockIdx.y: the corner).
-// One map: column tile tx = blockIdx.x mod ntx_pad, rows of the kL3Waves waves
-// from wr0 + kL3Waves (blockIdx.x / ntx_pad) (half as many entries for R = 4).
-// R = 4 maps have the corner cells' rays in their first workgroups, ncb a cell:
-// one launch fewer where launches count (a map of 1.2e5 rays 136 -> 129 us; with
-// per-ray outputs the registers it takes cost more, 22.9 against 20.7 us).  ntx_pad is a multiple of the 8 XCDs, which take consecutive
-// workgroups in turn, so a column tile runs on the same XCD in every tile row
-// and finds its level-2 coefficients and lenses in that XCD's L2.
 // workgroups of n corner cells at ncb each, padded to whole rounds of the XCDs
 __host__ __device__ constexpr uint32_t corner_grid(uint32_t ncb, int32_t n)
 {
     return (ncb * (uint32_t)n + kXcds - 1) / kXcds * kXcds;
 }
 
+// One map: column tile tx = blockIdx.x mod ntx_pad, rows of the kL3Waves waves
+// from wr0 + kL3Waves (blockIdx.x / ntx_pad) (half as many entries for R = 4).
+// R = 4 maps have the corner cells' rays in their first workgroups, ncb a cell:
+// one launch fewer where launches count (a map of 1.2e5 rays 136 -> 129 us; with
+// per-ray outputs the registers it takes cost more, 22.9 against 20.7 us).
+// ntx_pad is a multiple of the 8 XCDs, which take consecutive workgroups in
+// turn, so a column tile runs on the same XCD in every tile row and finds its
+// level-2 coefficients and lenses in that XCD's L2.
 template <bool UNIT, bool BIN, int R>
 __global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t wr0, int32_t ntx_pad,
                                                          uint32_t ncb)
@@ -2107,6 +2107,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_level3(L3Map m, int32_t wr0, in
                                                (int32_t)(b / (uint32_t)ntx_pad), &lds);
 }
 
+// The corner cells' rays of a map, one per lane (blockIdx.y: the corner).
 template <bool UNIT, bool BIN>
 __global__ __launch_bounds__(kThreads) void k_level3_corner(L3Map m)
 {
@@ -2174,7 +2175,15 @@ __global__ __launch_bounds__(kThreads) void k_level3_maps_corners(const L3Map *m
                                   (ci - m.corner_items[c]) * kThreads + threadIdx.x);
 }
 
-// first ray row j with level2_row(j) >= G (level2_row is non-decreasing)
+// Level-2 row of ray row j: the level-2 grid splits the rectangle into n1y q rows,
+// so the ray at (j + 1/2) ray_dy lies in row floor((2j+1) n1y q / (2 ny)) -- exact
+// integer arithmetic, no rounding.
+int64_t level2_row_host(const DevGeom &g, int64_t j)
+{
+    return ((2 * j + 1) * (int64_t)g.n1y * g.q) / (2 * g.ny);
+}
+
+// first ray row j with level2_row_host(j) >= G (it is non-decreasing in j)
 int64_t first_row_at(const DevGeom &g, int64_t G)
 {
     int64_t lo = 0, hi = g.ny;
@@ -2185,11 +2194,6 @@ int64_t first_row_at(const DevGeom &g, int64_t G)
         else lo = mid + 1;
     }
     return lo;
-}
-
-int64_t level2_row_host(const DevGeom &g, int64_t j)
-{
-    return ((2 * j + 1) * (int64_t)g.n1y * g.q) / (2 * g.ny);
 }
 
 }  // namespace
@@ -2939,8 +2943,6 @@ int corner_blocks(const irs_plan_s *p, int64_t jA, int64_t jB, int64_t c[4][4])
     return n;
 }
 
-// k_level3_corner over the rays of rows [jA, jB) in the rectangle's corner
-// cells (m: the band's launch arguments)
 // most workgroups that a corner cell's rays of rows [jA, jB) take; sets m.corner
 unsigned corner_groups(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
 {
@@ -2951,6 +2953,8 @@ unsigned corner_groups(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
     return (unsigned)((most + kThreads - 1) / kThreads);
 }
 
+// k_level3_corner over the rays of rows [jA, jB) in the rectangle's corner
+// cells (m: the band's launch arguments)
 irs_status launch_corners(irs_plan_s *p, L3Map &m, int64_t jA, int64_t jB)
 {
     const unsigned nb = corner_groups(p, m, jA, jB);
@@ -3079,9 +3083,9 @@ namespace {
 
 // Launches of at most this many waves of eight rows (what the chip holds at once:
 // five a SIMD) take waves of four: with slots to spare a wave's own length counts.
-// 3e5 per-ray outputs (1,400 waves) 26.5 -> 24.1 us a call, 4e6 48.7 -> 46.4; level
-// 3 of a map of 240 waves 24.2 -> 19.9 us, 2,000 25.9 -> 24.3, 4,800 27.2 -> 26.3,
-// but 8,200 33.2 -> 34.1 and 17,000 46.0 -> 49.8.
+// 3e5 per-ray outputs (1,400 waves) 23.0 -> 20.7 us a call; level 3 of a map of 240
+// waves 24.2 -> 19.9 us, 2,000 25.9 -> 24.3, 4,800 27.2 -> 26.3, but 8,200 33.2 ->
+// 34.1 and 17,000 46.0 -> 49.8.
 constexpr int64_t kHalfTiles = 5 * 1024;
 
 // Level 3 of one band of level-1 rows [c0, c1] whose coefficients are in

@@ -982,8 +982,6 @@ __global__ __launch_bounds__(kThreads) void k_learn_err(const float *__restrict_
     err_base[k] = sg * sqrtf(Tr * Tr + Ti * Ti);
 }
 
-// The learned path's column table: ray column i's square column
-// gxc = floor((i + 1/2) n1x qc / nx) and level-1 column gxc / qc.
 // What a ray row's rays share: theta_2, the square row, its edges and the
 // offset in it, the level-1 row.  Read with scalar loads.
 struct alignas(16) LearnRow {
@@ -993,7 +991,8 @@ struct alignas(16) LearnRow {
     int64_t pad_;
 };
 
-// Square and level-1 cell of every ray column (cols); the ray rows (rows).
+// The learned path's tables.  cols: ray column i's square column
+// gxc = floor((i + 1/2) n1x qc / nx) and level-1 column gxc / qc.  rows: the ray rows.
 __global__ __launch_bounds__(kThreads) void k_learn_cols(DevGeom g, LearnGeom lg,
                                                          int2 *__restrict__ cols,
                                                          LearnRow *__restrict__ rows)
@@ -1043,10 +1042,11 @@ __global__ __launch_bounds__(kThreads) void k_ltab_eval(const float *__restrict_
 //
 // Bound by vector issue and LDS reads: a ray reads 256 bytes of the table
 // (four nodes), which at 64 bytes a node met four-way bank conflicts.  1e8 rays
-// through 9822 lenses: 2.80 -> 1.69 ms (the near pass with one reciprocal per
-// row and the conflicts before; the near pass is now about 0.57 of it, the
-// table 0.28, the binning 0.11, the squares and pixels the rest).  Four waves a
-// SIMD spill: 2.35 ms; items of 32 rows: 1.73 ms.
+// through 9822 lenses, whole calls with the corners resident: 2.86 ms with one
+// reciprocal per row and the conflicts, 1.58 now.  The two ray launches are 1.62 ms
+// on a card where the call takes 1.7; without the near pass 1.08, without the
+// table 1.41, without the binning 1.55.  Four waves a SIMD spill (2.35 against 1.69
+// ms), items of 32 rows 1.73.
 // ---------------------------------------------------------------------------
 constexpr int kL3Threads = 768;            // one workgroup a CU (its table), three waves a SIMD
 constexpr int kL3CornerThreads = 384;
@@ -1729,6 +1729,10 @@ irs_status launch_learned(irs_plan_s *p, const RaySel &sel)
     }
     CallStats *cs = sel.stats;
     const int ncu = device_cus();
+    // The corner table is the plan's, like the network's weight table: a function of
+    // its lenses and the network's grid alone, it is computed by the first call that
+    // meets a band and kept until another band or network takes its place
+    // (9822 lenses, coarse grid 16: 0.45 ms, once).
     for (int64_t c0 = cyA; c0 <= cyB; c0 += p->corner_rows_cap) {
         const int64_t c1 = std::min(cyB, c0 + p->corner_rows_cap - 1);
         if (!(p->corner_c0 <= c0 && c1 <= p->corner_c1)) {

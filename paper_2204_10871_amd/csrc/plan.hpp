@@ -88,8 +88,8 @@ struct irs_plan_s {
     void *d_tables = nullptr;             // one allocation: the four tables below
     void *d_rows = nullptr;               // level-3 row table (ny entries of 64 B)
     void *d_cols = nullptr;               // level-3 column table (nx entries of 16 B)
-    // level-3 tiles: column tiles of <= 64 ray columns, row tiles of <= 32 ray
-    // rows, following the level-1 cells where cells are wide (tall) enough
+    // level-3 tiles: column tiles of <= 64 ray columns and a wave's rows, <= 8,
+    // following the level-1 cells where cells are wide (tall) enough
     irs::TileSpan *d_tcol = nullptr, *d_trow = nullptr;
     std::vector<irs::TileSpan> h_tcol, h_trow;
     double *d_coef = nullptr;
