@@ -479,7 +479,10 @@ __device__ __forceinline__ void direct_block(Stage64<UNIT> &sm, BlockLds &bl, co
     double I1[R] = {}, I2[R] = {};
     int terms = 0;                                         // wave-uniform
     if (g.sheet == 1) {
-        const double x0 = ray_x(g, b0 + kBlock / 2), s = kBlock / 2 * g.ray_dx;
+        // about the middle of the block's columns of the grid: past the rectangle's
+        // edge the arctangents jump
+        const int64_t half = min<int64_t>(kBlock, g.nx - b0) / 2;
+        const double x0 = ray_x(g, b0 + half), s = (double)max<int64_t>(1, half) * g.ray_dx;
         double2 *T = bl.T[wave];
         terms = sheet_row_series(g, x0, t2, s, T);
         if (terms) {
