@@ -408,7 +408,7 @@ __device__ __forceinline__ void direct_rays(Stage64<UNIT> &sm, const DevGeom &g,
 }
 
 template <bool UNIT>
-__global__ __launch_bounds__(kThreads, 7) void k_direct_f64(
+__global__ __launch_bounds__(kThreads) void k_direct_f64(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
     const double *__restrict__ lm, int32_t nl, bool tame, int64_t r_begin, int64_t r_end,
     int64_t out_base, double *a1o, double *a2o, int64_t *pixo, uint32_t *counts,
