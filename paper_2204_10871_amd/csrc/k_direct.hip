@@ -215,11 +215,11 @@ __device__ __forceinline__ void row_lenses(const Stage64<UNIT> &sm, int cnt, con
     for (; t < cnt; ++t) row_lens<UNIT, R>(sm, t, t1, t2, s1, s2);
 }
 
-// The staged lenses for the first n of a lane's R rays (t1[k], t2), each with
-// its own quotient (what row_lenses<UNIT, 1> gives it, bit for bit).
+// The staged lenses for the first n of a lane's R rays of the row t2, by the
+// division: plans that are not tame.
 template <bool UNIT, int R>
-__device__ __forceinline__ void ray_lenses(const Stage64<UNIT> &sm, int cnt, bool tame, int n,
-                                           const double *t1, double t2, double *s1, double *s2)
+__device__ __forceinline__ void wild_lenses(const Stage64<UNIT> &sm, int cnt, int n,
+                                            const double *t1, double t2, double *s1, double *s2)
 {
     for (int t = 0; t < cnt; ++t) {
         const double2 z = sm.xy[t];
@@ -229,14 +229,7 @@ __device__ __forceinline__ void ray_lenses(const Stage64<UNIT> &sm, int cnt, boo
         for (int k = 0; k < R; ++k) {
             if (k >= n) break;
             const double d1 = t1[k] - z.x;
-            const double r2 = fma(d1, d1, d2 * d2);
-            if (__builtin_expect(tame && fabs(d2) >= kNear64, 1)) {
-                const double w = quotient<UNIT>(m, r2);
-                s1[k] = fma(w, d1, s1[k]);
-                s2[k] = fma(w, d2, s2[k]);
-            } else {
-                term_any(d1, r2, d2, m, s1[k], s2[k]);
-            }
+            term_any(d1, fma(d1, d1, d2 * d2), d2, m, s1[k], s2[k]);
         }
     }
 }
@@ -373,40 +366,60 @@ __device__ __forceinline__ int sheet_row_series(const DevGeom &g, double x0, dou
     return __builtin_amdgcn_readfirstlane(min(kSheetTerms, 2 + (int)ceilf(59.0f / fmaxf(bits, 1.0f))));
 }
 
-// One ray a lane, a workgroup's rays consecutive ones from r0 (clamped to r1 - 1).
-// A ray's sums do not depend on which rays share its wave.
+// The lens sums of a lane's ray (t1, t2), every lens in packed order; two lenses a
+// step, whose chains overlap, where the wave's rays lie in one row.
 template <bool UNIT>
-__device__ __forceinline__ void direct_rays(Stage64<UNIT> &sm, const DevGeom &g,
-                                            const double *__restrict__ lx,
-                                            const double *__restrict__ ly,
-                                            const double *__restrict__ lm, int32_t nl, bool tame,
-                                            int64_t r0, int64_t r1, int64_t out_base, double *a1o,
-                                            double *a2o, int64_t *pixo, uint32_t *counts,
-                                            unsigned long long *landed)
+__device__ __forceinline__ void lens_sums(Stage64<UNIT> &sm, const double *__restrict__ lx,
+                                          const double *__restrict__ ly,
+                                          const double *__restrict__ lm, int32_t nl, bool tame,
+                                          const double *t1, const double *t2, bool one_row,
+                                          double *s1, double *s2)
 {
-    const int lane = threadIdx.x % kWave;
-    const int64_t w0 = r0 + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) * kWave;
-    // the wave's first ray's row; most waves stay in it
-    const int64_t j0 = w0 / g.nx, i0 = w0 - j0 * g.nx;
-    const bool one_row = i0 + kWave <= g.nx;
-    int64_t i = i0 + lane, j = j0;
-    if (!one_row) {
-        const int64_t r = min(w0 + lane, r1 - 1);
-        j = r / g.nx;
-        i = r - j * g.nx;
+    const int tid = threadIdx.x;
+    s1[0] = s2[0] = 0.0;
+    for (int32_t base = 0; base < nl; base += kLens64) {
+        __syncthreads();
+        if (base + tid < nl) {
+            sm.xy[tid] = make_double2(lx[base + tid], ly[base + tid]);
+            if (!UNIT) sm.m[tid] = lm[base + tid];
+        }
+        __syncthreads();
+        const int cnt = min(kLens64, nl - base);
+        if (tame && one_row) {                               // wave-uniform
+            int t = 0;
+            for (; t + 1 < cnt; t += 2) {
+                const double2 za = sm.xy[t], zb = sm.xy[t + 1];
+                const double da = t2[0] - za.y, db = t2[0] - zb.y;
+                if (__builtin_expect(fmin(fabs(da), fabs(db)) < kNear64, 0)) {
+                    row_lens<UNIT, 1>(sm, t, t1, t2[0], s1, s2);
+                    row_lens<UNIT, 1>(sm, t + 1, t1, t2[0], s1, s2);
+                } else {
+                    row_lens_far<UNIT, 1>(za.x, da, UNIT ? 1.0 : sm.m[t], t1, s1, s2);
+                    row_lens_far<UNIT, 1>(zb.x, db, UNIT ? 1.0 : sm.m[t + 1], t1, s1, s2);
+                }
+            }
+            if (t < cnt) row_lens<UNIT, 1>(sm, t, t1, t2[0], s1, s2);
+        } else {
+            for (int t = 0; t < cnt; ++t) {
+                const double2 z = sm.xy[t];
+                const double m = UNIT ? 1.0 : sm.m[t];
+                const double d1 = t1[0] - z.x, d2 = t2[0] - z.y;
+                const double r2 = fma(d1, d1, d2 * d2);
+                if (__builtin_expect(tame && fabs(d2) >= kNear64, 1)) {
+                    const double w = quotient<UNIT>(m, r2);
+                    s1[0] = fma(w, d1, s1[0]);
+                    s2[0] = fma(w, d2, s2[0]);
+                } else {
+                    term_any(d1, r2, d2, m, s1[0], s2[0]);
+                }
+            }
+        }
     }
-    const double t1 = ray_x(g, i), t2 = ray_y(g, j);
-    double s1 = 0.0, s2 = 0.0;
-    lens_stages<UNIT>(sm, lx, ly, lm, nl, [&](int cnt) {
-        if (tame && one_row) row_lenses<UNIT, 1>(sm, cnt, &t1, t2, &s1, &s2);   // wave-uniform
-        else ray_lenses<UNIT, 1>(sm, cnt, tame, 1, &t1, t2, &s1, &s2);
-    });
-    double a1, a2;
-    int32_t pix;
-    assemble(g, t1, t2, s1, s2, a1, a2, pix);
-    emit(w0 + lane < r1, w0 + lane - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
 }
 
+// One ray a lane, a workgroup's rays consecutive ones.  A ray's sums do not depend
+// on which rays share its wave.  (Arrays of one ray: with scalars the compiler
+// takes 74 registers instead of 65, six waves a SIMD instead of seven.)
 template <bool UNIT>
 __global__ __launch_bounds__(kThreads) void k_direct_f64(
     DevGeom g, const double *__restrict__ lx, const double *__restrict__ ly,
@@ -415,8 +428,33 @@ __global__ __launch_bounds__(kThreads) void k_direct_f64(
     unsigned long long *landed)
 {
     __shared__ Stage64<UNIT> sm;
-    direct_rays<UNIT>(sm, g, lx, ly, lm, nl, tame, r_begin + (int64_t)blockIdx.x * kThreads, r_end,
-                      out_base, a1o, a2o, pixo, counts, landed);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave;
+    const int64_t w0 = r_begin + ((int64_t)blockIdx.x * kWaves + wave) * kWave;
+    double t1[1], t2[1], s1[1], s2[1];
+    // the wave's first ray's row; most waves stay in it
+    const int64_t j0 = w0 / g.nx, i0 = w0 - j0 * g.nx;
+    const bool one_row = i0 + kWave <= g.nx;
+#pragma unroll
+    for (int k = 0; k < 1; ++k) {
+        int64_t i = i0 + lane + kWave * k, j = j0;
+        if (!one_row) {
+            const int64_t r = min(w0 + lane + kWave * k, r_end - 1);
+            j = r / g.nx;
+            i = r - j * g.nx;
+        }
+        t1[k] = ray_x(g, i);
+        t2[k] = ray_y(g, j);
+    }
+    lens_sums<UNIT>(sm, lx, ly, lm, nl, tame, t1, t2, one_row, s1, s2);
+#pragma unroll
+    for (int k = 0; k < 1; ++k) {
+        const int64_t r = w0 + lane + kWave * k;
+        double a1, a2;
+        int32_t pix;
+        assemble(g, t1[k], t2[k], s1[k], s2[k], a1, a2, pix);
+        emit(r < r_end, r - out_base, a1, a2, pix, a1o, a2o, pixo, counts, landed);
+    }
 }
 
 // Blocks: the kBlock columns from a multiple of kBlock of one ray row, in four
@@ -466,7 +504,7 @@ __device__ __forceinline__ void direct_block(Stage64<UNIT> &sm, BlockLds &bl, co
     }
     lens_stages<UNIT>(sm, lx, ly, lm, nl, [&](int cnt) {
         if (!tame) {
-            ray_lenses<UNIT, R>(sm, cnt, tame, n, t1, t2, s1, s2);
+            wild_lenses<UNIT, R>(sm, cnt, n, t1, t2, s1, s2);
         } else if (n == R) {
             row_lenses<UNIT, R>(sm, cnt, t1, t2, s1, s2);
         } else {
@@ -558,14 +596,24 @@ __global__ __launch_bounds__(kThreads, 4) void k_direct_f64_queue(
         }
         const DirectArgs &a = maps[lo];
         const int64_t n = item - item_start[lo];
-        if (a.blocks)
+        if (a.blocks) {
             direct_block<UNIT, 4>(sm, bl, a.g, a.lx, a.ly, a.lm, a.nl, a.tame != 0,
-                                      n * kWaves + __builtin_amdgcn_readfirstlane(tid / kWave),
-                                      a.blocks, a.ray_first, a.ray_last, 0, nullptr, nullptr,
-                                      nullptr, a.counts, a.landed);
-        else
-            direct_rays<UNIT>(sm, a.g, a.lx, a.ly, a.lm, a.nl, a.tame != 0, n * kThreads,
-                              a.ray_last, 0, nullptr, nullptr, nullptr, a.counts, a.landed);
+                                  n * kWaves + __builtin_amdgcn_readfirstlane(tid / kWave),
+                                  a.blocks, a.ray_first, a.ray_last, 0, nullptr, nullptr,
+                                  nullptr, a.counts, a.landed);
+        } else {
+            const DevGeom &g = a.g;
+            const int64_t r = n * kThreads + tid;
+            const bool valid = r < a.ray_last;
+            const int64_t rr = valid ? r : 0;
+            const double t1 = ray_x(g, rr % g.nx), t2 = ray_y(g, rr / g.nx);
+            double s1, s2;
+            lens_sums<UNIT>(sm, a.lx, a.ly, a.lm, a.nl, a.tame != 0, &t1, &t2, false, &s1, &s2);
+            double a1, a2;
+            int32_t pix;
+            assemble(g, t1, t2, s1, s2, a1, a2, pix);
+            emit(valid, 0, a1, a2, pix, nullptr, nullptr, nullptr, a.counts, a.landed);
+        }
     }
 }
 
