@@ -460,10 +460,12 @@ __global__ __launch_bounds__(kThreads) void k_direct_f64(
 // Blocks: the kBlock columns from a multiple of kBlock of one ray row, in four
 // groups of 64 (lane: columns lane + 64 k).  Rays of groups 0 and 1, and of 2 and
 // 3, share a reciprocal where both groups hold columns of the grid, the others
-// take their own, and all take the sheet as the series about the block's middle
-// where sheet_row_series allows it, else in closed form.  Which of these a ray
-// takes, and its partner, depend on the plan and the ray alone, so that maps,
-// bands of rows, ranges of deflections and batches agree bit for bit.
+// take their own, and all take the sheet as the series about the middle of the
+// block's columns where sheet_row_series allows it, else in closed form.  Which of
+// these a ray takes, and its partner, depend on the plan and the ray alone, so
+// that maps, bands of rows, ranges of deflections and batches agree bit for bit
+// (a call of a few rays pays 1 us for the series: 4 rays, 75 lenses 21.6 us
+// against 20.7 with the closed form).
 //
 // A wave takes R of a block's groups: all four, or, for calls of few blocks
 // (kFewBlocks), two.  Bound by FP64 issue: with four rays a lane, per ray and lens
